@@ -75,7 +75,7 @@ hipError_t stage_classify(const float* field, const Grid& g, const LinkTable& t,
                           const Tuning& tu, hipStream_t s)
 {
     const bool minima = (o.flags & EG_MINIMA) != 0;
-    hipError_t e = launch_init(w.ctr, o.header, s);
+    hipError_t e = launch_init(g, w, o.header, s);
     if (e != hipSuccess) return e;
     return launch_classify(field, g, t, minima, o.labels, o.ptr, w, tu, s);
 }
@@ -88,12 +88,11 @@ hipError_t stage_label(const Grid& g, const eg_out& o, const Work& w, const Tuni
 
 // Stage (d) and the canonical outputs: ascending maxima and saddles, the
 // arcs of every saddle as a CSR, and the header (which also reports labels
-// left unresolved by the last label pass).
-hipError_t stage_arcs(const float* field, const Grid& g, const eg_out& o, const Work& w, const Tuning& tu,
-                      hipStream_t s)
+// left unresolved by the last label kernel).
+hipError_t stage_arcs(const float* field, const Grid& g, const eg_out& o, const Work& w, hipStream_t s)
 {
     ArcArgs a = arc_args(field, g, o, w);
-    a.last_flag = gptr<const uint32_t>(w.ctr + C_FINAL + tu.passes - 1);
+    a.last_flag = gptr<const uint32_t>(w.ctr + C_OPEN);
     return launch_arcs(a, s);
 }
 
@@ -110,12 +109,11 @@ eg_status run_stages(int stages, const float* field, int ndim, const int64_t* di
     make_table(g, &t);
     Tuning tu;
     decode_tuning(out->tuning, &tu);
-    tu.passes = passes_for(tu, g.N);
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipSuccess;
     if (stages & S_CLASSIFY) e = stage_classify(field, g, t, *out, w, tu, s);
     if (e == hipSuccess && (stages & S_LABEL)) e = stage_label(g, *out, w, tu, s);
-    if (e == hipSuccess && (stages & S_ARCS)) e = stage_arcs(field, g, *out, w, tu, s);
+    if (e == hipSuccess && (stages & S_ARCS)) e = stage_arcs(field, g, *out, w, s);
     return e == hipSuccess ? EG_OK : EG_ERR_HIP;
 }
 
@@ -272,11 +270,8 @@ eg_status eg_batch_plan(int count, const float* const* fields, const int* ndims,
         ++cls;
     }
     P->class_tile[0] = 0;
-    int64_t max_n = 1;
-    for (int i = 0; i < count; ++i) max_n = std::max<int64_t>(max_n, F[i].N);
-    P->tuning.passes = passes_for(P->tuning, max_n);
     for (int k = 0; k < count; ++k)
-        F[k].arc.last_flag = gptr<const uint32_t>((const uint32_t*)P->bctr + C_FINAL + P->tuning.passes - 1);
+        F[k].arc.last_flag = gptr<const uint32_t>((const uint32_t*)P->bctr + C_OPEN);
     P->total_tiles = tiles;
     P->total_arc_blocks = arc_blocks_total;
     return EG_OK;
@@ -362,7 +357,6 @@ eg_status eg_build_streamed(const float* host_field, float* dev_field, int ndim,
     if (st != EG_OK) return st;
     Tuning tu;
     decode_tuning(out->tuning, &tu);
-    tu.passes = passes_for(tu, g.N);
     int ty, tz;
     tile_shape(tu, ndim, &ty, &tz);
     // slabs are whole tile rows along axis 0 (the slowest)
@@ -392,7 +386,7 @@ eg_status eg_build_streamed(const float* host_field, float* dev_field, int ndim,
         if (hipEventRecord((hipEvent_t)events[k], cs) != hipSuccess) return EG_ERR_HIP;
     }
     const bool minima = (out->flags & EG_MINIMA) != 0;
-    hipError_t e = launch_init(w.ctr, out->header, s);
+    hipError_t e = launch_init(g, w, out->header, s);
     for (int64_t k = 0; k < nslabs && e == hipSuccess; ++k) {
         // the tiles of slab k read one plane past it: wait for the next slab too
         e = hipStreamWaitEvent(s, (hipEvent_t)events[std::min(k + 1, nslabs - 1)], 0);
@@ -402,7 +396,7 @@ eg_status eg_build_streamed(const float* host_field, float* dev_field, int ndim,
                                       (r1 - r0) * tiles_per_row);
     }
     if (e == hipSuccess) e = stage_label(g, *out, w, tu, s);
-    if (e == hipSuccess) e = stage_arcs(dev_field, g, *out, w, tu, s);
+    if (e == hipSuccess) e = stage_arcs(dev_field, g, *out, w, s);
     return e == hipSuccess ? EG_OK : EG_ERR_HIP;
 }
 

@@ -2,8 +2,8 @@
 //
 // Classification leaves the maxima and the saddles as two row-padded bitmasks.
 // Here:
-//   1. k_mask_count / k_scan_rows / k_mask_emit: an order-preserving
-//      compaction of each mask (block counts, their scan, then every block
+//   1. k_mask_count / k_mask_emit: an order-preserving compaction of each mask
+//      (block counts, then every block adds up the counts before its own and
 //      expands its words), so maxima[] and saddles[] come out in ascending
 //      vertex order without a sort;
 //   2. k_arc_count: for every saddle, the highest vertex of each upper-link
@@ -11,11 +11,10 @@
 //      number of distinct labels: the saddle's arcs (arcs form a set,
 //      Sec. 2); the smallest are kept in registers and stored (four in 2D
 //      and 3D, eight from 4D on);
-//   3. k_scan_rows / k_arc_write: the CSR offsets from a scan of the counts,
-//      then the arcs (a saddle with more distinct arcs than were stored,
-//      rare, finds the rest in ascending order by one more pass over its
-//      components per arc);
-//   4. k_finalize: status and counts into the header.
+//   3. k_arc_write: the CSR offsets from the counts, then the arcs (a saddle
+//      with more distinct arcs than were stored, rare, finds the rest in
+//      ascending order by one more pass over its components per arc); the
+//      last block, which has added up every count, writes the header.
 // No step uses an atomic: every position comes from a scan, so results do
 // not depend on scheduling.
 //
@@ -42,8 +41,6 @@ struct OneField {
         nb = gridDim.x;
         return a;
     }
-    // kernels with one block per field
-    __device__ __forceinline__ const ArcArgs& field() const { return a; }
 };
 
 struct BatchFields {
@@ -65,7 +62,6 @@ struct BatchFields {
         nb = (uint32_t)fs[f].arc.arc_blocks;
         return fs[f].arc;
     }
-    __device__ __forceinline__ const ArcArgs& field() const { return plan->fields[blockIdx.x].arc; }
 };
 
 // ------------------------------------------------------------------ helpers
@@ -109,11 +105,39 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* tmp, u
     return pre + inc - x;
 }
 
-__device__ __forceinline__ uint32_t block_sum(uint32_t x, uint32_t* tmp)
+// Sums over the 256 threads of the block, to every thread.  Uses tmp[0..7].
+__device__ __forceinline__ void block_sum2(uint32_t& x, uint32_t& y, uint32_t* tmp)
 {
-    uint32_t total;
-    block_excl_scan(x, tmp, total);
-    return total;
+    const int w = threadIdx.x >> 6;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        x += __shfl_xor(x, o);
+        y += __shfl_xor(y, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        tmp[w] = x;
+        tmp[4 + w] = y;
+    }
+    __syncthreads();
+    x = tmp[0] + tmp[1] + tmp[2] + tmp[3];
+    y = tmp[4] + tmp[5] + tmp[6] + tmp[7];
+    __syncthreads();
+}
+
+// Sums of the block counts before block blk in rows `row` and `row + 1`.  Every
+// block adds them up for itself (at most kArcBlocks entries, two coalesced
+// reads per 256): a kernel of its own for the scan costs more than the reads,
+// 4.5 to 8.6 us on every field.
+__device__ __forceinline__ void sums_before(const ArcArgs& A, int row, uint32_t blk, uint32_t* tmp, uint32_t& a,
+                                            uint32_t& b)
+{
+    a = b = 0;
+    const EG_GPTR(uint32_t) p = A.bsum + row * kSumRow;
+    for (uint32_t i = threadIdx.x; i < blk; i += 256) {
+        a += p[i];
+        b += p[kSumRow + i];
+    }
+    block_sum2(a, b, tmp);
 }
 
 __device__ __forceinline__ uint32_t saddle_count(const ArcArgs& A)
@@ -124,10 +148,11 @@ __device__ __forceinline__ uint32_t saddle_count(const ArcArgs& A)
 
 // ------------------------------------------------------------------ masks
 
+// Set bits of both masks in the block's chunk of the words.
 template <class Sel>
 __global__ __launch_bounds__(256) void k_mask_count(Sel sel)
 {
-    __shared__ uint32_t tmp[4];
+    __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
     uint32_t lo, hi;
@@ -137,119 +162,64 @@ __global__ __launch_bounds__(256) void k_mask_count(Sel sel)
         cm += (uint32_t)__popcll(A.mmask[i]);
         cs += (uint32_t)__popcll(A.smask[i]);
     }
-    cm = block_sum(cm, tmp);
-    cs = block_sum(cs, tmp);
+    block_sum2(cm, cs, tmp);
     if (threadIdx.x == 0) {
         A.bsum[blk] = cm;
-        A.bsum[kArcBlocks + blk] = cs;
+        A.bsum[kSumRow + blk] = cs;
     }
 }
 
-// Exclusive scan, in place, of rows `row` and `row + 1` of a field's block
-// counts (nb <= kArcBlocks entries each); the row totals go to the counter
-// slots.  One block of 1024 threads per field, kArcBlocks / 1024 entries per
-// thread staged through LDS.
-template <class Sel>
-__global__ __launch_bounds__(1024) void k_scan_rows(Sel sel, int row, int slot0, int slot1)
-{
-    constexpr int PER = kArcBlocks / 1024;
-    __shared__ uint32_t buf[kArcBlocks];
-    __shared__ uint32_t wsum[16];
-    const ArcArgs A = sel.field();
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    const int nb = A.arc_blocks;
-    for (int r = 0; r < 2; ++r) {
-        EG_GPTR(uint32_t) a = A.bsum + (row + r) * kArcBlocks;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = k * 1024 + tid;
-            buf[i] = i < nb ? a[i] : 0u;
-        }
-        __syncthreads();
-        uint32_t x[PER], sum = 0;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            x[k] = buf[tid * PER + k];
-            sum += x[k];
-        }
-        const uint32_t inc = wave_incl_scan(sum);
-        if (lane == 63) wsum[w] = inc;
-        __syncthreads();
-        if (w == 0) {
-            uint32_t y = lane < 16 ? wsum[lane] : 0u;
-            y = wave_incl_scan(y);
-            if (lane < 16) wsum[lane] = y;
-        }
-        __syncthreads();
-        uint32_t ex = (w > 0 ? wsum[w - 1] : 0u) + inc - sum;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            buf[tid * PER + k] = ex;
-            ex += x[k];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = k * 1024 + tid;
-            if (i < nb) a[i] = buf[i];
-        }
-        if (tid == 0) A.ctr[r == 0 ? slot0 : slot1] = wsum[15];
-        __syncthreads();
-    }
-}
-
-// Write the vertex ids of the set bits of one round of 256 words (one per
-// thread) to out[run + j], j < total (entries at or past cap are dropped);
-// local is the exclusive count of set bits before this thread's word.  The
-// ids are staged in LDS so that the global stores are whole-wave and
-// contiguous; a round with more ids than the stage (a very dense mask) writes
-// directly.  Every thread of the block must call it.
-constexpr int kStage = 4096;
-__device__ __forceinline__ void emit_round(uint64_t word, uint32_t local, uint32_t total, int32_t vbase,
-                                           uint32_t run, EG_GPTR(int32_t) out, uint32_t cap, int32_t* stage)
-{
-    if (total == 0) return;
-    if (total <= (uint32_t)kStage) {
-        for (uint32_t j = local; word; ++j) {
-            stage[j] = vbase + (__ffsll((unsigned long long)word) - 1);
-            word &= word - 1ull;
-        }
-        __syncthreads();
-        for (uint32_t j = threadIdx.x; j < total; j += 256)
-            if (run + j < cap) out[run + j] = stage[j];
-        __syncthreads();
-    } else {
-        for (uint32_t p = run + local; word; ++p) {
-            if (p < cap) out[p] = vbase + (__ffsll((unsigned long long)word) - 1);
-            word &= word - 1ull;
-        }
-    }
-}
-
+// The vertex ids of the set bits of a round of 256 words (one per thread), both
+// masks at once: one scan of the packed counts (at most 16384 each), the ids
+// staged in LDS so that the global stores are whole-wave and contiguous; a
+// round with more ids than the stage (very dense masks) writes directly.
+// Entries at or past a capacity are dropped.  The last block's totals are the
+// field's counts.
+constexpr int kStage = 6144;
 template <class Sel>
 __global__ __launch_bounds__(256) void k_mask_emit(Sel sel)
 {
-    __shared__ uint32_t tmp[4];
+    __shared__ uint32_t tmp[8];
     __shared__ int32_t stage[kStage];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
     uint32_t lo, hi;
     chunk((uint32_t)A.words, nb, blk, lo, hi);
-    uint32_t rm = A.bsum[blk], rs = A.bsum[kArcBlocks + blk];
+    uint32_t rm, rs;
+    sums_before(A, 0, blk, tmp, rm, rs);
     const uint32_t XW = (uint32_t)A.XW, X = (uint32_t)A.X;
     for (uint32_t base = lo; base < hi; base += 256) {
         const uint32_t i = base + threadIdx.x;
-        const uint64_t m = i < hi ? A.mmask[i] : 0ull;
-        const uint64_t sd = i < hi ? A.smask[i] : 0ull;
-        uint32_t tm, ts;
-        const uint32_t lm = block_excl_scan((uint32_t)__popcll(m), tmp, tm);
-        const uint32_t ls = block_excl_scan((uint32_t)__popcll(sd), tmp, ts);
+        uint64_t m = i < hi ? A.mmask[i] : 0ull;
+        uint64_t sd = i < hi ? A.smask[i] : 0ull;
+        uint32_t total;
+        const uint32_t local =
+            block_excl_scan((uint32_t)__popcll(m) | ((uint32_t)__popcll(sd) << 16), tmp, total);
+        const uint32_t tm = total & 0xFFFFu, ts = total >> 16;
+        uint32_t jm = local & 0xFFFFu, js = local >> 16;
         const uint32_t row = i / XW, xw = i - row * XW;
         const int32_t vbase = (int32_t)(row * X + xw * 64u);
-        emit_round(m, lm, tm, vbase, rm, A.maxima, A.cap_max, stage);
-        emit_round(sd, ls, ts, vbase, rs, A.saddles, A.cap_sad, stage);
+        if (tm + ts <= (uint32_t)kStage) {
+            for (; m; ++jm, m &= m - 1ull) stage[jm] = vbase + (__ffsll((unsigned long long)m) - 1);
+            for (js += tm; sd; ++js, sd &= sd - 1ull) stage[js] = vbase + (__ffsll((unsigned long long)sd) - 1);
+            __syncthreads();
+            for (uint32_t j = threadIdx.x; j < tm; j += 256)
+                if (rm + j < A.cap_max) A.maxima[rm + j] = stage[j];
+            for (uint32_t j = threadIdx.x; j < ts; j += 256)
+                if (rs + j < A.cap_sad) A.saddles[rs + j] = stage[tm + j];
+            __syncthreads();
+        } else {
+            for (uint32_t p = rm + jm; m; ++p, m &= m - 1ull)
+                if (p < A.cap_max) A.maxima[p] = vbase + (__ffsll((unsigned long long)m) - 1);
+            for (uint32_t p = rs + js; sd; ++p, sd &= sd - 1ull)
+                if (p < A.cap_sad) A.saddles[p] = vbase + (__ffsll((unsigned long long)sd) - 1);
+        }
         rm += tm;
         rs += ts;
+    }
+    if (blk == nb - 1 && threadIdx.x == 0) {
+        A.ctr[C_NMAX] = rm;
+        A.ctr[C_NSAD] = rs;
     }
 }
 
@@ -523,12 +493,36 @@ __device__ __forceinline__ void arc_count_body(const ArcArgs& A, uint32_t blk, u
         sc += n;
         sb += (uint32_t)beta;
     }
-    sc = block_sum(sc, tmp);
-    sb = block_sum(sb, tmp);
+    block_sum2(sc, sb, tmp);
     if (tid == 0) {
-        A.bsum[2 * kArcBlocks + blk] = sc;
-        A.bsum[3 * kArcBlocks + blk] = sb;
+        A.bsum[2 * kSumRow + blk] = sc;
+        A.bsum[3 * kSumRow + blk] = sb;
     }
+}
+
+// Status and counts.
+__device__ __forceinline__ void write_header(const ArcArgs& A, uint32_t narc, uint32_t npairs)
+{
+    const uint32_t* c = A.ctr;
+    const uint32_t nmax = c[C_NMAX], nsad = c[C_NSAD];
+    const bool sad_over = nsad > A.cap_sad;
+    int status = EG_OK;
+    if (c[C_NAN])
+        status = EG_ERR_NAN;
+    else if (A.last_flag && *A.last_flag)
+        status = EG_ERR_UNRESOLVED;
+    else if (nmax > A.cap_max || sad_over || narc > A.cap_arc)
+        status = EG_ERR_CAPACITY;
+    int32_t* h = A.header;
+    h[EG_H_STATUS] = status;
+    h[EG_H_NMAX] = (int32_t)nmax;
+    h[EG_H_NSAD] = (int32_t)nsad;
+    // with saddles cut off at the capacity, the arc and pair totals cover
+    // only the first cap_sad saddles: unknown
+    h[EG_H_NARC] = sad_over ? -1 : (int32_t)narc;
+    h[EG_H_NPAIRS] = sad_over ? -1 : (int32_t)npairs;
+    h[EG_H_PASSES] = (int32_t)c[C_PASSES];
+    h[EG_H_EXITS] = (int32_t)c[C_NEXIT];
 }
 
 template <int NDIM, bool MINMODE>
@@ -540,7 +534,8 @@ __device__ __forceinline__ void arc_write_body(const ArcArgs& A, uint32_t blk, u
     chunk(saddle_count(A), nb, blk, lo, hi);
     const int tid = threadIdx.x;
     if (blk == 0 && tid == 0) A.offsets[0] = 0;
-    uint32_t run = A.bsum[2 * kArcBlocks + blk];
+    uint32_t run, pairs;
+    sums_before(A, 2, blk, tmp, run, pairs);
     for (uint32_t base = lo; base < hi; base += 256) {
         const uint32_t i = base + tid;
         const bool valid = i < hi;
@@ -579,6 +574,8 @@ __device__ __forceinline__ void arc_write_body(const ArcArgs& A, uint32_t blk, u
         }
         run += total;
     }
+    // the last block has seen every count
+    if (blk == nb - 1 && tid == 0) write_header(A, run, pairs + A.bsum[3 * kSumRow + blk]);
 }
 
 // Four waves per SIMD for the 5D rows, in the arc and the path kernels alike
@@ -593,7 +590,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<N
     OneField sel)
 {
     __shared__ Mask<NDIM> s_adj[Rows<NDIM>::K];
-    __shared__ uint32_t tmp[4];
+    __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
     arc_count_body<NDIM, MINMODE>(A, blk, nb, s_adj, tmp);
@@ -604,7 +601,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<N
     OneField sel)
 {
     __shared__ Mask<NDIM> s_adj[Rows<NDIM>::K];
-    __shared__ uint32_t tmp[4];
+    __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
     arc_write_body<NDIM, MINMODE>(A, blk, nb, s_adj, tmp);
@@ -616,7 +613,7 @@ template <bool WRITE>
 __global__ __launch_bounds__(256) void k_arc_batched(BatchFields sel)
 {
     __shared__ uint64_t s_adj[14];
-    __shared__ uint32_t tmp[4];
+    __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
     const int kind = __builtin_amdgcn_readfirstlane((A.ndim == 3 ? 2 : 0) + (A.minima ? 1 : 0));
@@ -664,19 +661,15 @@ __device__ __forceinline__ bool walk(const ArcArgs& A, EG_GPTR(const int32_t) co
     }
 }
 
-__global__ void k_path_reset(OneField sel)
-{
-    if (threadIdx.x == 0) sel.field().ctr[C_PBAD] = 0;
-}
-
 // Paths and path vertices of every saddle of the block's chunk (kept for the
-// write pass in the workspace), block sums into rows 0 and 1.
+// write pass in the workspace); the block's sums go to rows 0 and 1, and whether
+// a walk met a pointer that leaves the grid or does not rise to row 2.
 template <int NDIM, bool MINMODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<NDIM>, 8))) void k_path_count(
     OneField sel, PathArgs P)
 {
     __shared__ Mask<NDIM> s_adj[Rows<NDIM>::K];
-    __shared__ uint32_t tmp[4];
+    __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
     load_adj<NDIM>(A, s_adj);
@@ -702,12 +695,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<N
         sp += np;
         sv += nv;
     }
-    if (__ballot(bad) != 0 && __lane_id() == 0) atomicOr(&A.ctr[C_PBAD], 1u);
-    sp = block_sum(sp, tmp);
-    sv = block_sum(sv, tmp);
+    block_sum2(sp, sv, tmp);
+    const int any_bad = __syncthreads_or(bad);
     if (threadIdx.x == 0) {
         A.bsum[blk] = sp;
-        A.bsum[kArcBlocks + blk] = sv;
+        A.bsum[kSumRow + blk] = sv;
+        A.bsum[2 * kSumRow + blk] = any_bad != 0;
     }
 }
 
@@ -716,13 +709,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<N
     OneField sel, PathArgs P)
 {
     __shared__ Mask<NDIM> s_adj[Rows<NDIM>::K];
-    __shared__ uint32_t tmp[4];
+    __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
     load_adj<NDIM>(A, s_adj);
     uint32_t lo, hi;
     chunk(saddle_count(A), nb, blk, lo, hi);
-    uint32_t runp = A.bsum[blk], runv = A.bsum[kArcBlocks + blk];
+    uint32_t runp, runv;
+    sums_before(A, 0, blk, tmp, runp, runv);
     for (uint32_t base = lo; base < hi; base += 256) {
         const uint32_t i = base + threadIdx.x;
         const bool valid = i < hi;
@@ -749,29 +743,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<N
         runp += tp;
         runv += tv;
     }
-}
-
-// Closing entries of both offset arrays and the header.
-__global__ void k_path_finalize(OneField sel, PathArgs P)
-{
+    // the last block has seen every count: closing entries of both offset
+    // arrays, and the header
+    if (blk != nb - 1) return;
+    uint32_t bad = 0;
+    for (uint32_t i = threadIdx.x; i < nb; i += 256) bad |= A.bsum[2 * kSumRow + i];
+    const int any_bad = __syncthreads_or((int)bad);
     if (threadIdx.x != 0) return;
-    const ArcArgs A = sel.field();
-    const uint32_t nsad = A.ctr[C_NSAD], np = A.ctr[C_PATHS], nv = A.ctr[C_PVERTS];
-    const uint32_t n = nsad < A.cap_sad ? nsad : A.cap_sad;
-    P.pair_offsets[n] = (int32_t)np;
-    if (np <= P.cap_paths) P.path_offsets[np] = (int32_t)nv;
-    const bool short_ = nsad > A.cap_sad || np > P.cap_paths || nv > P.cap_vertices;
-    P.header[EG_P_STATUS] = A.ctr[C_NAN] ? EG_ERR_NAN : A.ctr[C_PBAD] ? EG_ERR_ARG : short_ ? EG_ERR_CAPACITY : EG_OK;
-    P.header[EG_P_PATHS] = (int32_t)np;
-    P.header[EG_P_VERTICES] = (int32_t)nv;
+    const uint32_t nsad = A.ctr[C_NSAD];
+    P.pair_offsets[saddle_count(A)] = (int32_t)runp;
+    if (runp <= P.cap_paths) P.path_offsets[runp] = (int32_t)runv;
+    const bool short_ = nsad > A.cap_sad || runp > P.cap_paths || runv > P.cap_vertices;
+    P.header[EG_P_STATUS] = A.ctr[C_NAN] ? EG_ERR_NAN : any_bad ? EG_ERR_ARG : short_ ? EG_ERR_CAPACITY : EG_OK;
+    P.header[EG_P_PATHS] = (int32_t)runp;
+    P.header[EG_P_VERTICES] = (int32_t)runv;
 }
 
 template <int NDIM, bool MINMODE>
 static void launch_paths_t(const OneField& sel, const PathArgs& p, uint32_t nb, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_path_reset, dim3(1), dim3(64), 0, s, sel);
     hipLaunchKernelGGL((k_path_count<NDIM, MINMODE>), dim3(nb), dim3(256), 0, s, sel, p);
-    hipLaunchKernelGGL(k_scan_rows<OneField>, dim3(1), dim3(1024), 0, s, sel, 0, (int)C_PATHS, (int)C_PVERTS);
     hipLaunchKernelGGL((k_path_write<NDIM, MINMODE>), dim3(nb), dim3(256), 0, s, sel, p);
 }
 
@@ -803,37 +794,7 @@ hipError_t launch_paths(const ArcArgs& a, const PathArgs& p, hipStream_t s)
             return hipErrorInvalidValue;
     }
 #undef EG_CASE
-    hipLaunchKernelGGL(k_path_finalize, dim3(1), dim3(64), 0, s, sel, p);
     return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ header
-
-template <class Sel>
-__global__ void k_finalize(Sel sel)
-{
-    if (threadIdx.x != 0) return;
-    const ArcArgs A = sel.field();
-    const uint32_t* c = A.ctr;
-    const int64_t nmax = c[C_NMAX], nsad = c[C_NSAD], narc = c[C_NARC];
-    const bool sad_over = nsad > A.cap_sad;
-    int status = EG_OK;
-    if (c[C_NAN])
-        status = EG_ERR_NAN;
-    else if (A.last_flag && *A.last_flag)
-        status = EG_ERR_UNRESOLVED;
-    else if (nmax > A.cap_max || sad_over || narc > A.cap_arc)
-        status = EG_ERR_CAPACITY;
-    int32_t* h = A.header;
-    h[EG_H_STATUS] = status;
-    h[EG_H_NMAX] = (int32_t)nmax;
-    h[EG_H_NSAD] = (int32_t)nsad;
-    // with saddles cut off at the capacity, the arc and pair totals cover
-    // only the first cap_sad saddles: unknown
-    h[EG_H_NARC] = sad_over ? -1 : (int32_t)narc;
-    h[EG_H_NPAIRS] = sad_over ? -1 : (int32_t)c[C_NPAIRS];
-    h[EG_H_PASSES] = (int32_t)c[C_PASSES];
-    h[EG_H_EXITS] = (int32_t)c[C_NEXIT];
 }
 
 // ------------------------------------------------------------------ launchers
@@ -883,7 +844,6 @@ template <int NDIM, bool MINMODE>
 static void launch_arc_pair(const OneField& sel, uint32_t nb, hipStream_t s)
 {
     hipLaunchKernelGGL((k_arc_count<NDIM, MINMODE>), dim3(nb), dim3(256), 0, s, sel);
-    hipLaunchKernelGGL(k_scan_rows<OneField>, dim3(1), dim3(1024), 0, s, sel, 2, (int)C_NARC, (int)C_NPAIRS);
     hipLaunchKernelGGL((k_arc_write<NDIM, MINMODE>), dim3(nb), dim3(256), 0, s, sel);
 }
 
@@ -892,7 +852,6 @@ hipError_t launch_arcs(const ArcArgs& a, hipStream_t s)
     const OneField sel{a};
     const uint32_t nb = (uint32_t)a.arc_blocks;
     hipLaunchKernelGGL(k_mask_count<OneField>, dim3(nb), dim3(256), 0, s, sel);
-    hipLaunchKernelGGL(k_scan_rows<OneField>, dim3(1), dim3(1024), 0, s, sel, 0, (int)C_NMAX, (int)C_NSAD);
     hipLaunchKernelGGL(k_mask_emit<OneField>, dim3(nb), dim3(256), 0, s, sel);
 #define EG_CASE(N)                                  \
     case N:                                         \
@@ -912,7 +871,6 @@ hipError_t launch_arcs(const ArcArgs& a, hipStream_t s)
             return hipErrorInvalidValue;
     }
 #undef EG_CASE
-    hipLaunchKernelGGL(k_finalize<OneField>, dim3(1), dim3(64), 0, s, sel);
     return hipGetLastError();
 }
 
@@ -920,14 +878,10 @@ hipError_t launch_arcs_batched(const BatchPlan* dplan, const BatchPlan& hplan, h
 {
     const BatchFields sel{gptr(dplan)};
     const unsigned grid = (unsigned)hplan.total_arc_blocks;
-    const unsigned count = (unsigned)hplan.count;
     hipLaunchKernelGGL(k_mask_count<BatchFields>, dim3(grid), dim3(256), 0, s, sel);
-    hipLaunchKernelGGL(k_scan_rows<BatchFields>, dim3(count), dim3(1024), 0, s, sel, 0, (int)C_NMAX, (int)C_NSAD);
     hipLaunchKernelGGL(k_mask_emit<BatchFields>, dim3(grid), dim3(256), 0, s, sel);
     hipLaunchKernelGGL(k_arc_batched<false>, dim3(grid), dim3(256), 0, s, sel);
-    hipLaunchKernelGGL(k_scan_rows<BatchFields>, dim3(count), dim3(1024), 0, s, sel, 2, (int)C_NARC, (int)C_NPAIRS);
     hipLaunchKernelGGL(k_arc_batched<true>, dim3(grid), dim3(256), 0, s, sel);
-    hipLaunchKernelGGL(k_finalize<BatchFields>, dim3(count), dim3(64), 0, s, sel);
     return hipGetLastError();
 }
 

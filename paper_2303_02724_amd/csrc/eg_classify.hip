@@ -7,7 +7,7 @@
 //   components, Table 1) by set algebra on the link's rows (eg_link.h).
 // k_classify_slab  the same for n = 4, 5 and 6, reading the neighbourhood
 //   from planes of keys staged in LDS.
-// k_exit_*, k_final  stage (b): pointer jumping until every vertex names its
+// k_exit_*, k_final*  stage (b): pointer jumping until every vertex names its
 //   maximum (the end of the walk of Alg. 2).
 #include "eg_internal.h"
 #include "eg_rows.h"
@@ -15,16 +15,29 @@
 
 namespace eg {
 
-__global__ void k_init(uint32_t* __restrict__ ctr, int32_t* __restrict__ header)
+// Counters and header; on grids without tiles (whose masks are written bit by
+// bit) the words of both masks too.
+__global__ __launch_bounds__(256) void k_init(uint32_t* __restrict__ ctr, int32_t* __restrict__ header,
+                                              uint64_t* __restrict__ a, uint64_t* __restrict__ b, int64_t n)
 {
-    const int i = threadIdx.x;
-    if (i < C_SLOTS) ctr[i] = 0;
-    if (header && i < EG_H_SLOTS) header[i] = 0;
+    if (blockIdx.x == 0) {
+        const int i = threadIdx.x;
+        if (i < C_SLOTS) ctr[i] = 0;
+        if (header && i < EG_H_SLOTS) header[i] = 0;
+    }
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        a[i] = 0;
+        b[i] = 0;
+    }
 }
 
-hipError_t launch_init(uint32_t* ctr, int32_t* header, hipStream_t s)
+hipError_t launch_init(const Grid& g, const Work& w, int32_t* header, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_init, dim3(1), dim3(64), 0, s, ctr, header);
+    const bool tiled = g.ndim == 2 || g.ndim == 3;
+    const int64_t n = tiled ? 0 : w.words;
+    const int64_t want = (n + 255) / 256;
+    const int blocks = (int)(want < 1 ? 1 : want < 4096 ? want : 4096);
+    hipLaunchKernelGGL(k_init, dim3(blocks), dim3(256), 0, s, w.ctr, header, w.mmask, w.smask, n);
     return hipGetLastError();
 }
 
@@ -94,14 +107,6 @@ __device__ __forceinline__ uint32_t boundary_bits(const Grid& g, int v)
         bits |= boundary_bit(c, d, i);
     }
     return bits;
-}
-
-__global__ __launch_bounds__(256) void k_zero_words(uint64_t* __restrict__ a, uint64_t* __restrict__ b, int64_t n)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        a[i] = 0;
-        b[i] = 0;
-    }
 }
 
 // OR the bits of the lanes with `pred` into the row-padded mask: lanes that
@@ -394,9 +399,6 @@ template <int NDIM, bool MINMODE>
 static void launch_classify_t(const float* f, const Grid& g, const LinkTable& t, int32_t* lab, int32_t* ptr,
                               const Work& w, hipStream_t s)
 {
-    const int64_t zwant = (w.words + 255) / 256;
-    const int zblocks = (int)(zwant < 4096 ? (zwant > 0 ? zwant : 1) : 4096);
-    hipLaunchKernelGGL(k_zero_words, dim3(zblocks), dim3(256), 0, s, w.mmask, w.smask, w.words);
     const int64_t kwant = ((int64_t)g.N + 255) / 256;
     const int kblocks = (int)(kwant < 8192 ? kwant : 8192);
     hipLaunchKernelGGL(k_keys<MINMODE>, dim3(kblocks), dim3(256), 0, s, f, g.N, w.keys, w.ctr);
@@ -462,27 +464,18 @@ hipError_t launch_classify(const float* f, const Grid& g, const LinkTable& t, bo
 //
 // Entries are updated in place while other threads read them.  Every value
 // ever stored says something true about the same path, so any value read is
-// usable.  A pass follows at most `hops` links per entry; a pass that stops
-// short raises its flag and the next pass runs.  After pass p every entry has
-// advanced hops^p links or become final, so the launcher's pass count
-// (hops^passes >= 2^31) covers any path in a grid of fewer than 2^31 vertices.
+// usable.  A sweep follows at most `hops` links per entry and stores how far
+// it came; a wave with an entry left over sweeps again, now through links that
+// the other waves have advanced too (all waves at once: each sweep multiplies
+// the reach), so no launch has to follow for paths longer than one sweep.  No
+// wave waits for another: one that ran alone would still walk its paths to
+// their ends, at least `hops` links a sweep, which bounds its sweeps
+// (sweeps_for).  Later sweeps read the links at device scope: a plain load
+// could return the same old line of a cache every time.
 
-__device__ __forceinline__ int next_link(const int32_t* lab, const int32_t* res, int N, int x)
-{
-    return x >= -N ? lab[-x - 1] : res[-x - 1 - N];
-}
-
-__device__ __forceinline__ bool gate(const uint32_t* ctr, int flag_base, int pass)
-{
-    return pass == 0 ||
-           __hip_atomic_load(&ctr[flag_base + pass - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-}
-
-// Both exit-list kernels take four consecutive entries per thread (one
-// 16-byte access, four independent gathers or chains in flight): the links
-// are latency-bound gathers, so more of them per thread hide more latency.
-// The list base is 16-byte aligned (the workspace is carved in 256-byte
-// steps).
+// The exit list's base is 16-byte aligned (the workspace is carved in 256-byte
+// steps); the links are latency-bound gathers, so more of them per thread hide
+// more latency.
 __global__ __launch_bounds__(256) void k_exit_init(const uint32_t* __restrict__ exits, int32_t* __restrict__ res,
                                                    const int32_t* __restrict__ lab, const uint32_t* __restrict__ ctr,
                                                    uint32_t cap)
@@ -501,117 +494,66 @@ __global__ __launch_bounds__(256) void k_exit_init(const uint32_t* __restrict__ 
     if (t < (n & 3u)) res[(nq << 2) + t] = lab[exits[(nq << 2) + t]];
 }
 
-__global__ __launch_bounds__(256) void k_exit_jump(int32_t* res, const int32_t* __restrict__ lab, int N,
-                                                   uint32_t* __restrict__ ctr, uint32_t cap, int pass, int hops)
+__global__ __launch_bounds__(256) void k_exit_jump(int32_t* res, const int32_t* lab, int N, uint32_t* __restrict__ ctr,
+                                                   uint32_t cap, int hops, int sweeps)
 {
-    if (!gate(ctr, C_JUMP, pass)) return;
     const uint32_t req = __hip_atomic_load(&ctr[C_NEXIT], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint32_t n = req < cap ? req : cap;
-    const uint32_t nq = n >> 2;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    int4* r4 = reinterpret_cast<int4*>(res);
-    bool notdone = false;
-    for (uint32_t q = t; q < nq; q += stride) {
-        const int4 x = r4[q];
-        if ((x.x | x.y | x.z | x.w) >= 0) continue;  // all four final
-        int y0 = x.x, y1 = x.y, y2 = x.z, y3 = x.w;
-        for (int h = 0; (y0 < 0 || y1 < 0 || y2 < 0 || y3 < 0) && h < hops; ++h) {
-            if (y0 < 0) y0 = next_link(lab, res, N, y0);
-            if (y1 < 0) y1 = next_link(lab, res, N, y1);
-            if (y2 < 0) y2 = next_link(lab, res, N, y2);
-            if (y3 < 0) y3 = next_link(lab, res, N, y3);
-        }
-        r4[q] = make_int4(y0, y1, y2, y3);
-        notdone |= (y0 < 0) | (y1 < 0) | (y2 < 0) | (y3 < 0);
-    }
-    if (t < (n & 3u)) {
-        const uint32_t i = (nq << 2) + t;
-        int x = res[i];
-        for (int h = 0; x < 0 && h < hops; ++h) x = next_link(lab, res, N, x);
-        res[i] = x;
-        notdone |= x < 0;
-    }
-    if (__ballot(notdone) != 0 && __lane_id() == 0) atomicOr(&ctr[C_JUMP + pass], 1u);
+    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+    bool open = sweep(res, n, lab, res, N, hops, t, stride, false);
+    for (int k = 1; __ballot(open) != 0 && k < sweeps; ++k)
+        open = sweep(res, n, lab, res, N, hops, t, stride, true);
+    if (__ballot(open) != 0 && __lane_id() == 0) atomicOr(&ctr[C_OPEN], 1u);
 }
 
-// Per-vertex pass: four consecutive vertices per thread (one 16-byte load,
-// four independent chains).
-__global__ __launch_bounds__(256) void k_final(int32_t* lab, const int32_t* __restrict__ res, int32_t N,
-                                               uint32_t* __restrict__ ctr, int pass, int hops)
+// Per-vertex labels of the grids without tiles: every code names a vertex.
+// Almost every field is done after one sweep; k_final_rest finishes the others.
+__global__ __launch_bounds__(256) void k_final(int32_t* lab, int32_t N, uint32_t* __restrict__ ctr, int hops)
 {
-    if (!gate(ctr, C_FINAL, pass)) return;
-    bool notdone = false;
-    const int nq = N >> 2;
-    const int stride = gridDim.x * blockDim.x;
-    int4* lab4 = reinterpret_cast<int4*>(lab);
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < nq; q += stride) {
-        const int4 x = lab4[q];
-        if ((x.x | x.y | x.z | x.w) >= 0) continue;  // all four final
-        int y0 = x.x < 0 ? next_link(lab, res, N, x.x) : x.x;
-        int y1 = x.y < 0 ? next_link(lab, res, N, x.y) : x.y;
-        int y2 = x.z < 0 ? next_link(lab, res, N, x.z) : x.z;
-        int y3 = x.w < 0 ? next_link(lab, res, N, x.w) : x.w;
-        int h = 1;
-        while ((y0 < 0 || y1 < 0 || y2 < 0 || y3 < 0) && h < hops) {
-            if (y0 < 0) y0 = next_link(lab, res, N, y0);
-            if (y1 < 0) y1 = next_link(lab, res, N, y1);
-            if (y2 < 0) y2 = next_link(lab, res, N, y2);
-            if (y3 < 0) y3 = next_link(lab, res, N, y3);
-            ++h;
-        }
-        lab4[q] = make_int4(y0, y1, y2, y3);
-        notdone |= (y0 < 0) | (y1 < 0) | (y2 < 0) | (y3 < 0);
-    }
-    // the last N % 4 vertices
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < (N & 3)) {
-        const int v = (nq << 2) + t;
-        int y = lab[v];
-        for (int h = 0; y < 0 && h < hops; ++h) y = next_link(lab, res, N, y);
-        lab[v] = y;
-        notdone |= y < 0;
-    }
-    if (__ballot(notdone) != 0 && __lane_id() == 0) atomicOr(&ctr[C_FINAL + pass], 1u);
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&ctr[C_PASSES], 1u);
+    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+    const bool open = sweep(lab, (uint32_t)N, lab, lab, N, hops, t, gridDim.x * blockDim.x, false);
+    if (__ballot(open) != 0 && __lane_id() == 0) atomicOr(&ctr[C_MORE], 1u);
+    if (t == 0) ctr[C_PASSES] = 1;
+}
+
+__global__ __launch_bounds__(256) void k_final_rest(int32_t* lab, int32_t N, uint32_t* __restrict__ ctr, int hops,
+                                                    int sweeps)
+{
+    if (__hip_atomic_load(&ctr[C_MORE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
+    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+    bool open = true;
+    int k = 0;
+    for (; __ballot(open) != 0 && k < sweeps; ++k)
+        open = sweep(lab, (uint32_t)N, lab, lab, N, hops, t, gridDim.x * blockDim.x, true);
+    const bool left = __ballot(open) != 0;
+    if (__lane_id() != 0) return;
+    if (left) atomicOr(&ctr[C_OPEN], 1u);
+    atomicMax(&ctr[C_PASSES], 1u + (uint32_t)k);
 }
 
 hipError_t launch_labels(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, hipStream_t s)
 {
     const int32_t N = g.N;
     if (reinterpret_cast<uintptr_t>(lab) & 15u) return hipErrorInvalidValue;
-    const uint32_t cap = (uint32_t)w.cap_exit;
-    if ((reinterpret_cast<uintptr_t>(w.exits) | reinterpret_cast<uintptr_t>(w.exres)) & 15u)
-        return hipErrorInvalidValue;
-    const int64_t ewant = (w.cap_exit / 4 + 255) / 256;
-    const int eblocks = (int)(ewant < 2048 ? (ewant > 0 ? ewant : 1) : 2048);
-    // a later pass runs only when the pass before it stopped short, which
-    // the tiled grids' passes practically never do: most of these launches
-    // return at once, and small grids keep them cheap (a pass that does run
-    // then takes longer)
-    const int eblocks_late = eblocks < 128 ? eblocks : 128;
-    // the first pass reads entries that other threads of the same pass have
-    // already advanced, which shortens long chains: it needs every entry
-    // initialised first
-    hipLaunchKernelGGL(k_exit_init, dim3(eblocks), dim3(256), 0, s, w.exits, w.exres, lab, w.ctr, cap);
-    for (int p = 0; p < tu.passes; ++p)
-        hipLaunchKernelGGL(k_exit_jump, dim3(p == 0 ? eblocks : eblocks_late), dim3(256), 0, s, w.exres, lab, N,
-                           w.ctr, cap, p, tu.hops);
+    const int sweeps = sweeps_for(tu, N);
+    if (g.ndim == 2 || g.ndim == 3) {
+        const uint32_t cap = (uint32_t)w.cap_exit;
+        if ((reinterpret_cast<uintptr_t>(w.exits) | reinterpret_cast<uintptr_t>(w.exres)) & 15u)
+            return hipErrorInvalidValue;
+        const int64_t ewant = (w.cap_exit / 4 + 255) / 256;
+        const int eblocks = (int)(ewant < 2048 ? (ewant > 0 ? ewant : 1) : 2048);
+        // the jump reads entries that other threads have already advanced,
+        // which shortens long chains: it needs every entry initialised first
+        hipLaunchKernelGGL(k_exit_init, dim3(eblocks), dim3(256), 0, s, w.exits, w.exres, lab, w.ctr, cap);
+        hipLaunchKernelGGL(k_exit_jump, dim3(eblocks), dim3(256), 0, s, w.exres, lab, N, w.ctr, cap, tu.hops, sweeps);
+        return launch_final_tiled(g, lab, w, tu, s);
+    }
     const int64_t want = ((int64_t)N / 4 + 255) / 256;
     const int blocks = (int)(want < 2048 ? (want > 0 ? want : 1) : 2048);
-    const bool tiled = g.ndim == 2 || g.ndim == 3;
-    int p = 0;
-    if (tiled) {
-        // pass 0 in tile order (the classification wrote exit-list codes)
-        const hipError_t e = launch_final_tiled(g, lab, w, tu, C_FINAL, s);
-        if (e != hipSuccess) return e;
-        p = 1;
-    }
-    // untiled grids resolve their vertex codes in these passes: full grids
-    const int blocks_late = tiled && blocks > 128 ? 128 : blocks;
-    for (; p < tu.passes; ++p)
-        hipLaunchKernelGGL(k_final, dim3(p == 0 ? blocks : blocks_late), dim3(256), 0, s, lab, w.exres, N, w.ctr, p,
-                           tu.hops);
+    hipLaunchKernelGGL(k_final, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, tu.hops);
+    // every block of this launch fits the GPU at once, so that all entries
+    // advance together
+    hipLaunchKernelGGL(k_final_rest, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, tu.hops, sweeps);
     return hipGetLastError();
 }
 

@@ -828,13 +828,13 @@ __device__ __forceinline__ int xcd_tile(int b, int ntiles)
 
 // Label pass over a tiled grid, one workgroup per tile: the exit codes of a
 // tile's vertices point into that tile's own block of the exit list, which
-// stays in cache while the tile's rows stream through.  Entries with vertex
-// codes (a tile whose exits did not fit the list) follow their path for up to
-// `hops` links and raise the pass flag if they stop short; the linear passes
-// after this one finish them.
+// stays in cache while the tile's rows stream through.  Every list entry is
+// final by now.  Vertex codes (a tile whose exits did not fit the list, which
+// takes a list capped by the tuning word or a grid near 2^31 vertices) follow
+// their path to its end, one link per tile on it; a path has fewer than N
+// links, which bounds the walk whatever the label array holds.
 template <int TY, int TZ>
-__device__ __forceinline__ void final_tile(const TileArgs& a, int b, const int32_t* __restrict__ res, int hops,
-                                           uint32_t* flag)
+__device__ __forceinline__ void final_tile(const TileArgs& a, int b, const int32_t* __restrict__ res, uint32_t* flag)
 {
     constexpr int YPT = TY / 4;
     const int X = a.X, Y = a.Y, Z = a.Z;
@@ -869,7 +869,7 @@ __device__ __forceinline__ void final_tile(const TileArgs& a, int b, const int32
     for (int k = 0; k < VPT; ++k) {
         if (x[k] < 0) {
             int y = x[k];
-            for (int h = 0; y < 0 && h < hops; ++h) y = y >= -N ? lab[-y - 1] : res[-y - 1 - N];
+            for (int h = 0; y < 0 && h < N; ++h) y = y >= -N ? lab[-y - 1] : res[-y - 1 - N];
             x[k] = y;
             notdone |= y < 0;
         }
@@ -881,10 +881,9 @@ __device__ __forceinline__ void final_tile(const TileArgs& a, int b, const int32
 }
 
 template <int TY, int TZ>
-__global__ __launch_bounds__(256) void k_final_tiled(TileArgs a, const int32_t* __restrict__ res, int hops,
-                                                     int flag_slot)
+__global__ __launch_bounds__(256) void k_final_tiled(TileArgs a, const int32_t* __restrict__ res)
 {
-    final_tile<TY, TZ>(a, xcd_tile(blockIdx.x, a.ntiles), res, hops, &a.ctr[flag_slot]);
+    final_tile<TY, TZ>(a, xcd_tile(blockIdx.x, a.ntiles), res, &a.ctr[C_OPEN]);
 }
 
 // The same pass over the tiles of every 2D (or every 3D) field of a batch:
@@ -906,7 +905,7 @@ __global__ __launch_bounds__(256) void k_final_tiled_batched(const BatchPlan* __
     }
     const int f = __builtin_amdgcn_readfirstlane(lo);
     const TileArgs a = fs[f].ta;
-    final_tile<TY, TZ>(a, (int)(item - fs[f].tile_base), fs[f].exres, plan->tuning.hops, &plan->bctr[C_FINAL]);
+    final_tile<TY, TZ>(a, (int)(item - fs[f].tile_base), fs[f].exres, &plan->bctr[C_OPEN]);
 }
 
 hipError_t launch_final_tiled_batched(const BatchPlan* dplan, const BatchPlan& hplan, hipStream_t s)
@@ -1057,24 +1056,23 @@ static void launch_2d(const TileArgs& a, bool minima, int first, int count, hipS
         hipLaunchKernelGGL((k_classify2d<false, TY>), dim3(count), dim3(256), 0, s, a, first, count);
 }
 
-hipError_t launch_final_tiled(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, int flag_slot,
-                              hipStream_t s)
+hipError_t launch_final_tiled(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, hipStream_t s)
 {
     int ty, tz;
     tile_shape(tu, g.ndim, &ty, &tz);
     const TileArgs a = tile_args(nullptr, g, lab, nullptr, w, ty, tz);
     if (g.ndim == 3) {
         if (tu.tile3 == 1)
-            hipLaunchKernelGGL((k_final_tiled<4, 16>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres, tu.hops, flag_slot);
+            hipLaunchKernelGGL((k_final_tiled<4, 16>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres);
         else if (tu.tile3 == 2)
-            hipLaunchKernelGGL((k_final_tiled<8, 4>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres, tu.hops, flag_slot);
+            hipLaunchKernelGGL((k_final_tiled<8, 4>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres);
         else
-            hipLaunchKernelGGL((k_final_tiled<8, 8>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres, tu.hops, flag_slot);
+            hipLaunchKernelGGL((k_final_tiled<8, 8>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres);
     } else if (g.ndim == 2) {
         if (tu.tile2 == 1)
-            hipLaunchKernelGGL((k_final_tiled<16, 1>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres, tu.hops, flag_slot);
+            hipLaunchKernelGGL((k_final_tiled<16, 1>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres);
         else
-            hipLaunchKernelGGL((k_final_tiled<32, 1>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres, tu.hops, flag_slot);
+            hipLaunchKernelGGL((k_final_tiled<32, 1>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres);
     } else {
         return hipErrorInvalidValue;
     }

@@ -26,8 +26,8 @@ namespace eg {
 
 constexpr int kMaxNb = 126;         // 2(2^6 - 1)
 constexpr int kJumpHops = 64;       // default links per pointer-jumping pass
-constexpr int kMaxPasses = 8;       // flag slots per pass sequence
-constexpr int kArcBlocks = 8192;    // most blocks per field of the stage (d) kernels
+constexpr int kSumRow = 8192;  // entries per row of the stage (d) block sums
+constexpr int kArcBlocks = 4096;    // most blocks per field of the stage (d) kernels
 constexpr int kArcVertsPerBlock = 8192;  // stage (d) blocks: one per this many vertices
 constexpr int kTile3Y = 8, kTile3Z = 8;  // default 3D tile: 64 x 8 x 8 vertices
 constexpr int kTile2Y = 32;             // default 2D tile: 64 x 32 vertices
@@ -36,15 +36,14 @@ constexpr int kTile2Y = 32;             // default 2D tile: 64 x 32 vertices
 struct Tuning {
     int tile3;  // 0: 64x8x8, 1: 64x4x16, 2: 64x8x4
     int tile2;  // 0: 64x32, 1: 64x16
-    int hops;   // links per label pass
-    int passes; // passes that cover any path of fewer than 2^31 links
+    int hops;   // links per label sweep
     int64_t exit_cap;  // most exit-list entries (0: the default capacity)
 };
 bool decode_tuning(uint32_t t, Tuning* out);
-// Label passes for a grid of n vertices: a steepest-ascent path has fewer
-// than n links and pass p leaves every entry hops^(p+1) links further on or
-// final, so the smallest p with hops^p >= n suffices (at most t.passes).
-int passes_for(const Tuning& t, int64_t n);
+// Most sweeps of a label kernel over its entries on a grid of n vertices: a
+// steepest-ascent path has fewer than n links and every sweep leaves an entry
+// at least `hops` links further on or final.
+__host__ __device__ inline int sweeps_for(const Tuning& t, int64_t n) { return (int)(n / t.hops) + 2; }
 inline void tile_shape(const Tuning& t, int ndim, int* ty, int* tz)
 {
     if (ndim == 3) {
@@ -63,15 +62,10 @@ enum : int {
     C_NAN = 0,
     C_NMAX = 1,
     C_NSAD = 2,
-    C_NPAIRS = 3,
-    C_NARC = 4,
-    C_PASSES = 6,
-    C_PATHS = 40,     // paths (sum of beta over the saddles) for eg_paths
-    C_PVERTS = 41,    // their vertices
-    C_PBAD = 42,      // eg_paths met a pointer that leaves the grid or does not rise
-    C_NEXIT = 7,  // exit-list entries requested by the tiles
-    C_JUMP = 8,   // kMaxPasses "not converged" flags of the exit-list passes
-    C_FINAL = 16, // kMaxPasses "not converged" flags of the per-vertex passes
+    C_PASSES = 6,  // per-vertex label passes (untiled grids)
+    C_NEXIT = 7,   // exit-list entries requested by the tiles
+    C_MORE = 16,   // untiled grids: labels left over by the first per-vertex pass
+    C_OPEN = 17,   // labels left over by the last label kernel (an internal error)
     C_SLOTS = 64,
 };
 
@@ -102,7 +96,7 @@ struct Work {
     uint32_t* ctr;    // [C_SLOTS]
     uint64_t* mmask;  // [words] maxima
     uint64_t* smask;  // [words] saddles
-    uint32_t* bsum;   // [4 * kArcBlocks] per-block counts of stage (d)
+    uint32_t* bsum;   // [4 * kSumRow] per-block counts of stage (d)
     uint4* atmp;      // [cap_sad] the first four arcs of every saddle ([2 cap_sad], eight, from 4D on)
     uint32_t* exits;  // [cap_exit] exit vertices published by the tiles
     int32_t* exres;   // [cap_exit] their labels while being resolved
@@ -161,8 +155,8 @@ struct ArcArgs {
     uint32_t cap_max, cap_sad, cap_arc;
     int32_t arc_blocks;  // blocks of this field in the stage (d) kernels (<= kArcBlocks)
     int32_t pad0;
-    // "not converged" flag of the last label pass (set: some label is still
-    // a code, the header reports EG_ERR_UNRESOLVED); null: not checked
+    // flag of the last label kernel (set: some label is still a code, the
+    // header reports EG_ERR_UNRESOLVED); null: not checked
     EG_GPTR(const uint32_t) last_flag;
 };
 
@@ -196,7 +190,7 @@ struct BatchPlan {
     int32_t class_field[5];
     int32_t pad1;
     int64_t class_tile[5];
-    EG_GPTR(uint32_t) bctr;      // [C_SLOTS] batch counters (label pass flags)
+    EG_GPTR(uint32_t) bctr;      // [C_SLOTS] batch counters (label flags)
     EG_GPTR(BatchField) fields;  // device address of fields[] (right after this header)
     const BatchPlan* dev; // device address of this plan (start of the batch workspace)
     int64_t plan_bytes;
@@ -295,9 +289,54 @@ __device__ __forceinline__ uint32_t first_above(uint32_t u, uint32_t c)
     return r;
 }
 
+// Links between label entries (see the codes below and eg_classify.hip): at
+// device scope when `fresh`.
+__device__ __forceinline__ int link_at(const int32_t* p, bool fresh)
+{
+    return fresh ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+__device__ __forceinline__ int next_link(const int32_t* lab, const int32_t* res, int N, int x, bool fresh)
+{
+    return link_at(x >= -N ? lab + (-x - 1) : res + (-x - 1 - N), fresh);
+}
+
+// One sweep over the quads t, t + stride, ... of a[0, n) and over the n % 4
+// entries behind them (thread t the t-th): four consecutive entries per thread
+// (one 16-byte access, four independent chains in flight).  Returns whether an
+// entry of this thread is not final.
+__device__ __forceinline__ bool sweep(int32_t* a, uint32_t n, const int32_t* lab, const int32_t* res, int N, int hops,
+                                      uint32_t t, uint32_t stride, bool fresh)
+{
+    int4* a4 = reinterpret_cast<int4*>(a);
+    const uint32_t nq = n >> 2;
+    bool open = false;
+    for (uint32_t q = t; q < nq; q += stride) {
+        const int4 x = a4[q];
+        if ((x.x | x.y | x.z | x.w) >= 0) continue;  // all four final
+        int y0 = x.x, y1 = x.y, y2 = x.z, y3 = x.w;
+        for (int h = 0; (y0 < 0 || y1 < 0 || y2 < 0 || y3 < 0) && h < hops; ++h) {
+            if (y0 < 0) y0 = next_link(lab, res, N, y0, fresh);
+            if (y1 < 0) y1 = next_link(lab, res, N, y1, fresh);
+            if (y2 < 0) y2 = next_link(lab, res, N, y2, fresh);
+            if (y3 < 0) y3 = next_link(lab, res, N, y3, fresh);
+        }
+        a4[q] = make_int4(y0, y1, y2, y3);
+        open |= (y0 | y1 | y2 | y3) < 0;
+    }
+    if (t < (n & 3u)) {
+        const uint32_t i = (nq << 2) + t;
+        int y = a[i];
+        for (int h = 0; y < 0 && h < hops; ++h) y = next_link(lab, res, N, y, fresh);
+        a[i] = y;
+        open |= y < 0;
+    }
+    return open;
+}
+
 // ------------------------------------------------------------------ launchers
 
-hipError_t launch_init(uint32_t* ctr, int32_t* header, hipStream_t s);
+// Counters and header to zero; the two masks too on grids without tiles.
+hipError_t launch_init(const Grid& g, const Work& w, int32_t* header, hipStream_t s);
 hipError_t launch_classify(const float* f, const Grid& g, const LinkTable& t, bool minima, int32_t* lab,
                            int32_t* ptr, const Work& w, const Tuning& tu, hipStream_t s);
 // Classification of the 2D/3D tiles [first, first + count) (tiles in C order:
@@ -318,11 +357,10 @@ hipError_t launch_batched_rest(const BatchPlan* dplan, const BatchPlan& hplan, h
 //   x < -N            "same label as exit-list entry -x-1-N"
 __device__ __forceinline__ int exit_list_code(int N, uint32_t idx) { return -(N + 1 + (int)idx); }
 hipError_t launch_labels(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, hipStream_t s);
-// Tile-ordered first per-vertex label pass (2D/3D grids); raises ctr[flag_slot]
-// if some vertex is not final yet.
-hipError_t launch_final_tiled(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, int flag_slot,
-                              hipStream_t s);
-// The tile-ordered pass over every field of a batch; raises bctr[C_FINAL].
+// Tile-ordered per-vertex label pass (2D/3D grids); raises ctr[C_OPEN] if some
+// vertex is not final.
+hipError_t launch_final_tiled(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, hipStream_t s);
+// The tile-ordered pass over every field of a batch; raises bctr[C_OPEN].
 hipError_t launch_final_tiled_batched(const BatchPlan* dplan, const BatchPlan& hplan, hipStream_t s);
 // Stage (d) of one field: ascending maxima and saddles from the bitmasks,
 // the arcs of every saddle, the CSR and the header.

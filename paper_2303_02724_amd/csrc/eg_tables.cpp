@@ -38,13 +38,6 @@ int make_rows(int ndim, int8_t (*off)[EG_MAX_NDIM], uint64_t* adj)
     }
 }
 
-int passes_for(const Tuning& t, int64_t n)
-{
-    int p = 1;
-    for (int64_t reach = t.hops; reach < n && p < t.passes; reach *= t.hops) ++p;
-    return p;
-}
-
 void make_table(const Grid& g, LinkTable* t)
 {
     int8_t off[kMaxNb][EG_MAX_NDIM];
@@ -83,10 +76,6 @@ bool decode_tuning(uint32_t t, Tuning* out)
     u.exit_cap = e == 0 ? 0 : int64_t(1) << e;
     u.hops = h == 0 ? kJumpHops : h;
     if (u.hops != 16 && u.hops != 32 && u.hops != 64 && u.hops != 128) return false;
-    int bits = 0;
-    while ((1 << bits) < u.hops) ++bits;
-    u.passes = (31 + bits - 1) / bits;  // hops^passes >= 2^31
-    if (u.passes > kMaxPasses) return false;
     *out = u;
     return true;
 }
@@ -117,7 +106,7 @@ Work carve(void* base, int ndim, int64_t N, int64_t X, int64_t cap_sad, int64_t 
     const size_t o_ctr = take(sizeof(uint32_t) * C_SLOTS);
     const size_t o_mm = take(sizeof(uint64_t) * (size_t)w.words);
     const size_t o_sm = take(sizeof(uint64_t) * (size_t)w.words);
-    const size_t o_bs = take(sizeof(uint32_t) * 4 * kArcBlocks);
+    const size_t o_bs = take(sizeof(uint32_t) * 4 * kSumRow);
     // the first four arcs of every saddle; 4D and up keep eight (a second
     // block of cap_sad entries)
     const size_t at_rows = ndim >= 4 ? 2 : 1;
