@@ -16,6 +16,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 from dataclasses import dataclass, field as dc_field
 
 import numpy as np
@@ -148,6 +149,22 @@ def status_string(status: int) -> str:
         return lib().eg_status_string(int(status)).decode()
     except RuntimeError:
         return "?"
+
+
+_host = threading.local()
+
+
+def _fetch(t: torch.Tensor) -> list:
+    """The values of a small int32 device tensor behind the work queued on its
+    device's current stream: one copy into this thread's pinned buffer and one
+    wait (a pageable copy has the runtime stage it and wait on its own)."""
+    n = t.numel()
+    buf = getattr(_host, "buf", None)
+    if buf is None or buf.numel() < n:
+        buf = _host.buf = torch.empty(max(64, n), dtype=torch.int32, pin_memory=True)
+    buf[:n].copy_(t, non_blocking=True)
+    torch.cuda.current_stream(t.device).synchronize()
+    return buf[:n].tolist()
 
 
 def _dims(shape):
@@ -381,7 +398,10 @@ class Builder:
 
     def finish(self, check: bool = True) -> EGResult:
         self._stream.synchronize()
-        h = self.header_values()
+        return self._result(_fetch(self.header), check)
+
+    def _result(self, h, check: bool = True) -> EGResult:
+        """The result behind the header values ``h`` of the last launch."""
         if check and h[H_STATUS] != EG_OK:
             raise EGError(h[H_STATUS], f"header={h}")
         nmax, nsad, narc = h[H_NMAX], h[H_NSAD], h[H_NARC]
@@ -442,14 +462,13 @@ class Builder:
     def paths(self, field: torch.Tensor, max_retries: int = 4) -> EGPaths:
         """Gradient-path geometry of the last build of `field` (run() first),
         growing the path buffers while the library reports a shortfall."""
-        h = self.header_values()
-        npairs = max(0, h[H_NPAIRS])
-        if getattr(self, "pcaps", None) is None or self.pcaps[0] < npairs or self.p_pair.numel() < self.caps["cap_sad"] + 1:
+        if getattr(self, "pcaps", None) is None or self.p_pair.numel() < self.caps["cap_sad"] + 1:
+            npairs = max(0, self.header_values()[H_NPAIRS])
             self._alloc_paths(max(1, npairs), max(64, 32 * npairs))
         for _ in range(max_retries + 1):
             self.launch_paths(field)
-            self._stream.synchronize()
-            ph = [int(x) for x in self.p_header.cpu().tolist()]
+            both = _fetch(torch.cat((self.header, self.p_header)))
+            h, ph = both[:H_SLOTS], both[H_SLOTS:]
             if ph[P_STATUS] == EG_ERR_CAPACITY and h[H_NSAD] <= self.caps["cap_sad"]:
                 self._alloc_paths(max(self.pcaps[0], ph[P_PATHS]), max(self.pcaps[1], ph[P_VERTICES]))
                 continue
@@ -464,12 +483,11 @@ class Builder:
         capacity shortfall."""
         for _ in range(max_retries + 1):
             self.launch(field)
-            self._stream.synchronize()
-            h = self.header_values()
+            h = _fetch(self.header)
             if h[H_STATUS] == EG_ERR_CAPACITY:
                 self.grow(h)
                 continue
-            return self.finish()
+            return self._result(h)
         raise EGError(EG_ERR_CAPACITY, "capacity retries exhausted")
 
     def run_streamed(self, host: torch.Tensor, slab_planes: int, max_retries: int = 4) -> EGResult:
@@ -477,12 +495,11 @@ class Builder:
         reports a capacity shortfall (the field is copied again)."""
         for _ in range(max_retries + 1):
             self.launch_streamed(host, slab_planes)
-            self._stream.synchronize()
-            h = self.header_values()
+            h = _fetch(self.header)
             if h[H_STATUS] == EG_ERR_CAPACITY:
                 self.grow(h)
                 continue
-            return self.finish()
+            return self._result(h)
         raise EGError(EG_ERR_CAPACITY, "capacity retries exhausted")
 
 
@@ -597,23 +614,28 @@ class BatchBuilder:
         for b in self.builders:
             b._stream = s
 
+    def _heads(self):
+        """Header values of every field, in one read."""
+        flat = _fetch(torch.cat([b.header for b in self.builders]))
+        return [flat[i:i + H_SLOTS] for i in range(0, len(flat), H_SLOTS)]
+
     def finish(self, check: bool = True):
-        self._stream.synchronize()
-        return [b.finish(check=check) for b in self.builders]
+        for st in {self._stream} | {b._stream for b in self.builders}:
+            st.synchronize()
+        return [b._result(h, check) for b, h in zip(self.builders, self._heads())]
 
     def run(self, fields, max_retries: int = 4):
         """plan + launch + finish, growing per-field buffers on capacity errors."""
         for _ in range(max_retries + 1):
             self.plan(fields)
             self.launch()
-            self._stream.synchronize()
-            heads = [b.header_values() for b in self.builders]
+            heads = self._heads()
             short = [i for i, h in enumerate(heads) if h[H_STATUS] == EG_ERR_CAPACITY]
             if short:
                 for i in short:
                     self.builders[i].grow(heads[i])
                 continue
-            return self.finish()
+            return [b._result(h) for b, h in zip(self.builders, heads)]
         raise EGError(EG_ERR_CAPACITY, "capacity retries exhausted")
 
 
