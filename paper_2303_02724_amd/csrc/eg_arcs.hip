@@ -90,8 +90,9 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
     return x;
 }
 
-// Exclusive scan of x over the 256 threads of the block; total gets the sum.
-// Uses tmp[0..3]; every thread must call it.
+// Exclusive scan of x over the block's threads; total gets the sum.  Uses
+// tmp[0 .. BT / 64); every thread must call it.
+template <int BT = 256>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* tmp, uint32_t& total)
 {
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
@@ -99,13 +100,18 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* tmp, u
     if (lane == 63) tmp[w] = inc;
     __syncthreads();
     uint32_t pre = 0;
-    for (int k = 0; k < w; ++k) pre += tmp[k];
-    total = tmp[0] + tmp[1] + tmp[2] + tmp[3];
+    total = 0;
+#pragma unroll
+    for (int k = 0; k < BT / 64; ++k) {
+        pre += k < w ? tmp[k] : 0u;
+        total += tmp[k];
+    }
     __syncthreads();
     return pre + inc - x;
 }
 
-// Sums over the 256 threads of the block, to every thread.  Uses tmp[0..7].
+// Sums over the block's threads, to every thread.  Uses tmp[0 .. BT / 32).
+template <int BT = 256>
 __device__ __forceinline__ void block_sum2(uint32_t& x, uint32_t& y, uint32_t* tmp)
 {
     const int w = threadIdx.x >> 6;
@@ -115,12 +121,16 @@ __device__ __forceinline__ void block_sum2(uint32_t& x, uint32_t& y, uint32_t* t
         y += __shfl_xor(y, o);
     }
     if ((threadIdx.x & 63) == 0) {
-        tmp[w] = x;
-        tmp[4 + w] = y;
+        tmp[2 * w] = x;
+        tmp[2 * w + 1] = y;
     }
     __syncthreads();
-    x = tmp[0] + tmp[1] + tmp[2] + tmp[3];
-    y = tmp[4] + tmp[5] + tmp[6] + tmp[7];
+    x = y = 0;
+#pragma unroll
+    for (int k = 0; k < BT / 64; ++k) {
+        x += tmp[2 * k];
+        y += tmp[2 * k + 1];
+    }
     __syncthreads();
 }
 
@@ -128,16 +138,17 @@ __device__ __forceinline__ void block_sum2(uint32_t& x, uint32_t& y, uint32_t* t
 // block adds them up for itself (at most kArcBlocks entries, two coalesced
 // reads per 256): a kernel of its own for the scan costs more than the reads,
 // 4.5 to 8.6 us on every field.
+template <int BT = 256>
 __device__ __forceinline__ void sums_before(const ArcArgs& A, int row, uint32_t blk, uint32_t* tmp, uint32_t& a,
                                             uint32_t& b)
 {
     a = b = 0;
     const EG_GPTR(uint32_t) p = A.bsum + row * kSumRow;
-    for (uint32_t i = threadIdx.x; i < blk; i += 256) {
+    for (uint32_t i = threadIdx.x; i < blk; i += BT) {
         a += p[i];
         b += p[kSumRow + i];
     }
-    block_sum2(a, b, tmp);
+    block_sum2<BT>(a, b, tmp);
 }
 
 __device__ __forceinline__ uint32_t saddle_count(const ArcArgs& A)
@@ -225,37 +236,98 @@ __global__ __launch_bounds__(256) void k_mask_emit(Sel sel)
 
 // ------------------------------------------------------------------ arcs
 
-// The neighbourhood of saddle v: order keys (0 outside the grid, below every
-// vertex) and linear offsets of the K Freudenthal rows, and the upper-link
-// mask (Alg. 1, Sec. 3.3).
-// From 4D on (30 to 126 rows) the rows' offsets come from a per-block table
-// in LDS when a rep is found (only the rep's offset is needed).  In 6D (126
-// rows) the keys are not kept either: holding them costs more registers, and
-// waves, than reloading the few keys of one component when its rep is sought.
+// Rows of the link as a mask: one bit per row.
 template <int NDIM>
-constexpr bool kLazyNbhd = NDIM >= 6;
+struct LinkMask {
+    using type = uint32_t;
+};
+template <>
+struct LinkMask<5> {
+    using type = uint64_t;
+};
+template <>
+struct LinkMask<6> {
+    using type = unsigned __int128;
+};
 template <int NDIM>
-constexpr bool kOffsInLds = NDIM >= 4;
+using LMask = typename LinkMask<NDIM>::type;
+
+__device__ __forceinline__ int low_row(uint32_t m) { return __ffs((int)m) - 1; }
+__device__ __forceinline__ int low_row(uint64_t m) { return lowest_bit(m); }
+__device__ __forceinline__ int low_row(unsigned __int128 m) { return lowest_bit(m); }
+
+// 1D and 4D-6D classification stores every vertex's order key (already
+// reversed for the minimum graph); 2D and 3D read the field.
+template <int NDIM>
+constexpr bool kStoredKeys = NDIM != 2 && NDIM != 3;
+// Up to 5D a thread of k_arc_count parks the keys of its saddle's
+// neighbourhood in its own column of LDS, so that a rep is found by visiting
+// its component's rows only (registers cannot be indexed: there, every
+// component costs a scan of all rows; a column is one bank, so the reads do
+// not conflict).  Stage (d), before and after, with the stored lists' sort as
+// minima and maxima: 201 x 190 x 333 noise (1.95 M saddles) 124 -> 110 us,
+// 4D (0.92 M of 10 M vertices) 132 -> 95, 5D (3.8 M) 577 -> 523.  What bounds
+// 5D now is the L2: a gather fetches 128 bytes for the 8 it uses.  6D (126
+// rows, 32 KB a wave) reads the keys of a component's rows again instead, as
+// the write and path kernels do everywhere: they need the waves.
+template <int NDIM>
+constexpr bool kKeysInLds = NDIM <= 5;
+// Threads per block: a 5D wave's keys take 16 KB of LDS, and ten of them fit a
+// compute unit in blocks of two, eight in blocks of four.
+template <int NDIM>
+constexpr int kArcThreads = NDIM == 5 ? 128 : 256;
+
+// Most waves per SIMD that k_arc_count schedules its registers for: 6D is
+// bound by the latency of its 126 gathers, and more of them in flight in fewer
+// waves is the better trade (16^6, stage (d): 64 us with 77 registers, 52 with
+// room for two waves).
+template <int NDIM>
+constexpr int kArcWaves = NDIM == 6 ? 2 : 8;
 
 template <int NDIM, bool MINMODE>
-struct Nbhd {
-    static constexpr int K = Rows<NDIM>::K;
-    uint32_t us[kLazyNbhd<NDIM> ? 1 : K];
-    int offs[kOffsInLds<NDIM> ? 1 : K];
-    Mask<NDIM> up;
-    EG_GPTR(const uint32_t) keys;  // the order keys (lazy neighbourhoods)
-};
-
-// Linear offset of every row, per block (lazy neighbourhoods).
-template <int NDIM>
-__device__ __forceinline__ int* row_offsets()
+__device__ __forceinline__ uint32_t vertex_key(const ArcArgs& A, int v)
 {
-    __shared__ int s_off[Rows<NDIM>::K];
-    return s_off;
+    if constexpr (kStoredKeys<NDIM>)
+        return A.keys[v];
+    else
+        return mode_key<MINMODE>(A.f[v]);
 }
 
-template <int NDIM, bool MINMODE>
-__device__ __forceinline__ void load_nbhd(const ArcArgs& A, int v, Nbhd<NDIM, MINMODE>& nb)
+// LDS of a block of the arc and path kernels: the rows' linear offsets, and
+// the keys (row j of thread t at keys[j][t]) where they are parked.
+template <int NDIM, bool PARK>
+struct RowLds {
+    static constexpr int K = Rows<NDIM>::K;
+    static constexpr int N = NDIM;
+    static constexpr bool kPark = PARK;
+    int off[K];
+    uint32_t keys[PARK ? K : 1][PARK ? kArcThreads<NDIM> : 1];
+};
+
+template <class LDS>
+__device__ __forceinline__ void load_rows(const ArcArgs& A, LDS& T)
+{
+    constexpr int NDIM = LDS::N;
+    constexpr Rows<NDIM> R = make_rows_ce<NDIM>();
+    constexpr int K = Rows<NDIM>::K;
+    int st[NDIM];
+    st[NDIM - 1] = 1;
+#pragma unroll
+    for (int i = NDIM - 2; i >= 0; --i) st[i] = st[i + 1] * A.dims[i + 1];
+    for (int j = threadIdx.x; j < K; j += kArcThreads<NDIM>) {
+        int off = 0;
+#pragma unroll
+        for (int i = 0; i < NDIM; ++i) off += R.d[j][i] * st[i];
+        T.off[j] = off;
+    }
+    __syncthreads();
+}
+
+// The upper-link mask of saddle v over the K Freudenthal rows (Alg. 1, Sec.
+// 3.3), and the rows' keys into this thread's column (0 outside the grid,
+// below every vertex).
+template <int NDIM, bool MINMODE, class LDS>
+__device__ __forceinline__ LMask<NDIM> load_nbhd(const ArcArgs& A, int v, LDS& T)
 {
     constexpr Rows<NDIM> R = make_rows_ce<NDIM>();
     constexpr int K = Rows<NDIM>::K;
@@ -271,14 +343,12 @@ __device__ __forceinline__ void load_nbhd(const ArcArgs& A, int v, Nbhd<NDIM, MI
             stride *= d;
         }
     }
-    // keys stored by classification already carry the reversal of the
-    // minimum graph
-    const bool stored = A.keys != nullptr;
-    const uint32_t uv = stored ? A.keys[v] : mode_key<MINMODE>(A.f[v]);
-    nb.up = 0;
-    nb.keys = A.keys;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
+    const uint32_t uv = vertex_key<NDIM, MINMODE>(A, v);
+    // 32 rows per word, pushed from the highest row down
+    constexpr int NW = (K + 31) / 32;
+    uint32_t wd[NW];
+    static_for<0, K>([&](auto step) {
+        constexpr int j = K - 1 - decltype(step)::value;
         bool in = true;
         int off = 0;
 #pragma unroll
@@ -289,93 +359,125 @@ __device__ __forceinline__ void load_nbhd(const ArcArgs& A, int v, Nbhd<NDIM, MI
                 off += d * st[i];
             }
         }
-        uint32_t u;
-        if constexpr (NDIM >= 4 && !kLazyNbhd<NDIM>) {
-            // no branch around the load: every row's load is in flight at once
-            const int w = in ? v + off : v;
-            const uint32_t x = stored ? A.keys[w] : mode_key<MINMODE>(A.f[w]);
-            u = in ? x : 0u;
-        } else {
-            u = !in ? 0u : stored ? A.keys[v + off] : mode_key<MINMODE>(A.f[v + off]);
-        }
-        if constexpr (!kLazyNbhd<NDIM>) nb.us[j] = u;
-        if constexpr (!kOffsInLds<NDIM>) nb.offs[j] = off;
-        const bool wins_tie = (j >= K / 2) != MINMODE;
-        nb.up |= Mask<NDIM>(wins_tie ? (u >= uv) : (u > uv)) << j;
-    }
-}
-
-// Calls f(rep) for every upper-link component of saddle v, with rep the
-// component's highest vertex (UpperLinkRep, Sec. 3.4), found by scanning in
-// the order in which the later of two equal vertices wins.  Components are
-// grown from the lowest remaining row (a bit-parallel BFS over the link
-// edges; from 4D on by set algebra on the link's rows, eg_link.h); rows are
-// in linear-index order, so components come in ascending order of their
-// smallest vertex.
-template <int NDIM, bool MINMODE, class F>
-__device__ __forceinline__ void for_each_rep(int v, const Nbhd<NDIM, MINMODE>& nb, const Mask<NDIM>* s_adj, F&& f)
-{
-    constexpr int K = Rows<NDIM>::K;
-    for (Mask<NDIM> rem = nb.up; rem != 0;) {
-        Mask<NDIM> comp;
-        if constexpr (NDIM >= 4)
-            comp = link_component<NDIM>(rem);
+        // no branch around the load: every row's load is in flight at once
+        const uint32_t x = vertex_key<NDIM, MINMODE>(A, in ? v + off : v);
+        const uint32_t u = in ? x : 0u;
+        if constexpr (LDS::kPark) T.keys[j][threadIdx.x] = u;
+        constexpr bool wins = (j >= K / 2) != MINMODE;
+        if constexpr (j == K - 1 || j % 32 == 31)
+            wd[j / 32] = first_above<wins>(u, uv);
         else
-            comp = closure(rem & (~rem + 1), rem, s_adj);
+            wd[j / 32] = push_above<wins>(wd[j / 32], u, uv);
+    });
+    LMask<NDIM> up = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) up |= LMask<NDIM>(wd[w]) << (w == 0 ? 0 : 32 * w);
+    return up;
+}
+
+// The component of the lowest row of `rem`: a table of every mask up to 3D,
+// set algebra on the link's rows (eg_link.h) above.
+template <int NDIM>
+struct CompTable {
+    uint16_t c[1 << Rows<NDIM>::K];
+};
+template <int NDIM>
+constexpr CompTable<NDIM> make_comps()
+{
+    constexpr Rows<NDIM> r = make_rows_ce<NDIM>();
+    CompTable<NDIM> t{};
+    for (uint32_t m = 1; m < (1u << Rows<NDIM>::K); ++m)
+        t.c[m] = (uint16_t)closure_ce<NDIM>(r, m & (~m + 1u), m);
+    return t;
+}
+__constant__ CompTable<1> c_comp1 = make_comps<1>();
+__constant__ CompTable<2> c_comp2 = make_comps<2>();
+__constant__ CompTable<3> c_comp3 = make_comps<3>();
+
+template <int NDIM>
+__device__ __forceinline__ LMask<NDIM> first_component(LMask<NDIM> rem)
+{
+    if constexpr (NDIM == 1)
+        return c_comp1.c[rem];
+    else if constexpr (NDIM == 2)
+        return c_comp2.c[rem];
+    else if constexpr (NDIM == 3)
+        return c_comp3.c[rem];
+    else
+        return link_component<NDIM>(rem);
+}
+
+// The key of row j of saddle v's link (a row in the grid).
+template <int NDIM, bool MINMODE, class LDS>
+__device__ __forceinline__ uint32_t key_at(const ArcArgs& A, int v, int j, const LDS& T)
+{
+    if constexpr (LDS::kPark)
+        return T.keys[j][threadIdx.x];
+    else
+        return vertex_key<NDIM, MINMODE>(A, v + T.off[j]);
+}
+
+// The highest vertex of a component (UpperLinkRep, Sec. 3.4): its rows in
+// ascending vertex order, the later of two equal vertices the higher one, the
+// earlier in the minimum graph.
+template <int NDIM, bool MINMODE, class LDS>
+__device__ __forceinline__ int rep_of(const ArcArgs& A, int v, LMask<NDIM> comp, const LDS& T)
+{
+    uint32_t best_u = 0;
+    int best = 0;
+    // two rows a round (the second again the first when there is none left),
+    // so that two reads are in flight
+    do {
+        const int j0 = low_row(comp);
+        comp &= comp - 1;
+        const int j1 = comp != 0 ? low_row(comp) : j0;
+        comp &= comp - 1;  // 0 & anything stays 0
+        const uint32_t u0 = key_at<NDIM, MINMODE>(A, v, j0, T);
+        const uint32_t u1 = key_at<NDIM, MINMODE>(A, v, j1, T);
+        const bool w0 = MINMODE ? u0 > best_u : u0 >= best_u;
+        best_u = w0 ? u0 : best_u;
+        best = w0 ? j0 : best;
+        const bool w1 = MINMODE ? u1 > best_u : u1 >= best_u;
+        best_u = w1 ? u1 : best_u;
+        best = w1 ? j1 : best;
+    } while (comp != 0);
+    return v + T.off[best];
+}
+
+// Calls f(rep) for every upper-link component of saddle v, in ascending order
+// of the components' smallest vertices (rows are in linear-index order).
+template <int NDIM, bool MINMODE, class LDS, class F>
+__device__ __forceinline__ void for_each_rep(const ArcArgs& A, int v, LMask<NDIM> rem, const LDS& T, F&& f)
+{
+    while (rem != 0) {
+        const LMask<NDIM> comp = first_component<NDIM>(rem);
         rem &= ~comp;
-        uint32_t best_u = 0;
-        int best_off = 0;
-        if constexpr (kLazyNbhd<NDIM>) {
-            // the component's rows in scan order: ascending rows, descending in
-            // the minimum graph; every row of the mask lies in the grid
-            const int* s_off = row_offsets<NDIM>();
-            for (Mask<NDIM> c = comp; c != 0;) {
-                const int j = MINMODE ? highest_bit(c) : lowest_bit(c);
-                c &= ~(Mask<NDIM>(1) << j);
-                const int off = s_off[j];
-                const uint32_t u = nb.keys[v + off];
-                if (u >= best_u) {
-                    best_u = u;
-                    best_off = off;
-                }
-            }
-        } else if constexpr (kOffsInLds<NDIM>) {
-            int best_j = 0;
-#pragma unroll
-            for (int s = 0; s < K; ++s) {
-                const int j = MINMODE ? K - 1 - s : s;
-                if ((uint32_t)(comp >> j) & 1u && nb.us[j] >= best_u) {
-                    best_u = nb.us[j];
-                    best_j = j;
-                }
-            }
-            best_off = row_offsets<NDIM>()[best_j];
-        } else {
-#pragma unroll
-            for (int s = 0; s < K; ++s) {
-                const int j = MINMODE ? K - 1 - s : s;
-                if ((uint32_t)(comp >> j) & 1u && nb.us[j] >= best_u) {
-                    best_u = nb.us[j];
-                    best_off = nb.offs[j];
-                }
-            }
-        }
-        f(v + best_off);
+        f(rep_of<NDIM, MINMODE>(A, v, comp, T));
     }
 }
 
-// f(label) for every component: the label its rep reaches.
-template <int NDIM, bool MINMODE, class F>
-__device__ __forceinline__ void for_each_arc_label(const ArcArgs& A, int v, const Nbhd<NDIM, MINMODE>& nb,
-                                                   const Mask<NDIM>* s_adj, F&& f)
+// f(label) for every component: the label its rep reaches.  A label is used
+// only after the next component's rep has been sought, so its load is not
+// waited for on its own.
+template <int NDIM, bool MINMODE, class LDS, class F>
+__device__ __forceinline__ void for_each_arc_label(const ArcArgs& A, int v, LMask<NDIM> up, const LDS& T, F&& f)
 {
-    for_each_rep<NDIM, MINMODE>(v, nb, s_adj, [&](int rep) { f((uint32_t)A.lab[rep]); });
+    uint32_t last = 0;
+    bool have = false;
+    for_each_rep<NDIM, MINMODE>(A, v, up, T, [&](int rep) {
+        const uint32_t L = (uint32_t)A.lab[rep];
+        if (have) f(last);
+        last = L;
+        have = true;
+    });
+    if (have) f(last);
 }
 
 // The S smallest distinct arc labels of a saddle, ascending (unused entries
-// ~0u; labels are vertex ids below 2^31).  `more` is set when the saddle has
-// further distinct labels above lo[S-1].  S = 4 in 2D/3D (at most 3 and 6
-// components), 8 from 4D on, where more components are common.
+// ~0u; labels are vertex ids below 2^31), and the number of distinct labels as
+// far as it is known: `more` is set when there are further ones above lo[S-1].
+// S = 4 in 2D/3D (at most 3 and 6 components), 8 from 4D on, where more
+// components are common.
 template <int NDIM>
 struct ArcList {
     static constexpr int S = NDIM >= 4 ? 8 : 4;
@@ -383,51 +485,90 @@ struct ArcList {
     bool more;
 };
 
-template <int NDIM, bool MINMODE>
-__device__ __forceinline__ ArcList<NDIM> first_arcs(const ArcArgs& A, int v, const Nbhd<NDIM, MINMODE>& nb,
-                                                    const Mask<NDIM>* s_adj, int& beta)
+__device__ __forceinline__ void order2(uint32_t& a, uint32_t& b)
+{
+    const uint32_t t = min(a, b);
+    b = max(a, b);
+    a = t;
+}
+// Ascending order of 6 or 8 values (Batcher's odd-even merge sort).
+__device__ __forceinline__ void sort_few(uint32_t (&x)[6])
+{
+    order2(x[0], x[5]), order2(x[1], x[3]), order2(x[2], x[4]);
+    order2(x[1], x[2]), order2(x[3], x[4]);
+    order2(x[0], x[3]), order2(x[2], x[5]);
+    order2(x[0], x[1]), order2(x[2], x[3]), order2(x[4], x[5]);
+    order2(x[1], x[2]), order2(x[3], x[4]);
+}
+__device__ __forceinline__ void sort_few(uint32_t (&x)[8])
+{
+    order2(x[0], x[1]), order2(x[2], x[3]), order2(x[4], x[5]), order2(x[6], x[7]);
+    order2(x[0], x[2]), order2(x[1], x[3]), order2(x[4], x[6]), order2(x[5], x[7]);
+    order2(x[1], x[2]), order2(x[5], x[6]);
+    order2(x[0], x[4]), order2(x[1], x[5]), order2(x[2], x[6]), order2(x[3], x[7]);
+    order2(x[2], x[4]), order2(x[3], x[5]);
+    order2(x[1], x[2]), order2(x[3], x[4]), order2(x[5], x[6]);
+}
+
+template <int NDIM, bool MINMODE, class LDS>
+__device__ __forceinline__ ArcList<NDIM> first_arcs(const ArcArgs& A, int v, LMask<NDIM> up, const LDS& T, int& beta)
 {
     constexpr int S = ArcList<NDIM>::S;
-    ArcList<NDIM> r;
+    // every component of a saddle up to 3D, nearly every saddle's above, has a
+    // place in x: its labels go in by one pass of minima and maxima each,
+    // equal ones drop out afterwards
+    constexpr int X = NDIM >= 4 ? 8 : 6;
+    uint32_t x[X];
 #pragma unroll
-    for (int k = 0; k < S; ++k) r.lo[k] = ~0u;
-    r.more = false;
+    for (int k = 0; k < X; ++k) x[k] = ~0u;
     beta = 0;
-    for_each_arc_label<NDIM, MINMODE>(A, v, nb, s_adj, [&](uint32_t L) {
+    for_each_arc_label<NDIM, MINMODE>(A, v, up, T, [&](uint32_t L) {
         ++beta;
-        bool dup = false;
 #pragma unroll
-        for (int k = 0; k < S; ++k) dup |= L == r.lo[k];
-        if (dup) return;
-        if (L > r.lo[S - 1]) {  // a distinct label above a full list
-            r.more = true;
-            return;
-        }
-        if (r.lo[S - 1] != ~0u) r.more = true;  // the list is full: its largest moves out
-        r.lo[S - 1] = L;
-        // one insertion step keeps the list sorted
-#pragma unroll
-        for (int k = S - 1; k > 0; --k)
-            if (r.lo[k] < r.lo[k - 1]) {
-                const uint32_t t = r.lo[k - 1];
-                r.lo[k - 1] = r.lo[k];
-                r.lo[k] = t;
-            }
+        for (int k = 0; k < X; ++k) order2(x[k], L);
     });
+    ArcList<NDIM> r;
+    bool dup = false;
+#pragma unroll
+    for (int k = X - 1; k > 0; --k) {
+        const bool same = x[k] == x[k - 1] && x[k] != ~0u;
+        dup |= same;
+        x[k] = same ? ~0u : x[k];
+    }
+    if (dup) sort_few(x);
+#pragma unroll
+    for (int k = 0; k < S; ++k) r.lo[k] = x[k];
+    r.more = false;
+    if constexpr (X > S) {
+        r.more = x[S] != ~0u;
+    } else if (beta > X) {
+        // more components than places: the list again, label by label
+#pragma unroll
+        for (int k = 0; k < S; ++k) r.lo[k] = ~0u;
+        for_each_arc_label<NDIM, MINMODE>(A, v, up, T, [&](uint32_t L) {
+            bool known = false;
+#pragma unroll
+            for (int k = 0; k < S; ++k) known |= L == r.lo[k];
+            if (known) return;
+#pragma unroll
+            for (int k = 0; k < S; ++k) order2(r.lo[k], L);
+            r.more |= L != ~0u;  // the largest moved out
+        });
+    }
     return r;
 }
 
 // Distinct labels above `last`, ascending, one pass over the components
-// each: for saddles with more than four distinct arcs (rare).  Calls
+// each: for saddles with more distinct arcs than the list holds (rare).  Calls
 // emit(k, label) for the k-th of them and returns their number.
-template <int NDIM, bool MINMODE, class E>
-__device__ __forceinline__ uint32_t labels_above(const ArcArgs& A, int v, const Nbhd<NDIM, MINMODE>& nb,
-                                                 const Mask<NDIM>* s_adj, uint32_t last, E&& emit)
+template <int NDIM, bool MINMODE, class LDS, class E>
+__device__ __forceinline__ uint32_t labels_above(const ArcArgs& A, int v, LMask<NDIM> up, const LDS& T, uint32_t last,
+                                                 E&& emit)
 {
     uint32_t k = 0;
     for (;;) {
         uint32_t next = ~0u;
-        for_each_arc_label<NDIM, MINMODE>(A, v, nb, s_adj, [&](uint32_t L) {
+        for_each_arc_label<NDIM, MINMODE>(A, v, up, T, [&](uint32_t L) {
             if (L > last && L < next) next = L;
         });
         if (next == ~0u) return k;
@@ -437,55 +578,29 @@ __device__ __forceinline__ uint32_t labels_above(const ArcArgs& A, int v, const 
     }
 }
 
-template <int NDIM>
-__device__ __forceinline__ void load_adj(const ArcArgs& A, Mask<NDIM>* s_adj)
+// Distinct-arc count, beta and the first four (eight from 4D on) arcs of every
+// saddle of the block's chunk; the block's sums of both counts go to rows 2
+// and 3.
+template <int NDIM, bool MINMODE, class LDS>
+__device__ __forceinline__ void arc_count_body(const ArcArgs& A, uint32_t blk, uint32_t nb, LDS& T, uint32_t* tmp)
 {
-    constexpr int K = Rows<NDIM>::K;
-    if constexpr (NDIM < 4) {  // from 4D on components come from set algebra
-        const Mask<NDIM>* t = adj_table<NDIM>();
-        for (int i = threadIdx.x; i < K; i += blockDim.x) s_adj[i] = t[i];
-    }
-    if constexpr (kOffsInLds<NDIM>) {
-        constexpr Rows<NDIM> R = make_rows_ce<NDIM>();
-        int* s_off = row_offsets<NDIM>();
-        int st[NDIM];
-        st[NDIM - 1] = 1;
-#pragma unroll
-        for (int i = NDIM - 2; i >= 0; --i) st[i] = st[i + 1] * A.dims[i + 1];
-        for (int j = threadIdx.x; j < K; j += blockDim.x) {
-            int off = 0;
-#pragma unroll
-            for (int i = 0; i < NDIM; ++i) off += R.d[j][i] * st[i];
-            s_off[j] = off;
-        }
-    }
-    __syncthreads();
-}
-
-// Distinct-arc count, beta and the first four (eight from 4D on) arcs of every saddle of the
-// block's chunk; the block's sums of both counts go to rows 2 and 3.
-template <int NDIM, bool MINMODE>
-__device__ __forceinline__ void arc_count_body(const ArcArgs& A, uint32_t blk, uint32_t nb, Mask<NDIM>* s_adj,
-                                               uint32_t* tmp)
-{
-    load_adj<NDIM>(A, s_adj);
+    load_rows(A, T);
     uint32_t lo, hi;
     chunk(saddle_count(A), nb, blk, lo, hi);
     const int tid = threadIdx.x;
     uint32_t sc = 0, sb = 0;
-    for (uint32_t i = lo + tid; i < hi; i += 256) {
+    for (uint32_t i = lo + tid; i < hi; i += kArcThreads<NDIM>) {
         // saddle ids come from the compaction; the check keeps a stage run
         // on a workspace without classification inside the grid
         const int v = min(max(A.saddles[i], 0), A.N - 1);
-        Nbhd<NDIM, MINMODE> h;
-        load_nbhd<NDIM, MINMODE>(A, v, h);
+        const LMask<NDIM> up = load_nbhd<NDIM, MINMODE>(A, v, T);
         int beta;
-        const ArcList<NDIM> r = first_arcs<NDIM, MINMODE>(A, v, h, s_adj, beta);
+        const ArcList<NDIM> r = first_arcs<NDIM, MINMODE>(A, v, up, T, beta);
         constexpr int S = ArcList<NDIM>::S;
         uint32_t n = 0;
 #pragma unroll
         for (int k = 0; k < S; ++k) n += r.lo[k] != ~0u;
-        if (r.more) n += labels_above<NDIM, MINMODE>(A, v, h, s_adj, r.lo[S - 1], [](uint32_t, uint32_t) {});
+        if (r.more) n += labels_above<NDIM, MINMODE>(A, v, up, T, r.lo[S - 1], [](uint32_t, uint32_t) {});
         if (A.beta) A.beta[i] = beta;
         A.offsets[i + 1] = (int32_t)n;  // the count until k_arc_write turns it into an offset
         A.atmp[i] = make_uint4(r.lo[0], r.lo[1], r.lo[2], r.lo[3]);
@@ -493,7 +608,7 @@ __device__ __forceinline__ void arc_count_body(const ArcArgs& A, uint32_t blk, u
         sc += n;
         sb += (uint32_t)beta;
     }
-    block_sum2(sc, sb, tmp);
+    block_sum2<kArcThreads<NDIM>>(sc, sb, tmp);
     if (tid == 0) {
         A.bsum[2 * kSumRow + blk] = sc;
         A.bsum[3 * kSumRow + blk] = sb;
@@ -525,86 +640,106 @@ __device__ __forceinline__ void write_header(const ArcArgs& A, uint32_t narc, ui
     h[EG_H_EXITS] = (int32_t)c[C_NEXIT];
 }
 
-template <int NDIM, bool MINMODE>
-__device__ __forceinline__ void arc_write_body(const ArcArgs& A, uint32_t blk, uint32_t nb, Mask<NDIM>* s_adj,
-                                               uint32_t* tmp)
+// Four saddles per thread and round: their counts and stored arcs are all
+// loaded before the one scan of the round (the counts packed by 16 bits: a
+// saddle has at most 63 arcs).
+template <int NDIM, bool MINMODE, class LDS>
+__device__ __forceinline__ void arc_write_body(const ArcArgs& A, uint32_t blk, uint32_t nb, LDS& T, uint32_t* tmp)
 {
-    load_adj<NDIM>(A, s_adj);
+    constexpr int S = ArcList<NDIM>::S;
+    constexpr int R = 4, BT = kArcThreads<NDIM>;
     uint32_t lo, hi;
     chunk(saddle_count(A), nb, blk, lo, hi);
     const int tid = threadIdx.x;
     if (blk == 0 && tid == 0) A.offsets[0] = 0;
     uint32_t run, pairs;
-    sums_before(A, 2, blk, tmp, run, pairs);
-    for (uint32_t base = lo; base < hi; base += 256) {
-        const uint32_t i = base + tid;
-        const bool valid = i < hi;
-        const uint32_t n = valid ? (uint32_t)A.offsets[i + 1] : 0u;
-        uint32_t total;
-        const uint32_t pos = run + block_excl_scan(n, tmp, total);
-        if (valid) {
-            const uint4 t = A.atmp[i];
-            const uint32_t a4[4] = {t.x, t.y, t.z, t.w};
+    sums_before<BT>(A, 2, blk, tmp, run, pairs);
+    const uint32_t first = run;
+    bool big = false;
+    for (uint32_t base = lo; base < hi; base += BT * R) {
+        uint32_t n[R];
+        uint4 t[R], u[S > 4 ? R : 1];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t i = base + BT * r + tid;
+            const uint32_t at = i < hi ? i : lo;
+            n[r] = i < hi ? (uint32_t)A.offsets[at + 1] : 0u;
+            t[r] = A.atmp[at];
+        }
+        if constexpr (S > 4) {
+            // the next four stored arcs
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (n[r] > 4) u[r] = A.atmp[A.cap_sad + base + BT * r + tid];
+        }
+        uint32_t t01, t23;
+        const uint32_t e01 = block_excl_scan<BT>(n[0] | (n[1] << 16), tmp, t01);
+        const uint32_t e23 = block_excl_scan<BT>(n[2] | (n[3] << 16), tmp, t23);
+        const uint32_t tot[R] = {t01 & 0xFFFFu, t01 >> 16, t23 & 0xFFFFu, t23 >> 16};
+        const uint32_t ex[R] = {e01 & 0xFFFFu, e01 >> 16, e23 & 0xFFFFu, e23 >> 16};
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t i = base + BT * r + tid;
+            const uint32_t pos = run + ex[r];
+            run += tot[r];
+            if (i >= hi) continue;
+            const uint32_t a4[4] = {t[r].x, t[r].y, t[r].z, t[r].w};
 #pragma unroll
             for (uint32_t k = 0; k < 4; ++k)
-                if (k < n && pos + k < A.cap_arc) A.arcs[pos + k] = (int32_t)a4[k];
-            constexpr int S = ArcList<NDIM>::S;
-            uint32_t last = t.w;
+                if (k < n[r] && pos + k < A.cap_arc) A.arcs[pos + k] = (int32_t)a4[k];
             if constexpr (S > 4) {
-                // the next four stored arcs
-                if (n > 4) {
-                    const uint4 u = A.atmp[A.cap_sad + i];
-                    const uint32_t b4[4] = {u.x, u.y, u.z, u.w};
+                if (n[r] > 4) {
+                    const uint32_t b4[4] = {u[r].x, u[r].y, u[r].z, u[r].w};
 #pragma unroll
                     for (uint32_t k = 0; k < 4; ++k)
-                        if (4 + k < n && pos + 4 + k < A.cap_arc) A.arcs[pos + 4 + k] = (int32_t)b4[k];
-                    last = u.w;
+                        if (4 + k < n[r] && pos + 4 + k < A.cap_arc) A.arcs[pos + 4 + k] = (int32_t)b4[k];
                 }
             }
-            if (n > (uint32_t)S) {
-                // past the stored arcs: ascending selection over the components
+            big |= n[r] > (uint32_t)S;
+            A.offsets[i + 1] = (int32_t)(pos + n[r]);
+        }
+    }
+    if constexpr (NDIM >= 3) {  // at most three arcs in 1D and 2D
+        // saddles with arcs past the stored ones: ascending selection over
+        // their components, in a loop of its own (whose registers the loop
+        // above then does not carry)
+        if (__syncthreads_or(big)) {
+            load_rows(A, T);
+            for (uint32_t i = lo + tid; i < hi; i += BT) {
+                const uint32_t pos = i == lo ? first : (uint32_t)A.offsets[i];
+                if ((uint32_t)A.offsets[i + 1] - pos <= (uint32_t)S) continue;
                 const int v = min(max(A.saddles[i], 0), A.N - 1);
-                Nbhd<NDIM, MINMODE> h;
-                load_nbhd<NDIM, MINMODE>(A, v, h);
-                labels_above<NDIM, MINMODE>(A, v, h, s_adj, last, [&](uint32_t k, uint32_t L) {
+                const uint32_t last = S > 4 ? A.atmp[A.cap_sad + i].w : A.atmp[i].w;
+                const LMask<NDIM> up = load_nbhd<NDIM, MINMODE>(A, v, T);
+                labels_above<NDIM, MINMODE>(A, v, up, T, last, [&](uint32_t k, uint32_t L) {
                     if (pos + S + k < A.cap_arc) A.arcs[pos + S + k] = (int32_t)L;
                 });
             }
-            A.offsets[i + 1] = (int32_t)(pos + n);
         }
-        run += total;
     }
     // the last block has seen every count
     if (blk == nb - 1 && tid == 0) write_header(A, run, pairs + A.bsum[3 * kSumRow + blk]);
 }
 
-// Four waves per SIMD for the 5D rows, in the arc and the path kernels alike
-// (the compiler's own choice, 133 to 150 registers, leaves three and stalls
-// on the gathers; the few spilled values cost less); 6D keeps its registers,
-// since there the spills cost more.
-template <int NDIM>
-constexpr int kArcWaves = NDIM == 5 ? 4 : 1;
-
 template <int NDIM, bool MINMODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<NDIM>, 8))) void k_arc_count(
-    OneField sel)
+__global__ __launch_bounds__(kArcThreads<NDIM>)
+    __attribute__((amdgpu_waves_per_eu(1, kArcWaves<NDIM>))) void k_arc_count(OneField sel)
 {
-    __shared__ Mask<NDIM> s_adj[Rows<NDIM>::K];
+    __shared__ RowLds<NDIM, kKeysInLds<NDIM>> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
-    arc_count_body<NDIM, MINMODE>(A, blk, nb, s_adj, tmp);
+    arc_count_body<NDIM, MINMODE>(A, blk, nb, T, tmp);
 }
 
 template <int NDIM, bool MINMODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<NDIM>, 8))) void k_arc_write(
-    OneField sel)
+__global__ __launch_bounds__(kArcThreads<NDIM>) void k_arc_write(OneField sel)
 {
-    __shared__ Mask<NDIM> s_adj[Rows<NDIM>::K];
+    __shared__ RowLds<NDIM, false> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
-    arc_write_body<NDIM, MINMODE>(A, blk, nb, s_adj, tmp);
+    arc_write_body<NDIM, MINMODE>(A, blk, nb, T, tmp);
 }
 
 // Batches hold 2D and 3D fields of either graph: the body is chosen per
@@ -612,16 +747,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<N
 template <bool WRITE>
 __global__ __launch_bounds__(256) void k_arc_batched(BatchFields sel)
 {
-    __shared__ uint64_t s_adj[14];
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
     const int kind = __builtin_amdgcn_readfirstlane((A.ndim == 3 ? 2 : 0) + (A.minima ? 1 : 0));
-#define EG_BODY(ND, MM)                                                  \
-    if (WRITE)                                                           \
-        arc_write_body<ND, MM>(A, blk, nb, s_adj, tmp);                  \
-    else                                                                 \
-        arc_count_body<ND, MM>(A, blk, nb, s_adj, tmp);
+    using L3 = RowLds<3, !WRITE>;
+    using L2 = RowLds<2, !WRITE>;
+    __shared__ L3 T3;
+    L2& T2 = reinterpret_cast<L2&>(T3);
+#define EG_BODY(ND, MM)                               \
+    if (WRITE)                                        \
+        arc_write_body<ND, MM>(A, blk, nb, T##ND, tmp); \
+    else                                              \
+        arc_count_body<ND, MM>(A, blk, nb, T##ND, tmp);
     switch (kind) {
         case 0: EG_BODY(2, false) break;
         case 1: EG_BODY(2, true) break;
@@ -633,27 +771,21 @@ __global__ __launch_bounds__(256) void k_arc_batched(BatchFields sel)
 
 // ------------------------------------------------------------------ paths
 
-template <bool MINMODE>
-__device__ __forceinline__ uint32_t key_of(const ArcArgs& A, int x)
-{
-    return A.keys != nullptr ? A.keys[x] : mode_key<MINMODE>(A.f[x]);
-}
-
 // The walk of Alg. 2 from rep: visit(r) for rep and every vertex after it, up
 // to the maximum (ptr(m) = m).  Every step must stay in the grid and rise in
 // the order; a pointer that does not (out->ptr not holding this field's
 // pointers) ends the walk and returns false, so no input can make it leave
 // the grid or loop.
-template <bool MINMODE, class V>
+template <int NDIM, bool MINMODE, class V>
 __device__ __forceinline__ bool walk(const ArcArgs& A, EG_GPTR(const int32_t) const ptr, int r, V&& visit)
 {
     visit(r);
-    uint32_t ur = key_of<MINMODE>(A, r);
+    uint32_t ur = vertex_key<NDIM, MINMODE>(A, r);
     for (;;) {
         const int q = ptr[r];
         if (q == r) return true;
         if ((unsigned)q >= (unsigned)A.N) return false;
-        const uint32_t uq = key_of<MINMODE>(A, q);
+        const uint32_t uq = vertex_key<NDIM, MINMODE>(A, q);
         if (!(uq > ur || (uq == ur && (MINMODE ? q < r : q > r)))) return false;
         visit(q);
         r = q;
@@ -665,28 +797,27 @@ __device__ __forceinline__ bool walk(const ArcArgs& A, EG_GPTR(const int32_t) co
 // write pass in the workspace); the block's sums go to rows 0 and 1, and whether
 // a walk met a pointer that leaves the grid or does not rise to row 2.
 template <int NDIM, bool MINMODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<NDIM>, 8))) void k_path_count(
-    OneField sel, PathArgs P)
+__global__ __launch_bounds__(kArcThreads<NDIM>) void k_path_count(OneField sel, PathArgs P)
 {
-    __shared__ Mask<NDIM> s_adj[Rows<NDIM>::K];
+    constexpr int BT = kArcThreads<NDIM>;
+    __shared__ RowLds<NDIM, false> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
-    load_adj<NDIM>(A, s_adj);
+    load_rows(A, T);
     uint32_t lo, hi;
     chunk(saddle_count(A), nb, blk, lo, hi);
     uint32_t sp = 0, sv = 0;
     bool bad = false;
-    for (uint32_t i = lo + threadIdx.x; i < hi; i += 256) {
+    for (uint32_t i = lo + threadIdx.x; i < hi; i += BT) {
         const int v = A.saddles[i];
         uint32_t np = 0, nv = 0;
         if ((unsigned)v < (unsigned)A.N) {
-            Nbhd<NDIM, MINMODE> h;
-            load_nbhd<NDIM, MINMODE>(A, v, h);
-            for_each_rep<NDIM, MINMODE>(v, h, s_adj, [&](int rep) {
+            const LMask<NDIM> up = load_nbhd<NDIM, MINMODE>(A, v, T);
+            for_each_rep<NDIM, MINMODE>(A, v, up, T, [&](int rep) {
                 ++np;
                 ++nv;  // the saddle, then rep .. maximum
-                bad |= !walk<MINMODE>(A, P.ptr, rep, [&](int) { ++nv; });
+                bad |= !walk<NDIM, MINMODE>(A, P.ptr, rep, [&](int) { ++nv; });
             });
         } else {
             bad = true;
@@ -695,7 +826,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<N
         sp += np;
         sv += nv;
     }
-    block_sum2(sp, sv, tmp);
+    block_sum2<BT>(sp, sv, tmp);
     const int any_bad = __syncthreads_or(bad);
     if (threadIdx.x == 0) {
         A.bsum[blk] = sp;
@@ -705,36 +836,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<N
 }
 
 template <int NDIM, bool MINMODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<NDIM>, 8))) void k_path_write(
-    OneField sel, PathArgs P)
+__global__ __launch_bounds__(kArcThreads<NDIM>) void k_path_write(OneField sel, PathArgs P)
 {
-    __shared__ Mask<NDIM> s_adj[Rows<NDIM>::K];
+    constexpr int BT = kArcThreads<NDIM>;
+    __shared__ RowLds<NDIM, false> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
-    load_adj<NDIM>(A, s_adj);
+    load_rows(A, T);
     uint32_t lo, hi;
     chunk(saddle_count(A), nb, blk, lo, hi);
     uint32_t runp, runv;
-    sums_before(A, 0, blk, tmp, runp, runv);
-    for (uint32_t base = lo; base < hi; base += 256) {
+    sums_before<BT>(A, 0, blk, tmp, runp, runv);
+    for (uint32_t base = lo; base < hi; base += BT) {
         const uint32_t i = base + threadIdx.x;
         const bool valid = i < hi;
         const uint4 c = valid ? A.atmp[i] : make_uint4(0u, 0u, 0u, 0u);
         uint32_t tp, tv;
-        uint32_t pk = runp + block_excl_scan(c.x, tmp, tp);
-        uint32_t at = runv + block_excl_scan(c.y, tmp, tv);
+        uint32_t pk = runp + block_excl_scan<BT>(c.x, tmp, tp);
+        uint32_t at = runv + block_excl_scan<BT>(c.y, tmp, tv);
         const int v = valid ? A.saddles[i] : 0;
         if (valid) P.pair_offsets[i] = (int32_t)pk;
         if (valid && (unsigned)v < (unsigned)A.N) {
-            Nbhd<NDIM, MINMODE> h;
-            load_nbhd<NDIM, MINMODE>(A, v, h);
-            for_each_rep<NDIM, MINMODE>(v, h, s_adj, [&](int rep) {
+            const LMask<NDIM> up = load_nbhd<NDIM, MINMODE>(A, v, T);
+            for_each_rep<NDIM, MINMODE>(A, v, up, T, [&](int rep) {
                 if (pk <= P.cap_paths) P.path_offsets[pk] = (int32_t)at;
                 ++pk;
                 if (at < P.cap_vertices) P.vertices[at] = v;
                 ++at;
-                walk<MINMODE>(A, P.ptr, rep, [&](int r) {
+                walk<NDIM, MINMODE>(A, P.ptr, rep, [&](int r) {
                     if (at < P.cap_vertices) P.vertices[at] = r;
                     ++at;
                 });
@@ -747,7 +877,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<N
     // arrays, and the header
     if (blk != nb - 1) return;
     uint32_t bad = 0;
-    for (uint32_t i = threadIdx.x; i < nb; i += 256) bad |= A.bsum[2 * kSumRow + i];
+    for (uint32_t i = threadIdx.x; i < nb; i += BT) bad |= A.bsum[2 * kSumRow + i];
     const int any_bad = __syncthreads_or((int)bad);
     if (threadIdx.x != 0) return;
     const uint32_t nsad = A.ctr[C_NSAD];
@@ -762,8 +892,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kArcWaves<N
 template <int NDIM, bool MINMODE>
 static void launch_paths_t(const OneField& sel, const PathArgs& p, uint32_t nb, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_path_count<NDIM, MINMODE>), dim3(nb), dim3(256), 0, s, sel, p);
-    hipLaunchKernelGGL((k_path_write<NDIM, MINMODE>), dim3(nb), dim3(256), 0, s, sel, p);
+    hipLaunchKernelGGL((k_path_count<NDIM, MINMODE>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel, p);
+    hipLaunchKernelGGL((k_path_write<NDIM, MINMODE>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel, p);
 }
 
 hipError_t launch_paths(const ArcArgs& a, const PathArgs& p, hipStream_t s)
@@ -843,8 +973,8 @@ ArcArgs arc_args(const float* f, const Grid& g, const eg_out& o, const Work& w)
 template <int NDIM, bool MINMODE>
 static void launch_arc_pair(const OneField& sel, uint32_t nb, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_arc_count<NDIM, MINMODE>), dim3(nb), dim3(256), 0, s, sel);
-    hipLaunchKernelGGL((k_arc_write<NDIM, MINMODE>), dim3(nb), dim3(256), 0, s, sel);
+    hipLaunchKernelGGL((k_arc_count<NDIM, MINMODE>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel);
+    hipLaunchKernelGGL((k_arc_write<NDIM, MINMODE>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel);
 }
 
 hipError_t launch_arcs(const ArcArgs& a, hipStream_t s)
