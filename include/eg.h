@@ -439,6 +439,19 @@ size_t eg_order_workspace_bytes(int dtype, int64_t n);
 eg_status eg_order_field(int dtype, const void* field, int64_t n, float* out, void* workspace, size_t ws_bytes,
                          void* stream);
 
+/*
+ * eg_build and eg_paths of a field in its own sample type, without an order
+ * surrogate: a 3D field of any eg_dtype, or a float32 field of any dimension
+ * (then exactly eg_build and eg_paths).  Results equal those of the surrogate.
+ * The samples are naturally aligned.  Errors as eg_build and eg_paths, plus
+ * EG_ERR_ARG for an unknown dtype or another type than float32 on a grid that
+ * is not 3D.  The 3D tile of EG_TUNE_TILE3 applies to the label pass only.
+ */
+eg_status eg_build_typed(int dtype, const void* field, int ndim, const int64_t* dims, void* stream,
+                         const eg_out* out);
+eg_status eg_paths_typed(int dtype, const void* field, int ndim, const int64_t* dims, void* stream,
+                         const eg_out* out, const eg_paths_out* paths);
+
 /* Human-readable name of a status code (static string). */
 const char* eg_status_string(int status);
 

@@ -27,7 +27,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 # atomic per tile and needs its value only after the tile's pointer doubling;
 # the compiler's atomic optimizer would rewrite that atomic so that its result
 # is awaited at once, stalling the workgroup on a device-wide round trip.
-EXTRA = {"eg_classify_tiled.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
+_NO_ATOMIC_OPT = ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]
+EXTRA = {"eg_classify_tiled.hip": _NO_ATOMIC_OPT, "eg_classify_typed.hip": _NO_ATOMIC_OPT}
 
 
 def _compile(src: str, verbose: bool) -> str:

@@ -89,14 +89,40 @@ hipError_t stage_label(const Grid& g, const eg_out& o, const Work& w, const Tuni
 // Stage (d) and the canonical outputs: ascending maxima and saddles, the
 // arcs of every saddle as a CSR, and the header (which also reports labels
 // left unresolved by the last label kernel).
-hipError_t stage_arcs(const float* field, const Grid& g, const eg_out& o, const Work& w, hipStream_t s)
+hipError_t stage_arcs(const float* field, const Grid& g, const eg_out& o, const Work& w, hipStream_t s,
+                      int dtype = EG_F32)
 {
     ArcArgs a = arc_args(field, g, o, w);
+    a.dtype = dtype;
     a.last_flag = gptr<const uint32_t>(w.ctr + C_OPEN);
     return launch_arcs(a, s);
 }
 
 enum Stage { S_CLASSIFY = 1, S_LABEL = 2, S_ARCS = 4, S_ALL = 7 };
+
+// Field types that the kernels read as they are: float32, and 3D fields of
+// every other type.
+bool reads_type(int dtype, int ndim)
+{
+    return dtype == EG_F32 || (ndim == 3 && dtype > EG_F32 && dtype <= EG_U64);
+}
+
+eg_status run_typed(int dtype, const void* field, const int64_t* dims, void* stream, const eg_out* out)
+{
+    Grid g;
+    Work w;
+    const eg_status st = check_one((const float*)field, 3, dims, out, &g, &w);
+    if (st != EG_OK) return st;
+    Tuning tu;
+    decode_tuning(out->tuning, &tu);
+    hipStream_t s = (hipStream_t)stream;
+    const bool minima = (out->flags & EG_MINIMA) != 0;
+    hipError_t e = launch_init(g, w, out->header, s);
+    if (e == hipSuccess) e = launch_classify_typed(dtype, field, g, minima, out->labels, out->ptr, w, s);
+    if (e == hipSuccess) e = stage_label(g, *out, w, tu, s);
+    if (e == hipSuccess) e = stage_arcs((const float*)field, g, *out, w, s, dtype);
+    return e == hipSuccess ? EG_OK : EG_ERR_HIP;
+}
 
 eg_status run_stages(int stages, const float* field, int ndim, const int64_t* dims, void* stream,
                      const eg_out* out)
@@ -289,12 +315,14 @@ eg_status eg_build_batched(const void* host_plan, void* stream)
     return e == hipSuccess ? EG_OK : EG_ERR_HIP;
 }
 
-eg_status eg_paths(const float* field, int ndim, const int64_t* dims, void* stream, const eg_out* out,
-                   const eg_paths_out* paths)
+eg_status eg_paths_typed(int dtype, const void* field, int ndim, const int64_t* dims, void* stream, const eg_out* out,
+                         const eg_paths_out* paths)
 {
+    if (!reads_type(dtype, ndim)) return EG_ERR_ARG;
+    const float* f = (const float*)field;
     Grid g;
     Work w;
-    const eg_status st = check_one(field, ndim, dims, out, &g, &w);
+    const eg_status st = check_one(f, ndim, dims, out, &g, &w);
     if (st != EG_OK) return st;
     if (!paths || !out->ptr || !paths->pair_offsets || !paths->path_offsets || !paths->header) return EG_ERR_ARG;
     if (paths->cap_paths < 0 || paths->cap_vertices < 0) return EG_ERR_TOO_LARGE;
@@ -308,8 +336,16 @@ eg_status eg_paths(const float* field, int ndim, const int64_t* dims, void* stre
     p.header = gptr(paths->header);
     p.cap_paths = (uint32_t)paths->cap_paths;
     p.cap_vertices = (uint32_t)paths->cap_vertices;
-    const hipError_t e = launch_paths(arc_args(field, g, *out, w), p, (hipStream_t)stream);
+    ArcArgs a = arc_args(f, g, *out, w);
+    a.dtype = dtype;
+    const hipError_t e = launch_paths(a, p, (hipStream_t)stream);
     return e == hipSuccess ? EG_OK : EG_ERR_HIP;
+}
+
+eg_status eg_paths(const float* field, int ndim, const int64_t* dims, void* stream, const eg_out* out,
+                   const eg_paths_out* paths)
+{
+    return eg_paths_typed(EG_F32, field, ndim, dims, stream, out, paths);
 }
 
 size_t eg_workspace_bytes(int ndim, const int64_t* dims, int64_t cap_sad)
@@ -323,6 +359,13 @@ size_t eg_workspace_bytes(int ndim, const int64_t* dims, int64_t cap_sad)
 eg_status eg_build(const float* field, int ndim, const int64_t* dims, void* stream, const eg_out* out)
 {
     return run_stages(S_ALL, field, ndim, dims, stream, out);
+}
+
+eg_status eg_build_typed(int dtype, const void* field, int ndim, const int64_t* dims, void* stream, const eg_out* out)
+{
+    if (!reads_type(dtype, ndim)) return EG_ERR_ARG;
+    if (dtype == EG_F32) return run_stages(S_ALL, (const float*)field, ndim, dims, stream, out);
+    return run_typed(dtype, field, dims, stream, out);
 }
 
 eg_status eg_build_noalloc(const float* field, int ndim, const int64_t* dims, void* stream, const eg_out* out)

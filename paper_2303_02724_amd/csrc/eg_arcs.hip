@@ -26,6 +26,7 @@
 #include "eg_internal.h"
 #include "eg_rows.h"
 #include "eg_link.h"
+#include "eg_sample.h"
 
 namespace eg {
 
@@ -257,7 +258,19 @@ __device__ __forceinline__ int low_row(uint64_t m) { return lowest_bit(m); }
 __device__ __forceinline__ int low_row(unsigned __int128 m) { return lowest_bit(m); }
 
 // 1D and 4D-6D classification stores every vertex's order key (already
-// reversed for the minimum graph); 2D and 3D read the field.
+// reversed for the minimum graph); 2D and 3D read the field.  Fields of other
+// sample types (3D) are read in their own type: 32-bit keys for 8- and 16-bit
+// integers, exact 64-bit keys for the wider types.
+template <int SRC>
+struct VertexKey {
+    using type = uint32_t;
+};
+template <>
+struct VertexKey<SRC_WIDE> {
+    using type = uint64_t;
+};
+template <int SRC>
+using VKey = typename VertexKey<SRC>::type;
 template <int NDIM>
 constexpr bool kStoredKeys = NDIM != 2 && NDIM != 3;
 // Up to 5D a thread of k_arc_count parks the keys of its saddle's
@@ -284,10 +297,14 @@ constexpr int kArcThreads = NDIM == 5 ? 128 : 256;
 template <int NDIM>
 constexpr int kArcWaves = NDIM == 6 ? 2 : 8;
 
-template <int NDIM, bool MINMODE>
-__device__ __forceinline__ uint32_t vertex_key(const ArcArgs& A, int v)
+template <int NDIM, bool MINMODE, int SRC>
+__device__ __forceinline__ VKey<SRC> vertex_key(const ArcArgs& A, int v)
 {
-    if constexpr (kStoredKeys<NDIM>)
+    if constexpr (SRC == SRC_WIDE)
+        return exact_key<MINMODE>(A.f, A.dtype, v);
+    else if constexpr (SRC == SRC_INT)
+        return int_key<MINMODE>(A.f, A.dtype, v);
+    else if constexpr (kStoredKeys<NDIM>)
         return A.keys[v];
     else
         return mode_key<MINMODE>(A.f[v]);
@@ -295,13 +312,14 @@ __device__ __forceinline__ uint32_t vertex_key(const ArcArgs& A, int v)
 
 // LDS of a block of the arc and path kernels: the rows' linear offsets, and
 // the keys (row j of thread t at keys[j][t]) where they are parked.
-template <int NDIM, bool PARK>
+template <int NDIM, bool PARK, int SRC_ = SRC_F32>
 struct RowLds {
     static constexpr int K = Rows<NDIM>::K;
     static constexpr int N = NDIM;
+    static constexpr int SRC = SRC_;
     static constexpr bool kPark = PARK;
+    VKey<SRC> keys[PARK ? K : 1][PARK ? kArcThreads<NDIM> : 1];
     int off[K];
-    uint32_t keys[PARK ? K : 1][PARK ? kArcThreads<NDIM> : 1];
 };
 
 template <class LDS>
@@ -343,7 +361,7 @@ __device__ __forceinline__ LMask<NDIM> load_nbhd(const ArcArgs& A, int v, LDS& T
             stride *= d;
         }
     }
-    const uint32_t uv = vertex_key<NDIM, MINMODE>(A, v);
+    const VKey<LDS::SRC> uv = vertex_key<NDIM, MINMODE, LDS::SRC>(A, v);
     // 32 rows per word, pushed from the highest row down
     constexpr int NW = (K + 31) / 32;
     uint32_t wd[NW];
@@ -360,11 +378,13 @@ __device__ __forceinline__ LMask<NDIM> load_nbhd(const ArcArgs& A, int v, LDS& T
             }
         }
         // no branch around the load: every row's load is in flight at once
-        const uint32_t x = vertex_key<NDIM, MINMODE>(A, in ? v + off : v);
-        const uint32_t u = in ? x : 0u;
+        const VKey<LDS::SRC> x = vertex_key<NDIM, MINMODE, LDS::SRC>(A, in ? v + off : v);
+        const VKey<LDS::SRC> u = in ? x : 0;
         if constexpr (LDS::kPark) T.keys[j][threadIdx.x] = u;
         constexpr bool wins = (j >= K / 2) != MINMODE;
-        if constexpr (j == K - 1 || j % 32 == 31)
+        if constexpr (LDS::SRC == SRC_WIDE)  // a wide sample's key may be 0 itself
+            wd[0] = (j == K - 1 ? 0u : 2u * wd[0]) | (in && (wins ? u >= uv : u > uv) ? 1u : 0u);
+        else if constexpr (j == K - 1 || j % 32 == 31)
             wd[j / 32] = first_above<wins>(u, uv);
         else
             wd[j / 32] = push_above<wins>(wd[j / 32], u, uv);
@@ -409,12 +429,12 @@ __device__ __forceinline__ LMask<NDIM> first_component(LMask<NDIM> rem)
 
 // The key of row j of saddle v's link (a row in the grid).
 template <int NDIM, bool MINMODE, class LDS>
-__device__ __forceinline__ uint32_t key_at(const ArcArgs& A, int v, int j, const LDS& T)
+__device__ __forceinline__ VKey<LDS::SRC> key_at(const ArcArgs& A, int v, int j, const LDS& T)
 {
     if constexpr (LDS::kPark)
         return T.keys[j][threadIdx.x];
     else
-        return vertex_key<NDIM, MINMODE>(A, v + T.off[j]);
+        return vertex_key<NDIM, MINMODE, LDS::SRC>(A, v + T.off[j]);
 }
 
 // The highest vertex of a component (UpperLinkRep, Sec. 3.4): its rows in
@@ -423,17 +443,17 @@ __device__ __forceinline__ uint32_t key_at(const ArcArgs& A, int v, int j, const
 template <int NDIM, bool MINMODE, class LDS>
 __device__ __forceinline__ int rep_of(const ArcArgs& A, int v, LMask<NDIM> comp, const LDS& T)
 {
-    uint32_t best_u = 0;
-    int best = 0;
     // two rows a round (the second again the first when there is none left),
     // so that two reads are in flight
+    VKey<LDS::SRC> best_u = 0;
+    int best = low_row(comp);
     do {
         const int j0 = low_row(comp);
         comp &= comp - 1;
         const int j1 = comp != 0 ? low_row(comp) : j0;
         comp &= comp - 1;  // 0 & anything stays 0
-        const uint32_t u0 = key_at<NDIM, MINMODE>(A, v, j0, T);
-        const uint32_t u1 = key_at<NDIM, MINMODE>(A, v, j1, T);
+        const VKey<LDS::SRC> u0 = key_at<NDIM, MINMODE>(A, v, j0, T);
+        const VKey<LDS::SRC> u1 = key_at<NDIM, MINMODE>(A, v, j1, T);
         const bool w0 = MINMODE ? u0 > best_u : u0 >= best_u;
         best_u = w0 ? u0 : best_u;
         best = w0 ? j0 : best;
@@ -721,21 +741,21 @@ __device__ __forceinline__ void arc_write_body(const ArcArgs& A, uint32_t blk, u
     if (blk == nb - 1 && tid == 0) write_header(A, run, pairs + A.bsum[3 * kSumRow + blk]);
 }
 
-template <int NDIM, bool MINMODE>
+template <int NDIM, bool MINMODE, int SRC = SRC_F32>
 __global__ __launch_bounds__(kArcThreads<NDIM>)
     __attribute__((amdgpu_waves_per_eu(1, kArcWaves<NDIM>))) void k_arc_count(OneField sel)
 {
-    __shared__ RowLds<NDIM, kKeysInLds<NDIM>> T;
+    __shared__ RowLds<NDIM, kKeysInLds<NDIM>, SRC> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
     arc_count_body<NDIM, MINMODE>(A, blk, nb, T, tmp);
 }
 
-template <int NDIM, bool MINMODE>
+template <int NDIM, bool MINMODE, int SRC = SRC_F32>
 __global__ __launch_bounds__(kArcThreads<NDIM>) void k_arc_write(OneField sel)
 {
-    __shared__ RowLds<NDIM, false> T;
+    __shared__ RowLds<NDIM, false, SRC> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
@@ -776,16 +796,16 @@ __global__ __launch_bounds__(256) void k_arc_batched(BatchFields sel)
 // the order; a pointer that does not (out->ptr not holding this field's
 // pointers) ends the walk and returns false, so no input can make it leave
 // the grid or loop.
-template <int NDIM, bool MINMODE, class V>
+template <int NDIM, bool MINMODE, int SRC, class V>
 __device__ __forceinline__ bool walk(const ArcArgs& A, EG_GPTR(const int32_t) const ptr, int r, V&& visit)
 {
     visit(r);
-    uint32_t ur = vertex_key<NDIM, MINMODE>(A, r);
+    VKey<SRC> ur = vertex_key<NDIM, MINMODE, SRC>(A, r);
     for (;;) {
         const int q = ptr[r];
         if (q == r) return true;
         if ((unsigned)q >= (unsigned)A.N) return false;
-        const uint32_t uq = vertex_key<NDIM, MINMODE>(A, q);
+        const VKey<SRC> uq = vertex_key<NDIM, MINMODE, SRC>(A, q);
         if (!(uq > ur || (uq == ur && (MINMODE ? q < r : q > r)))) return false;
         visit(q);
         r = q;
@@ -796,11 +816,11 @@ __device__ __forceinline__ bool walk(const ArcArgs& A, EG_GPTR(const int32_t) co
 // Paths and path vertices of every saddle of the block's chunk (kept for the
 // write pass in the workspace); the block's sums go to rows 0 and 1, and whether
 // a walk met a pointer that leaves the grid or does not rise to row 2.
-template <int NDIM, bool MINMODE>
+template <int NDIM, bool MINMODE, int SRC = SRC_F32>
 __global__ __launch_bounds__(kArcThreads<NDIM>) void k_path_count(OneField sel, PathArgs P)
 {
     constexpr int BT = kArcThreads<NDIM>;
-    __shared__ RowLds<NDIM, false> T;
+    __shared__ RowLds<NDIM, false, SRC> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
@@ -817,7 +837,7 @@ __global__ __launch_bounds__(kArcThreads<NDIM>) void k_path_count(OneField sel, 
             for_each_rep<NDIM, MINMODE>(A, v, up, T, [&](int rep) {
                 ++np;
                 ++nv;  // the saddle, then rep .. maximum
-                bad |= !walk<NDIM, MINMODE>(A, P.ptr, rep, [&](int) { ++nv; });
+                bad |= !walk<NDIM, MINMODE, SRC>(A, P.ptr, rep, [&](int) { ++nv; });
             });
         } else {
             bad = true;
@@ -835,11 +855,11 @@ __global__ __launch_bounds__(kArcThreads<NDIM>) void k_path_count(OneField sel, 
     }
 }
 
-template <int NDIM, bool MINMODE>
+template <int NDIM, bool MINMODE, int SRC = SRC_F32>
 __global__ __launch_bounds__(kArcThreads<NDIM>) void k_path_write(OneField sel, PathArgs P)
 {
     constexpr int BT = kArcThreads<NDIM>;
-    __shared__ RowLds<NDIM, false> T;
+    __shared__ RowLds<NDIM, false, SRC> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
@@ -864,7 +884,7 @@ __global__ __launch_bounds__(kArcThreads<NDIM>) void k_path_write(OneField sel, 
                 ++pk;
                 if (at < P.cap_vertices) P.vertices[at] = v;
                 ++at;
-                walk<NDIM, MINMODE>(A, P.ptr, rep, [&](int r) {
+                walk<NDIM, MINMODE, SRC>(A, P.ptr, rep, [&](int r) {
                     if (at < P.cap_vertices) P.vertices[at] = r;
                     ++at;
                 });
@@ -889,11 +909,11 @@ __global__ __launch_bounds__(kArcThreads<NDIM>) void k_path_write(OneField sel, 
     P.header[EG_P_VERTICES] = (int32_t)runv;
 }
 
-template <int NDIM, bool MINMODE>
+template <int NDIM, bool MINMODE, int SRC = SRC_F32>
 static void launch_paths_t(const OneField& sel, const PathArgs& p, uint32_t nb, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_path_count<NDIM, MINMODE>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel, p);
-    hipLaunchKernelGGL((k_path_write<NDIM, MINMODE>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel, p);
+    hipLaunchKernelGGL((k_path_count<NDIM, MINMODE, SRC>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel, p);
+    hipLaunchKernelGGL((k_path_write<NDIM, MINMODE, SRC>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel, p);
 }
 
 hipError_t launch_paths(const ArcArgs& a, const PathArgs& p, hipStream_t s)
@@ -906,6 +926,22 @@ hipError_t launch_paths(const ArcArgs& a, const PathArgs& p, hipStream_t s)
     if (nbp > ap.arc_blocks) ap.arc_blocks = (int32_t)nbp;
     const OneField sel{ap};
     const uint32_t nb = (uint32_t)ap.arc_blocks;
+    if (a.dtype != EG_F32) {
+        if (a.ndim != 3) return hipErrorInvalidValue;
+        const bool wide = sample_source(a.dtype) == SRC_WIDE;
+        if (a.minima) {
+            if (wide)
+                launch_paths_t<3, true, SRC_WIDE>(sel, p, nb, s);
+            else
+                launch_paths_t<3, true, SRC_INT>(sel, p, nb, s);
+        } else {
+            if (wide)
+                launch_paths_t<3, false, SRC_WIDE>(sel, p, nb, s);
+            else
+                launch_paths_t<3, false, SRC_INT>(sel, p, nb, s);
+        }
+        return hipGetLastError();
+    }
 #define EG_CASE(N)                                    \
     case N:                                           \
         if (a.minima)                                 \
@@ -970,11 +1006,11 @@ ArcArgs arc_args(const float* f, const Grid& g, const eg_out& o, const Work& w)
     return a;
 }
 
-template <int NDIM, bool MINMODE>
+template <int NDIM, bool MINMODE, int SRC = SRC_F32>
 static void launch_arc_pair(const OneField& sel, uint32_t nb, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_arc_count<NDIM, MINMODE>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel);
-    hipLaunchKernelGGL((k_arc_write<NDIM, MINMODE>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel);
+    hipLaunchKernelGGL((k_arc_count<NDIM, MINMODE, SRC>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel);
+    hipLaunchKernelGGL((k_arc_write<NDIM, MINMODE, SRC>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel);
 }
 
 hipError_t launch_arcs(const ArcArgs& a, hipStream_t s)
@@ -983,6 +1019,22 @@ hipError_t launch_arcs(const ArcArgs& a, hipStream_t s)
     const uint32_t nb = (uint32_t)a.arc_blocks;
     hipLaunchKernelGGL(k_mask_count<OneField>, dim3(nb), dim3(256), 0, s, sel);
     hipLaunchKernelGGL(k_mask_emit<OneField>, dim3(nb), dim3(256), 0, s, sel);
+    if (a.dtype != EG_F32) {
+        if (a.ndim != 3) return hipErrorInvalidValue;
+        const bool wide = sample_source(a.dtype) == SRC_WIDE;
+        if (a.minima) {
+            if (wide)
+                launch_arc_pair<3, true, SRC_WIDE>(sel, nb, s);
+            else
+                launch_arc_pair<3, true, SRC_INT>(sel, nb, s);
+        } else {
+            if (wide)
+                launch_arc_pair<3, false, SRC_WIDE>(sel, nb, s);
+            else
+                launch_arc_pair<3, false, SRC_INT>(sel, nb, s);
+        }
+        return hipGetLastError();
+    }
 #define EG_CASE(N)                                  \
     case N:                                         \
         if (a.minima)                               \

@@ -131,7 +131,7 @@ struct TileArgs {
     EG_GPTR(uint64_t) smask;
     EG_GPTR(uint32_t) exits;
     int32_t X, Y, Z, tiles_x, tiles_y, ntiles;
-    uint32_t cap_exit, pad0;
+    uint32_t cap_exit, dtype;  // dtype: the samples behind f (eg_dtype)
 };
 
 // Everything stage (d) needs to know about its field.
@@ -154,7 +154,7 @@ struct ArcArgs {
     int32_t dims[EG_MAX_NDIM];
     uint32_t cap_max, cap_sad, cap_arc;
     int32_t arc_blocks;  // blocks of this field in the stage (d) kernels (<= kArcBlocks)
-    int32_t pad0;
+    int32_t dtype;       // the samples behind f (eg_dtype)
     // flag of the last label kernel (set: some label is still a code, the
     // header reports EG_ERR_UNRESOLVED); null: not checked
     EG_GPTR(const uint32_t) last_flag;
@@ -344,6 +344,9 @@ hipError_t launch_classify(const float* f, const Grid& g, const LinkTable& t, bo
 hipError_t launch_classify_tiled(const float* f, const Grid& g, bool minima, int32_t* lab, int32_t* ptr,
                                  const Work& w, const Tuning& tu, hipStream_t s, int64_t first = 0,
                                  int64_t count = -1);
+// The same for a 3D field of another sample type (the default tile).
+hipError_t launch_classify_typed(int dtype, const void* f, const Grid& g, bool minima, int32_t* lab, int32_t* ptr,
+                                 const Work& w, hipStream_t s);
 TileArgs tile_args(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, const Work& w, int ty, int tz);
 ArcArgs arc_args(const float* f, const Grid& g, const eg_out& o, const Work& w);
 uint32_t arc_blocks(int64_t N);

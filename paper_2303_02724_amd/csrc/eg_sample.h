@@ -1,0 +1,131 @@
+// eg_sample.h -- keys of the sample types other than float32 (eg_dtype).
+//
+// Two orders of a sample are used.  exact_key is an unsigned integer with
+// exactly the order of the samples.  tile_key is a 32-bit key whose order
+// never contradicts it but may make different samples equal: 8- and 16-bit
+// integers keep all of theirs, 32-bit integers all but the two at either end
+// (the key 0 is taken by positions outside the grid), and the 64-bit types go
+// through their nearest float32 (a monotone rounding).  A tile compares the
+// 32-bit keys and looks at the samples themselves only where two of them meet.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "eg_internal.h"
+
+namespace eg {
+
+// Where a kernel's samples come from.
+enum : int {
+    SRC_F32 = 0,   // float32, or the stored order keys
+    SRC_INT = 1,   // 8- and 16-bit integers: the 32-bit key is exact
+    SRC_WIDE = 2,  // 32- and 64-bit integers and float64
+};
+
+__host__ __device__ inline int sample_source(int dtype)
+{
+    return dtype == EG_F32 ? SRC_F32 : dtype >= EG_I8 && dtype <= EG_U16 ? SRC_INT : SRC_WIDE;
+}
+__host__ __device__ inline int sample_size(int dtype)
+{
+    return dtype == EG_I8 || dtype == EG_U8     ? 1
+           : dtype == EG_I16 || dtype == EG_U16 ? 2
+           : dtype == EG_F32 || dtype == EG_I32 || dtype == EG_U32 ? 4
+                                                                   : 8;
+}
+
+// An order-preserving key of the bit pattern, in four instructions: negative
+// values map to -b, the others to b | 2^31, so -0 and +0 meet at 2^31 and the
+// order of the numbers is kept (keys of the same value are equal, the index
+// decides); the top is clamped, so every vertex key lies in [1, 0xFFFFFFFE]
+// and the key 0 of positions outside the grid stays below all of them, NaN
+// included: no pointer can leave the grid.  The minimum graph takes the
+// complement.
+template <bool MINMODE>
+__device__ __forceinline__ uint32_t bits_key(uint32_t b)
+{
+    const uint32_t m = (uint32_t)((int32_t)b >> 31);
+    const uint32_t k = min((b ^ (m | 0x80000000u)) - m, 0xFFFFFFFEu);
+    return MINMODE ? ~k : k;
+}
+
+template <bool MINMODE>
+__device__ __forceinline__ uint32_t tile_key(double x)
+{
+    return bits_key<MINMODE>(__float_as_uint((float)x));
+}
+template <bool MINMODE>
+__device__ __forceinline__ uint32_t tile_key(int64_t x)
+{
+    return bits_key<MINMODE>(__float_as_uint((float)x));
+}
+template <bool MINMODE>
+__device__ __forceinline__ uint32_t tile_key(uint64_t x)
+{
+    return bits_key<MINMODE>(__float_as_uint((float)x));
+}
+template <bool MINMODE>
+__device__ __forceinline__ uint32_t tile_key(uint32_t x)
+{
+    const uint32_t k = min(max(x, 1u), 0xFFFFFFFEu);
+    return MINMODE ? ~k : k;
+}
+template <bool MINMODE>
+__device__ __forceinline__ uint32_t tile_key(int32_t x)
+{
+    return tile_key<MINMODE>((uint32_t)x ^ 0x80000000u);
+}
+// 8- and 16-bit integers: 1 .. 98304, spread out so that keys of different
+// samples differ above the four bits that the tiles' steepest candidate drops
+template <bool MINMODE, class T>
+__device__ __forceinline__ uint32_t tile_key_int(T x)
+{
+    const uint32_t k = (uint32_t)((int)x + 32769) << 15;
+    return MINMODE ? ~k : k;
+}
+template <bool MINMODE>
+__device__ __forceinline__ uint32_t tile_key(int8_t x) { return tile_key_int<MINMODE>(x); }
+template <bool MINMODE>
+__device__ __forceinline__ uint32_t tile_key(uint8_t x) { return tile_key_int<MINMODE>(x); }
+template <bool MINMODE>
+__device__ __forceinline__ uint32_t tile_key(int16_t x) { return tile_key_int<MINMODE>(x); }
+template <bool MINMODE>
+__device__ __forceinline__ uint32_t tile_key(uint16_t x) { return tile_key_int<MINMODE>(x); }
+
+// The 32-bit key of vertex v of a field of 8- or 16-bit integers.
+template <bool MINMODE>
+__device__ __forceinline__ uint32_t int_key(EG_GPTR(const float) f, int dtype, int64_t v)
+{
+    int x;
+    if (dtype == EG_U8)
+        x = ((EG_GPTR(const uint8_t))f)[v];
+    else if (dtype == EG_I8)
+        x = ((EG_GPTR(const int8_t))f)[v];
+    else if (dtype == EG_U16)
+        x = ((EG_GPTR(const uint16_t))f)[v];
+    else
+        x = ((EG_GPTR(const int16_t))f)[v];
+    return tile_key_int<MINMODE>(x);
+}
+
+// The exact key of vertex v of a field of a wide type: -0 meets +0, the
+// minimum graph takes the complement.
+template <bool MINMODE>
+__device__ __forceinline__ uint64_t exact_key(EG_GPTR(const float) f, int dtype, int64_t v)
+{
+    uint64_t k;
+    if (dtype == EG_I32 || dtype == EG_U32) {
+        k = ((EG_GPTR(const uint32_t))f)[v] ^ (dtype == EG_I32 ? 0x80000000u : 0u);
+    } else {
+        k = ((EG_GPTR(const uint64_t))f)[v];
+        if (dtype == EG_F64) {
+            k = (uint64_t)__double_as_longlong(__longlong_as_double((long long)k) + 0.0);
+            k ^= (uint64_t)((int64_t)k >> 63) | (uint64_t(1) << 63);
+        } else if (dtype == EG_I64) {
+            k ^= uint64_t(1) << 63;
+        }
+    }
+    return MINMODE ? ~k : k;
+}
+
+}  // namespace eg

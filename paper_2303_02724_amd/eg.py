@@ -121,6 +121,10 @@ def lib():
     L.eg_noalloc_scratch_bytes.restype = ctypes.c_size_t
     L.eg_paths.argtypes = [vp, ctypes.c_int, i64p, vp, ctypes.POINTER(eg_out), ctypes.POINTER(eg_paths_out)]
     L.eg_paths.restype = ctypes.c_int
+    L.eg_build_typed.argtypes = [ctypes.c_int] + L.eg_build.argtypes
+    L.eg_build_typed.restype = ctypes.c_int
+    L.eg_paths_typed.argtypes = [ctypes.c_int] + L.eg_paths.argtypes
+    L.eg_paths_typed.restype = ctypes.c_int
     L.eg_simplify.argtypes = [ctypes.POINTER(eg_graph_host), ctypes.c_uint32, ctypes.c_double, vp, vp, vp, vp, vp,
                               vp, ctypes.POINTER(ctypes.c_int64)]
     L.eg_simplify.restype = ctypes.c_int
@@ -332,6 +336,13 @@ class Builder:
         self.out = o
         self._dims = _dims(self.shape)
 
+    def _typed(self, field: torch.Tensor) -> bool:
+        """Whether the library reads ``field`` in its own sample type (3D builds
+        and paths; misaligned views take the surrogate)."""
+        return (len(self.shape) == 3 and not self.noalloc and field.dtype != torch.float32 and field.dtype in DTYPES
+                and field.is_cuda and field.is_contiguous() and field.numel() == self.n
+                and field.data_ptr() % field.element_size() == 0)
+
     def _float_field(self, field: torch.Tensor, s) -> torch.Tensor:
         """``field`` itself for float32, else its order surrogate (queued on s)."""
         if not field.is_cuda or not field.is_contiguous():
@@ -350,9 +361,17 @@ class Builder:
     def launch(self, field: torch.Tensor, stream=None, stage: str = "all"):
         """Queue the whole path (``stage="all"``, eg_build) or one stage
         (``"classify"``, ``"label"``, ``"arcs"``) on ``stream`` (default: the
-        current stream).  Fields of other sample types than float32 are first
-        replaced by their order surrogate (eg_order_field)."""
+        current stream).  Whole builds of 3D fields read other sample types than
+        float32 as they are (eg_build_typed); elsewhere such a field is first
+        replaced by its order surrogate (eg_order_field)."""
         s = stream if stream is not None else torch.cuda.current_stream(self.device)
+        if stage == "all" and self._typed(field):
+            st = lib().eg_build_typed(DTYPES[field.dtype], ctypes.c_void_p(field.data_ptr()), 3, self._dims,
+                                      ctypes.c_void_p(s.cuda_stream), ctypes.byref(self.out))
+            if st != EG_OK:
+                raise EGError(st)
+            self._stream = s
+            return
         field = self._float_field(field, s)
         if self.noalloc and stage != "all":
             raise EGError(EG_ERR_ARG, "a no-alloc builder runs whole builds only")
@@ -452,9 +471,10 @@ class Builder:
         if self.ptr is None:
             raise EGError(EG_ERR_ARG, "paths need the steepest-ascent pointers: Builder(..., want_ptr=True)")
         s = stream if stream is not None else torch.cuda.current_stream(self.device)
-        field = self._float_field(field, s)
-        st = lib().eg_paths(ctypes.c_void_p(field.data_ptr()), len(self.shape), self._dims,
-                            ctypes.c_void_p(s.cuda_stream), ctypes.byref(self.out), ctypes.byref(self.pout))
+        if not self._typed(field):
+            field = self._float_field(field, s)
+        st = lib().eg_paths_typed(DTYPES[field.dtype], ctypes.c_void_p(field.data_ptr()), len(self.shape), self._dims,
+                                  ctypes.c_void_p(s.cuda_stream), ctypes.byref(self.out), ctypes.byref(self.pout))
         if st != EG_OK:
             raise EGError(st, "eg_paths")
         self._stream = s
