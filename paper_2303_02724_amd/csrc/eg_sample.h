@@ -6,7 +6,10 @@
 // integers keep all of theirs, 32-bit integers all but the two at either end
 // (the key 0 is taken by positions outside the grid), and the 64-bit types go
 // through their nearest float32 (a monotone rounding).  A tile compares the
-// 32-bit keys and looks at the samples themselves only where two of them meet.
+// 32-bit keys and looks at the samples themselves only where two of them meet
+// and some key of the tile is not exact.  Tiles whose samples lie close
+// together (plateaus, a large offset with small differences) take the distances
+// of the exact keys from one of them as their keys.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -108,23 +111,42 @@ __device__ __forceinline__ uint32_t int_key(EG_GPTR(const float) f, int dtype, i
     return tile_key_int<MINMODE>(x);
 }
 
-// The exact key of vertex v of a field of a wide type: -0 meets +0, the
-// minimum graph takes the complement.
+// Unsigned integers with exactly the order of the samples (-0 meets +0).
+__device__ __forceinline__ uint64_t exact_of(double x)
+{
+    const uint64_t k = (uint64_t)__double_as_longlong(x + 0.0);
+    return k ^ ((uint64_t)((int64_t)k >> 63) | (uint64_t(1) << 63));
+}
+__device__ __forceinline__ uint64_t exact_of(int64_t x) { return (uint64_t)x ^ (uint64_t(1) << 63); }
+__device__ __forceinline__ uint64_t exact_of(uint64_t x) { return x; }
+__device__ __forceinline__ uint64_t exact_of(int32_t x) { return (uint32_t)x ^ 0x80000000u; }
+__device__ __forceinline__ uint64_t exact_of(uint32_t x) { return x; }
+
+// Whether samples with this sample's tile_key are all equal to it (a
+// sufficient test for the integers).
+__device__ __forceinline__ bool key_is_exact(double x) { return (double)(float)x == x; }
+__device__ __forceinline__ bool key_is_exact(int64_t x)
+{
+    return (uint64_t)(x + (int64_t(1) << 24)) <= (uint64_t(1) << 25);
+}
+__device__ __forceinline__ bool key_is_exact(uint64_t x) { return x <= (uint64_t(1) << 24); }
+__device__ __forceinline__ bool key_is_exact(uint32_t x) { return x - 2u <= 0xFFFFFFFBu; }
+__device__ __forceinline__ bool key_is_exact(int32_t x) { return key_is_exact((uint32_t)x ^ 0x80000000u); }
+
+// The exact key of vertex v of a field of a wide type; the minimum graph takes
+// the complement.
 template <bool MINMODE>
 __device__ __forceinline__ uint64_t exact_key(EG_GPTR(const float) f, int dtype, int64_t v)
 {
     uint64_t k;
-    if (dtype == EG_I32 || dtype == EG_U32) {
-        k = ((EG_GPTR(const uint32_t))f)[v] ^ (dtype == EG_I32 ? 0x80000000u : 0u);
-    } else {
+    if (dtype == EG_F64)
+        k = exact_of(((EG_GPTR(const double))f)[v]);
+    else if (dtype == EG_I64)
+        k = exact_of(((EG_GPTR(const int64_t))f)[v]);
+    else if (dtype == EG_U64)
         k = ((EG_GPTR(const uint64_t))f)[v];
-        if (dtype == EG_F64) {
-            k = (uint64_t)__double_as_longlong(__longlong_as_double((long long)k) + 0.0);
-            k ^= (uint64_t)((int64_t)k >> 63) | (uint64_t(1) << 63);
-        } else if (dtype == EG_I64) {
-            k ^= uint64_t(1) << 63;
-        }
-    }
+    else
+        k = ((EG_GPTR(const uint32_t))f)[v] ^ (dtype == EG_I32 ? 0x80000000u : 0u);
     return MINMODE ? ~k : k;
 }
 

@@ -479,9 +479,14 @@ struct Win {
 // Halo of a 3D tile of a field of samples T: rows of 64 aligned values, one
 // per lane, from a uniform row address (rows outside the grid read a clamped
 // row), then the two edge columns of every row; all loads first.  Positions
-// outside the grid get the key 0.  Returns whether a sample is a NaN.
+// outside the grid get the key 0.  `nan`: a sample is a NaN; returns whether
+// equal keys of this tile mean equal samples.  For the wide types that holds
+// where the exact keys lie within 2^31 of the tile's first vertex's (then
+// their distances are the keys), or where every sample is a float32 (or short
+// of the clamped ends, for 32-bit integers); uses s_flag[0..3].
 template <class T, bool MINMODE, int TY, int TZ, bool FULL>
-__device__ __forceinline__ bool stage_samples(const TileArgs& a, int x0, int y0, int z0, uint32_t* s_u)
+__device__ __forceinline__ bool stage_samples(const TileArgs& a, int x0, int y0, int z0, uint32_t* s_u,
+                                              uint32_t* s_flag, bool& nan)
 {
     constexpr int HX = 66, HY = TY + 2, HZ = TZ + 2;
     constexpr int ROWS = HY * HZ;
@@ -506,24 +511,55 @@ __device__ __forceinline__ bool stage_samples(const TileArgs& a, int x0, int y0,
     const bool ein = tid < EDGES && (unsigned)egx < (unsigned)X && (unsigned)egy < (unsigned)Y &&
                      (unsigned)egz < (unsigned)Z;
     const T eval = f[ein ? (int64_t)(egz * Y + egy) * X + egx : 0];
-    bool nan = ein && eval != eval;
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) {
+    nan = ein && eval != eval;
+    auto row_in = [&](int i) {
         const int row = wv + 4 * i;
-        const int gy = y0 + row % HY - 1, gz = z0 + row / HY - 1;
-        const bool ok = xin && (unsigned)gy < (unsigned)Y && (unsigned)gz < (unsigned)Z;
-        nan |= ok && vals[i] != vals[i];
-        (s_u + wv * HX + lx + 1)[4 * i * HX] = ok ? tile_key<MINMODE>(vals[i]) : 0u;
+        return xin && (unsigned)(y0 + row % HY - 1) < (unsigned)Y && (unsigned)(z0 + row / HY - 1) < (unsigned)Z;
+    };
+    uint32_t* own = s_u + wv * HX + lx + 1;  // the rows at immediate offsets
+    uint32_t* edge = s_u + erow * HX + ((tid & 1) ? HX - 1 : 0);
+    if constexpr (sizeof(T) < 4) {
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) own[4 * i * HX] = row_in(i) ? tile_key<MINMODE>(vals[i]) : 0u;
+        if (tid < EDGES) *edge = ein ? tile_key<MINMODE>(eval) : 0u;
+        return true;
+    } else {
+        const uint64_t base = exact_of(f[(int64_t)(z0 * Y + y0) * X + x0]) - (uint64_t(1) << 31);
+        uint32_t near[RPW];
+        bool far = false, round = false;
+        auto look = [&](T x, bool in) {
+            const uint64_t r = exact_of(x) - base;
+            far |= in && r - 1u >= 0xFFFFFFFEull;
+            round |= in && !key_is_exact(x);
+            nan |= in && x != x;
+            return (uint32_t)r;
+        };
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) near[i] = look(vals[i], row_in(i));
+        const uint32_t near_edge = look(eval, ein);
+        const uint32_t flags = (__ballot(far) != 0 ? 1u : 0u) | (__ballot(round) != 0 ? 2u : 0u);
+        if (lx == 0) s_flag[wv] = flags;
+        __syncthreads();
+        const uint32_t all = s_flag[0] | s_flag[1] | s_flag[2] | s_flag[3];
+        if (all & 1u) {
+#pragma unroll
+            for (int i = 0; i < RPW; ++i) own[4 * i * HX] = row_in(i) ? tile_key<MINMODE>(vals[i]) : 0u;
+            if (tid < EDGES) *edge = ein ? tile_key<MINMODE>(eval) : 0u;
+        } else {
+#pragma unroll
+            for (int i = 0; i < RPW; ++i) own[4 * i * HX] = row_in(i) ? (MINMODE ? ~near[i] : near[i]) : 0u;
+            if (tid < EDGES) *edge = ein ? (MINMODE ? ~near_edge : near_edge) : 0u;
+        }
+        return all != 3u;
     }
-    if (tid < EDGES) s_u[erow * HX + ((tid & 1) ? HX - 1 : 0)] = ein ? tile_key<MINMODE>(eval) : 0u;
-    return nan;
 }
 
 template <bool MINMODE, int TY, int TZ, bool FULL, int SRC>
-__device__ __forceinline__ bool stage_typed(const TileArgs& a, int x0, int y0, int z0, uint32_t* s_u)
+__device__ __forceinline__ bool stage_typed(const TileArgs& a, int x0, int y0, int z0, uint32_t* s_u,
+                                            uint32_t* s_flag, bool& nan)
 {
 #define EG_STAGE(CODE, T) \
-    case CODE: return stage_samples<T, MINMODE, TY, TZ, FULL>(a, x0, y0, z0, s_u);
+    case CODE: return stage_samples<T, MINMODE, TY, TZ, FULL>(a, x0, y0, z0, s_u, s_flag, nan);
     if constexpr (SRC == SRC_INT) {
         switch (a.dtype) {
             EG_STAGE(EG_I8, int8_t)
@@ -602,10 +638,11 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
     }
 
     bool nan = false;
+    [[maybe_unused]] bool exact = true;  // equal keys are equal samples
     if constexpr (SRC != SRC_F32) {
         s_conn[tid] = c_conn3.w[tid];
         s_conn[tid + 256] = c_conn3.w[tid + 256];
-        nan = stage_typed<MINMODE, TY, TZ, FULL, SRC>(a, x0, y0, z0, s_u);
+        exact = stage_typed<MINMODE, TY, TZ, FULL, SRC>(a, x0, y0, z0, s_u, s_tmp, nan);
     } else {
         // every load of this thread is issued before the first one is used:
         // rows of 64 aligned values (one per lane) from a uniform row address,
@@ -781,7 +818,7 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
                     if (us[st] == kbest) best_st = st;
                 });
             }
-            if constexpr (SRC == SRC_WIDE) {
+            if (SRC == SRC_WIDE && !exact) {
                 // open: a neighbour meets the vertex, or two candidates within
                 // 16 keys of each other lead (the last and the first of them
                 // differ); 32-bit keys are exact but for the two clamped ends
@@ -816,7 +853,7 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
             park_word(word, is_sad, 32 + c * TZ + lz);
         }
     }
-    if constexpr (SRC == SRC_WIDE) {
+    if (SRC == SRC_WIDE && !exact) {
         // the open vertices again, on the samples themselves (the halo's keys
         // still say which neighbours exist): rare on measured data, every
         // vertex on plateaus
