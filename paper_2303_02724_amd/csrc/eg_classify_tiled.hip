@@ -128,14 +128,17 @@ hipError_t launch_final_tiled_batched(const BatchPlan* dplan, const BatchPlan& h
 }
 
 // The tiles [first, first + count): every tile of the grid, or the tile rows
-// of one slab of a streamed build.
+// of one slab of a streamed build.  Five waves per SIMD, as many as the LDS of
+// the default tile allows: only the variant for ragged tiles that writes
+// pointers needs more than the 96 registers that this leaves, and spills (512^3
+// classification 421 us, 445 with its 105 registers and four waves).
 template <bool MINMODE, int TY, int TZ>
-__global__ __launch_bounds__(256) void k_classify3d(TileArgs a, int first, int count)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_classify3d(TileArgs a, int first, int count)
 {
     constexpr int HALO = 66 * (TY + 2) * (TZ + 2);
     __shared__ uint32_t s_u[HALO];
     __shared__ uint32_t s_conn[512];
-    __shared__ uint32_t s_tmp[64];
+    __shared__ __align__(8) uint32_t s_tmp[kTile3Words];
     tile3d<MINMODE, TY, TZ>(a, first + xcd_tile(blockIdx.x, count), s_u, s_conn, s_tmp);
 }
 
@@ -173,14 +176,14 @@ TileArgs tile_args(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, co
 // minimum graph) one launch covers the work list of (field, tile) items of
 // that class, one workgroup per item, which runs the tile code of its field.
 template <int NDIM, bool MINMODE, int TY, int TZ>
-__global__ __launch_bounds__(256) void k_classify_batched(const BatchPlan* __restrict__ plan, int cls)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_classify_batched(const BatchPlan* __restrict__ plan, int cls)
 {
     constexpr int HALO3 = 66 * (TY + 2) * (TZ + 2);
     constexpr int HALO2 = 66 * (TY + 2);
     constexpr int WORDS = NDIM == 3 ? HALO3 : HALO2 + 64 * TY;
     __shared__ uint32_t s_u[WORDS];
     __shared__ uint32_t s_conn[NDIM == 3 ? 512 : 1];
-    __shared__ uint32_t s_tmp[64];
+    __shared__ __align__(8) uint32_t s_tmp[kTile3Words];
     const EG_GPTR(BatchField) fs = plan->fields;
     const int f0 = plan->class_field[cls], f1 = plan->class_field[cls + 1];
     const int64_t item = plan->class_tile[cls] + blockIdx.x;

@@ -20,7 +20,7 @@ __global__ __launch_bounds__(256) void k_classify3d_typed(TileArgs a)
 {
     __shared__ uint32_t s_u[66 * (kTile3Y + 2) * (kTile3Z + 2)];
     __shared__ uint32_t s_conn[512];
-    __shared__ uint32_t s_tmp[64];
+    __shared__ __align__(8) uint32_t s_tmp[kTile3Words];
     tile3d<MINMODE, kTile3Y, kTile3Z, SRC>(a, xcd_tile(blockIdx.x, a.ntiles), s_u, s_conn, s_tmp);
 }
 

@@ -3,8 +3,9 @@
 // Two orders of a sample are used.  exact_key is an unsigned integer with
 // exactly the order of the samples.  tile_key is a 32-bit key whose order
 // never contradicts it but may make different samples equal: 8- and 16-bit
-// integers keep all of theirs, 32-bit integers all but the two at either end
-// (the key 0 is taken by positions outside the grid), and the 64-bit types go
+// integers keep all of theirs, 32-bit integers all but those at the ends (the key
+// 0 is taken by positions outside the grid, the keys from kKeyTop up would not
+// be finite numbers in the tiles' 64-bit maxima), and the 64-bit types go
 // through their nearest float32 (a monotone rounding).  A tile compares the
 // 32-bit keys and looks at the samples themselves only where two of them meet
 // and some key of the tile is not exact.  Tiles whose samples lie close
@@ -37,19 +38,23 @@ __host__ __device__ inline int sample_size(int dtype)
                                                                    : 8;
 }
 
-// An order-preserving key of the bit pattern, in four instructions: negative
-// values map to -b, the others to b | 2^31, so -0 and +0 meet at 2^31 and the
-// order of the numbers is kept (keys of the same value are equal, the index
-// decides); the top is clamped, so every vertex key lies in [1, 0xFFFFFFFE]
-// and the key 0 of positions outside the grid stays below all of them, NaN
-// included: no pointer can leave the grid.  The minimum graph takes the
-// complement.
+// Tile keys lie in [1, kKeyTop - 1]; in the minimum graph a key k becomes
+// kKeyTop - k, or the key of the negated number.
+constexpr uint32_t kKeyTop = 0xFFE00000u;
+
+// An order-preserving key of the bit pattern of a float32, in four or five
+// instructions: negative values map to -b, the others to b | 2^31, so -0 and
+// +0 meet at 2^31 and the order of the numbers is kept (keys of the same value
+// are equal, the index decides); the top is clamped, so every vertex key is
+// below kKeyTop and the key 0 of positions outside the grid stays below all of
+// them, NaN included: no pointer can leave the grid.  The minimum graph takes
+// the key of the negated number.
 template <bool MINMODE>
 __device__ __forceinline__ uint32_t bits_key(uint32_t b)
 {
+    if (MINMODE) b ^= 0x80000000u;
     const uint32_t m = (uint32_t)((int32_t)b >> 31);
-    const uint32_t k = min((b ^ (m | 0x80000000u)) - m, 0xFFFFFFFEu);
-    return MINMODE ? ~k : k;
+    return min((b ^ (m | 0x80000000u)) - m, kKeyTop - 1u);
 }
 
 template <bool MINMODE>
@@ -70,21 +75,20 @@ __device__ __forceinline__ uint32_t tile_key(uint64_t x)
 template <bool MINMODE>
 __device__ __forceinline__ uint32_t tile_key(uint32_t x)
 {
-    const uint32_t k = min(max(x, 1u), 0xFFFFFFFEu);
-    return MINMODE ? ~k : k;
+    const uint32_t k = min(max(x, 1u), kKeyTop - 1u);
+    return MINMODE ? kKeyTop - k : k;
 }
 template <bool MINMODE>
 __device__ __forceinline__ uint32_t tile_key(int32_t x)
 {
     return tile_key<MINMODE>((uint32_t)x ^ 0x80000000u);
 }
-// 8- and 16-bit integers: 1 .. 98304, spread out so that keys of different
-// samples differ above the four bits that the tiles' steepest candidate drops
+// 8- and 16-bit integers
 template <bool MINMODE, class T>
 __device__ __forceinline__ uint32_t tile_key_int(T x)
 {
-    const uint32_t k = (uint32_t)((int)x + 32769) << 15;
-    return MINMODE ? ~k : k;
+    const uint32_t k = (uint32_t)((int)x + 32769);
+    return MINMODE ? kKeyTop - k : k;
 }
 template <bool MINMODE>
 __device__ __forceinline__ uint32_t tile_key(int8_t x) { return tile_key_int<MINMODE>(x); }
@@ -130,7 +134,7 @@ __device__ __forceinline__ bool key_is_exact(int64_t x)
     return (uint64_t)(x + (int64_t(1) << 24)) <= (uint64_t(1) << 25);
 }
 __device__ __forceinline__ bool key_is_exact(uint64_t x) { return x <= (uint64_t(1) << 24); }
-__device__ __forceinline__ bool key_is_exact(uint32_t x) { return x - 2u <= 0xFFFFFFFBu; }
+__device__ __forceinline__ bool key_is_exact(uint32_t x) { return x - 2u <= kKeyTop - 4u; }
 __device__ __forceinline__ bool key_is_exact(int32_t x) { return key_is_exact((uint32_t)x ^ 0x80000000u); }
 
 // The exact key of vertex v of a field of a wide type; the minimum graph takes
