@@ -657,7 +657,9 @@ __device__ __forceinline__ void write_header(const ArcArgs& A, uint32_t narc, ui
     h[EG_H_NARC] = sad_over ? -1 : (int32_t)narc;
     h[EG_H_NPAIRS] = sad_over ? -1 : (int32_t)npairs;
     h[EG_H_PASSES] = (int32_t)c[C_PASSES];
-    h[EG_H_EXITS] = (int32_t)c[C_NEXIT];
+    uint32_t exits = 0;  // counters behind row 0 (zero on grids without tiles)
+    for (int r = 0; r < kRegions; ++r) exits += A.bsum[kArcBlocks + kRegionStride * r];
+    h[EG_H_EXITS] = (int32_t)exits;
 }
 
 // Four saddles per thread and round: their counts and stored arcs are all

@@ -7,18 +7,14 @@
 
 namespace eg {
 
-constexpr int kBatchBlocksPerField = 48;
-
-__device__ __forceinline__ uint32_t rd(const uint32_t* p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+constexpr int kBatchBlocksPerField = 48;  // a multiple of the exit list's regions
 
 __global__ __launch_bounds__(256) void k_binit(const BatchPlan* __restrict__ plan)
 {
     const BatchField& F = plan->fields[blockIdx.x];
     const int t = threadIdx.x;
     if (t < C_SLOTS) F.ta.ctr[t] = 0;
+    if (t < kRegions) F.ta.claims[kRegionStride * t] = 0;
     if (t < EG_H_SLOTS) F.arc.header[t] = 0;
     if (blockIdx.x == 0 && t < C_SLOTS) plan->bctr[t] = 0;
 }
@@ -31,31 +27,22 @@ __global__ __launch_bounds__(256) void k_binit(const BatchPlan* __restrict__ pla
 __global__ __launch_bounds__(256) void k_bexit_init(const BatchPlan* __restrict__ plan)
 {
     const BatchField F = plan->fields[blockIdx.y];  // a copy: loop loads cannot alias it
-    const uint32_t req = rd(&F.ta.ctr[C_NEXIT]);
-    const uint32_t n = req < F.ta.cap_exit ? req : F.ta.cap_exit;
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
-    const int32_t* lab = F.ta.lab;
-    const uint32_t nq = n >> 2;
-    const uint4* e4 = reinterpret_cast<const uint4*>(F.ta.exits);
-    int4* r4 = reinterpret_cast<int4*>(F.exres);
-    for (uint32_t q = t; q < nq; q += stride) {
-        const uint4 e = e4[q];
-        r4[q] = make_int4(lab[e.x], lab[e.y], lab[e.z], lab[e.w]);
-    }
-    if (t < (n & 3u)) F.exres[(nq << 2) + t] = lab[F.ta.exits[(nq << 2) + t]];
+    exit_first(exit_part(F.ta.claims, F.ta.cap_region, F.ta.regions, blockIdx.x, gridDim.x), F.ta.exits, F.exres,
+               F.ta.lab);
 }
 
 __global__ __launch_bounds__(256) void k_bexit_jump(const BatchPlan* __restrict__ plan)
 {
     const BatchField F = plan->fields[blockIdx.y];  // a copy: loop loads cannot alias it
-    const uint32_t req = rd(&F.ta.ctr[C_NEXIT]);
-    const uint32_t n = req < F.ta.cap_exit ? req : F.ta.cap_exit;
+    const ExitPart p = exit_part(F.ta.claims, F.ta.cap_region, F.ta.regions, blockIdx.x, gridDim.x);
     const int hops = plan->tuning.hops;
     const int sweeps = sweeps_for(plan->tuning, F.N);
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
-    bool open = sweep(F.exres, n, F.ta.lab, F.exres, F.N, hops, t, stride, false);
+    const int32_t* lab = F.ta.lab;
+    int32_t* res = F.exres;
+    int32_t* part = res + p.at;
+    bool open = sweep(part, p.n, lab, res, F.N, hops, p.t, p.stride, false);
     for (int k = 1; __ballot(open) != 0 && k < sweeps; ++k)
-        open = sweep(F.exres, n, F.ta.lab, F.exres, F.N, hops, t, stride, true);
+        open = sweep(part, p.n, lab, res, F.N, hops, p.t, p.stride, true);
     if (__ballot(open) != 0 && __lane_id() == 0) atomicOr(&plan->bctr[C_OPEN], 1u);
 }
 

@@ -17,12 +17,14 @@ namespace eg {
 
 // Counters and header; on grids without tiles (whose masks are written bit by
 // bit) the words of both masks too.
-__global__ __launch_bounds__(256) void k_init(uint32_t* __restrict__ ctr, int32_t* __restrict__ header,
-                                              uint64_t* __restrict__ a, uint64_t* __restrict__ b, int64_t n)
+__global__ __launch_bounds__(256) void k_init(uint32_t* __restrict__ ctr, uint32_t* __restrict__ claims,
+                                              int32_t* __restrict__ header, uint64_t* __restrict__ a,
+                                              uint64_t* __restrict__ b, int64_t n)
 {
     if (blockIdx.x == 0) {
         const int i = threadIdx.x;
         if (i < C_SLOTS) ctr[i] = 0;
+        if (i < kRegions) claims[kRegionStride * i] = 0;
         if (header && i < EG_H_SLOTS) header[i] = 0;
     }
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
@@ -37,7 +39,7 @@ hipError_t launch_init(const Grid& g, const Work& w, int32_t* header, hipStream_
     const int64_t n = tiled ? 0 : w.words;
     const int64_t want = (n + 255) / 256;
     const int blocks = (int)(want < 1 ? 1 : want < 4096 ? want : 4096);
-    hipLaunchKernelGGL(k_init, dim3(blocks), dim3(256), 0, s, w.ctr, header, w.mmask, w.smask, n);
+    hipLaunchKernelGGL(k_init, dim3(blocks), dim3(256), 0, s, w.ctr, w.claims, header, w.mmask, w.smask, n);
     return hipGetLastError();
 }
 
@@ -473,45 +475,36 @@ hipError_t launch_classify(const float* f, const Grid& g, const LinkTable& t, bo
 // (sweeps_for).  Later sweeps read the links at device scope: a plain load
 // could return the same old line of a cache every time.
 
-// The exit list's base is 16-byte aligned (the workspace is carved in 256-byte
-// steps); the links are latency-bound gathers, so more of them per thread hide
-// more latency.
-__global__ __launch_bounds__(256) void k_exit_init(const uint32_t* __restrict__ exits, int32_t* __restrict__ res,
-                                                   const int32_t* __restrict__ lab, const uint32_t* __restrict__ ctr,
-                                                   uint32_t cap)
+// The exit list's base and its regions are 16-byte aligned (the workspace is
+// carved in 256-byte steps, regions hold a multiple of four entries).
+__global__ __launch_bounds__(256) void k_exit_init(TileArgs a, int32_t* __restrict__ res)
 {
-    const uint32_t req = __hip_atomic_load(&ctr[C_NEXIT], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t n = req < cap ? req : cap;
-    const uint32_t nq = n >> 2;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint4* e4 = reinterpret_cast<const uint4*>(exits);
-    int4* r4 = reinterpret_cast<int4*>(res);
-    for (uint32_t q = t; q < nq; q += stride) {
-        const uint4 e = e4[q];
-        r4[q] = make_int4(lab[e.x], lab[e.y], lab[e.z], lab[e.w]);
-    }
-    if (t < (n & 3u)) res[(nq << 2) + t] = lab[exits[(nq << 2) + t]];
+    exit_first(exit_part(a.claims, a.cap_region, a.regions, blockIdx.x, gridDim.x), a.exits, res, a.lab);
 }
 
-__global__ __launch_bounds__(256) void k_exit_jump(int32_t* res, const int32_t* lab, int N, uint32_t* __restrict__ ctr,
-                                                   uint32_t cap, int hops, int sweeps)
+__global__ __launch_bounds__(256) void k_exit_jump(TileArgs a, int32_t* res, int N, int hops, int sweeps)
 {
-    const uint32_t req = __hip_atomic_load(&ctr[C_NEXIT], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t n = req < cap ? req : cap;
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
-    bool open = sweep(res, n, lab, res, N, hops, t, stride, false);
+    const ExitPart p = exit_part(a.claims, a.cap_region, a.regions, blockIdx.x, gridDim.x);
+    const int32_t* lab = a.lab;
+    int32_t* part = res + p.at;
+    bool open = sweep(part, p.n, lab, res, N, hops, p.t, p.stride, false);
     for (int k = 1; __ballot(open) != 0 && k < sweeps; ++k)
-        open = sweep(res, n, lab, res, N, hops, t, stride, true);
-    if (__ballot(open) != 0 && __lane_id() == 0) atomicOr(&ctr[C_OPEN], 1u);
+        open = sweep(part, p.n, lab, res, N, hops, p.t, p.stride, true);
+    if (__ballot(open) != 0 && __lane_id() == 0) atomicOr(&a.ctr[C_OPEN], 1u);
 }
 
 // Per-vertex labels of the grids without tiles: every code names a vertex.
 // Almost every field is done after one sweep; k_final_rest finishes the others.
+// Each XCD resolves a run of consecutive vertices, so that the links of
+// neighbouring vertices, which stay close, meet in its L2.
 __global__ __launch_bounds__(256) void k_final(int32_t* lab, int32_t N, uint32_t* __restrict__ ctr, int hops)
 {
     const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool open = sweep(lab, (uint32_t)N, lab, lab, N, hops, t, gridDim.x * blockDim.x, false);
+    // runs of whole quads; the last run ends with the vertices left over
+    const uint32_t x = blockIdx.x & 7u, q = (uint32_t)N >> 5;
+    const uint32_t lo = 4u * q * x, n = x == 7u ? (uint32_t)N - lo : 4u * q;
+    const bool open = sweep(lab + lo, n, lab, lab, N, hops, (blockIdx.x >> 3) * blockDim.x + threadIdx.x,
+                            (gridDim.x >> 3) * blockDim.x, false);
     if (__ballot(open) != 0 && __lane_id() == 0) atomicOr(&ctr[C_MORE], 1u);
     if (t == 0) ctr[C_PASSES] = 1;
 }
@@ -537,19 +530,21 @@ hipError_t launch_labels(const Grid& g, int32_t* lab, const Work& w, const Tunin
     if (reinterpret_cast<uintptr_t>(lab) & 15u) return hipErrorInvalidValue;
     const int sweeps = sweeps_for(tu, N);
     if (g.ndim == 2 || g.ndim == 3) {
-        const uint32_t cap = (uint32_t)w.cap_exit;
         if ((reinterpret_cast<uintptr_t>(w.exits) | reinterpret_cast<uintptr_t>(w.exres)) & 15u)
             return hipErrorInvalidValue;
+        int ty, tz;
+        tile_shape(tu, g.ndim, &ty, &tz);
+        const TileArgs a = tile_args(nullptr, g, lab, nullptr, w, ty, tz);
         const int64_t ewant = (w.cap_exit / 4 + 255) / 256;
-        const int eblocks = (int)(ewant < 2048 ? (ewant > 0 ? ewant : 1) : 2048);
+        const int eblocks = (int)(ewant < 2048 ? (ewant / 8 + 1) * 8 : 2048);  // a multiple of the regions
         // the jump reads entries that other threads have already advanced,
         // which shortens long chains: it needs every entry initialised first
-        hipLaunchKernelGGL(k_exit_init, dim3(eblocks), dim3(256), 0, s, w.exits, w.exres, lab, w.ctr, cap);
-        hipLaunchKernelGGL(k_exit_jump, dim3(eblocks), dim3(256), 0, s, w.exres, lab, N, w.ctr, cap, tu.hops, sweeps);
+        hipLaunchKernelGGL(k_exit_init, dim3(eblocks), dim3(256), 0, s, a, w.exres);
+        hipLaunchKernelGGL(k_exit_jump, dim3(eblocks), dim3(256), 0, s, a, w.exres, N, tu.hops, sweeps);
         return launch_final_tiled(g, lab, w, tu, s);
     }
     const int64_t want = ((int64_t)N / 4 + 255) / 256;
-    const int blocks = (int)(want < 2048 ? (want > 0 ? want : 1) : 2048);
+    const int blocks = (int)(want < 2048 ? (want / 8 + 1) * 8 : 2048);  // a multiple of the XCDs
     hipLaunchKernelGGL(k_final, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, tu.hops);
     // every block of this launch fits the GPU at once, so that all entries
     // advance together

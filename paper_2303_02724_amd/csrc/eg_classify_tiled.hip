@@ -132,14 +132,12 @@ hipError_t launch_final_tiled_batched(const BatchPlan* dplan, const BatchPlan& h
 // the default tile allows: only the variant for ragged tiles that writes
 // pointers needs more than the 96 registers that this leaves, and spills (512^3
 // classification 421 us, 445 with its 105 registers and four waves).
-template <bool MINMODE, int TY, int TZ>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_classify3d(TileArgs a, int first, int count)
+template <bool MINMODE, int TY, int TZ, bool PTR>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_classify3d(TileArgs a, int first,
+                                                                                            int count)
 {
-    constexpr int HALO = 66 * (TY + 2) * (TZ + 2);
-    __shared__ uint32_t s_u[HALO];
-    __shared__ uint32_t s_conn[512];
-    __shared__ __align__(8) uint32_t s_tmp[kTile3Words];
-    tile3d<MINMODE, TY, TZ>(a, first + xcd_tile(blockIdx.x, count), s_u, s_conn, s_tmp);
+    __shared__ __align__(8) Tile3Lds<TY, TZ> s;
+    tile3d<MINMODE, TY, TZ, PTR, SRC_F32>(a, first + xcd_tile(blockIdx.x, count), s);
 }
 
 template <bool MINMODE, int TY>
@@ -161,6 +159,7 @@ TileArgs tile_args(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, co
     a.mmask = gptr(w.mmask);
     a.smask = gptr(w.smask);
     a.exits = gptr(w.exits);
+    a.claims = gptr(w.claims);
     a.X = g.dims[g.ndim - 1];
     a.Y = g.dims[g.ndim - 2];
     a.Z = g.ndim == 3 ? g.dims[0] : 1;
@@ -168,7 +167,8 @@ TileArgs tile_args(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, co
     a.tiles_y = (a.Y + ty - 1) / ty;
     const int tiles_z = (a.Z + tz - 1) / tz;
     a.ntiles = a.tiles_x * a.tiles_y * tiles_z;
-    a.cap_exit = (uint32_t)w.cap_exit;
+    a.regions = exit_regions(a.ntiles);
+    a.cap_region = region_capacity(w.cap_exit, a.regions);
     return a;
 }
 
@@ -178,12 +178,10 @@ TileArgs tile_args(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, co
 template <int NDIM, bool MINMODE, int TY, int TZ>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_classify_batched(const BatchPlan* __restrict__ plan, int cls)
 {
-    constexpr int HALO3 = 66 * (TY + 2) * (TZ + 2);
     constexpr int HALO2 = 66 * (TY + 2);
-    constexpr int WORDS = NDIM == 3 ? HALO3 : HALO2 + 64 * TY;
-    __shared__ uint32_t s_u[WORDS];
-    __shared__ uint32_t s_conn[NDIM == 3 ? 512 : 1];
-    __shared__ __align__(8) uint32_t s_tmp[kTile3Words];
+    using Lds3 = Tile3Lds<TY, TZ>;
+    constexpr int WORDS = NDIM == 3 ? (int)(sizeof(Lds3) / 4) : 8 + HALO2 + 64 * TY;
+    __shared__ __align__(8) uint32_t s_mem[WORDS];
     const EG_GPTR(BatchField) fs = plan->fields;
     const int f0 = plan->class_field[cls], f1 = plan->class_field[cls + 1];
     const int64_t item = plan->class_tile[cls] + blockIdx.x;
@@ -199,10 +197,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     const int f = __builtin_amdgcn_readfirstlane(lo);
     const int tile = (int)(item - fs[f].tile_base);
     const TileArgs a = fs[f].ta;
-    if constexpr (NDIM == 3)
-        tile3d<MINMODE, TY, TZ>(a, tile, s_u, s_conn, s_tmp);
-    else
-        tile_nd<2, MINMODE, TY, 1>(a, tile, s_u, reinterpret_cast<int32_t*>(s_u + HALO2), nullptr, s_tmp);
+    if constexpr (NDIM == 3) {
+        Lds3& s = *reinterpret_cast<Lds3*>(s_mem);
+        if (a.ptr)
+            tile3d<MINMODE, TY, TZ, true, SRC_F32>(a, tile, s);
+        else
+            tile3d<MINMODE, TY, TZ, false, SRC_F32>(a, tile, s);
+    } else {
+        tile_nd<2, MINMODE, TY, 1>(a, tile, s_mem + 8, reinterpret_cast<int32_t*>(s_mem + 8 + HALO2), nullptr, s_mem);
+    }
 }
 
 template <int NDIM, int TY, int TZ>
@@ -241,10 +244,18 @@ hipError_t launch_classify_batched(const BatchPlan* dplan, const BatchPlan& hpla
 template <int TY, int TZ>
 static void launch_3d(const TileArgs& a, bool minima, int first, int count, hipStream_t s)
 {
-    if (minima)
-        hipLaunchKernelGGL((k_classify3d<true, TY, TZ>), dim3(count), dim3(256), 0, s, a, first, count);
-    else
-        hipLaunchKernelGGL((k_classify3d<false, TY, TZ>), dim3(count), dim3(256), 0, s, a, first, count);
+    const dim3 g(count), b(256);
+    if (minima) {
+        if (a.ptr)
+            hipLaunchKernelGGL((k_classify3d<true, TY, TZ, true>), g, b, 0, s, a, first, count);
+        else
+            hipLaunchKernelGGL((k_classify3d<true, TY, TZ, false>), g, b, 0, s, a, first, count);
+    } else {
+        if (a.ptr)
+            hipLaunchKernelGGL((k_classify3d<false, TY, TZ, true>), g, b, 0, s, a, first, count);
+        else
+            hipLaunchKernelGGL((k_classify3d<false, TY, TZ, false>), g, b, 0, s, a, first, count);
+    }
 }
 
 template <int TY>

@@ -15,13 +15,11 @@
 
 namespace eg {
 
-template <bool MINMODE, int SRC>
+template <bool MINMODE, bool PTR, int SRC>
 __global__ __launch_bounds__(256) void k_classify3d_typed(TileArgs a)
 {
-    __shared__ uint32_t s_u[66 * (kTile3Y + 2) * (kTile3Z + 2)];
-    __shared__ uint32_t s_conn[512];
-    __shared__ __align__(8) uint32_t s_tmp[kTile3Words];
-    tile3d<MINMODE, kTile3Y, kTile3Z, SRC>(a, xcd_tile(blockIdx.x, a.ntiles), s_u, s_conn, s_tmp);
+    __shared__ __align__(8) Tile3Lds<kTile3Y, kTile3Z> s;
+    tile3d<MINMODE, kTile3Y, kTile3Z, PTR, SRC>(a, xcd_tile(blockIdx.x, a.ntiles), s);
 }
 
 hipError_t launch_classify_typed(int dtype, const void* f, const Grid& g, bool minima, int32_t* lab, int32_t* ptr,
@@ -31,18 +29,23 @@ hipError_t launch_classify_typed(int dtype, const void* f, const Grid& g, bool m
     TileArgs a = tile_args((const float*)f, g, lab, ptr, w, kTile3Y, kTile3Z);
     a.dtype = (uint32_t)dtype;
     const bool wide = sample_source(dtype) == SRC_WIDE;
-#define EG_LAUNCH(MM, SRC) \
-    hipLaunchKernelGGL((k_classify3d_typed<MM, SRC>), dim3(a.ntiles), dim3(256), 0, s, a)
+#define EG_LAUNCH(MM, SRC)                                                                                 \
+    if (ptr)                                                                                               \
+        hipLaunchKernelGGL((k_classify3d_typed<MM, true, SRC>), dim3(a.ntiles), dim3(256), 0, s, a);       \
+    else                                                                                                   \
+        hipLaunchKernelGGL((k_classify3d_typed<MM, false, SRC>), dim3(a.ntiles), dim3(256), 0, s, a);
     if (minima) {
-        if (wide)
-            EG_LAUNCH(true, SRC_WIDE);
-        else
-            EG_LAUNCH(true, SRC_INT);
+        if (wide) {
+            EG_LAUNCH(true, SRC_WIDE)
+        } else {
+            EG_LAUNCH(true, SRC_INT)
+        }
     } else {
-        if (wide)
-            EG_LAUNCH(false, SRC_WIDE);
-        else
-            EG_LAUNCH(false, SRC_INT);
+        if (wide) {
+            EG_LAUNCH(false, SRC_WIDE)
+        } else {
+            EG_LAUNCH(false, SRC_INT)
+        }
     }
 #undef EG_LAUNCH
     return hipGetLastError();

@@ -28,6 +28,18 @@ constexpr int kMaxNb = 126;         // 2(2^6 - 1)
 constexpr int kJumpHops = 64;       // default links per pointer-jumping pass
 constexpr int kSumRow = 8192;  // entries per row of the stage (d) block sums
 constexpr int kArcBlocks = 4096;    // most blocks per field of the stage (d) kernels
+// The exit list of a grid of many tiles is split into regions, one for each of
+// the eight XCDs (workgroups are dispatched to them round-robin).  A tile
+// claims its block with an atomic on its region's counter: one counter for all
+// serialised the tiles' claims at 12.5 ns each, 410 us at 512^3, which hid
+// everything else the classification gained.  And the kernels that resolve a
+// region run on its XCD, whose tiles are neighbours, so their gathers meet in
+// one L2.  Below kRegionTiles tiles an uneven split could fill one region, so
+// there is only one.
+constexpr int kRegions = 8;
+constexpr int kRegionTiles = 512;
+constexpr int kRegionStride = 32;  // counters lie 128 bytes apart
+static_assert(kArcBlocks + kRegions * kRegionStride <= kSumRow, "the counters sit behind row 0's block sums");
 constexpr int kArcVertsPerBlock = 8192;  // stage (d) blocks: one per this many vertices
 constexpr int kTile3Y = 8, kTile3Z = 8;  // default 3D tile: 64 x 8 x 8 vertices
 constexpr int kTile2Y = 32;             // default 2D tile: 64 x 32 vertices
@@ -63,7 +75,6 @@ enum : int {
     C_NMAX = 1,
     C_NSAD = 2,
     C_PASSES = 6,  // per-vertex label passes (untiled grids)
-    C_NEXIT = 7,   // exit-list entries requested by the tiles
     C_MORE = 16,   // untiled grids: labels left over by the first per-vertex pass
     C_OPEN = 17,   // labels left over by the last label kernel (an internal error)
     C_SLOTS = 64,
@@ -98,6 +109,7 @@ struct Work {
     uint64_t* smask;  // [words] saddles
     uint32_t* bsum;   // [4 * kSumRow] per-block counts of stage (d)
     uint4* atmp;      // [cap_sad] the first four arcs of every saddle ([2 cap_sad], eight, from 4D on)
+    uint32_t* claims; // exit-list counters, region r at [kRegionStride r] (behind row 0 of bsum)
     uint32_t* exits;  // [cap_exit] exit vertices published by the tiles
     int32_t* exres;   // [cap_exit] their labels while being resolved
     uint32_t* keys;   // [N] order keys of the untiled grids (1D, 4D, 5D); else null
@@ -130,8 +142,11 @@ struct TileArgs {
     EG_GPTR(uint64_t) mmask;
     EG_GPTR(uint64_t) smask;
     EG_GPTR(uint32_t) exits;
+    EG_GPTR(uint32_t) claims;  // entries requested, region r at [kRegionStride r]
     int32_t X, Y, Z, tiles_x, tiles_y, ntiles;
-    uint32_t cap_exit, dtype;  // dtype: the samples behind f (eg_dtype)
+    uint32_t cap_region;       // entries per region
+    uint32_t regions;          // 1 or kRegions
+    uint32_t dtype, pad0;      // dtype: the samples behind f (eg_dtype)
 };
 
 // Everything stage (d) needs to know about its field.
@@ -300,10 +315,10 @@ __device__ __forceinline__ int next_link(const int32_t* lab, const int32_t* res,
     return link_at(x >= -N ? lab + (-x - 1) : res + (-x - 1 - N), fresh);
 }
 
-// One sweep over the quads t, t + stride, ... of a[0, n) and over the n % 4
-// entries behind them (thread t the t-th): four consecutive entries per thread
-// (one 16-byte access, four independent chains in flight).  Returns whether an
-// entry of this thread is not final.
+// One sweep over a[0, n) by quads t, t + stride, ..., the last n % 4 entries by
+// threads t < n % 4: four consecutive entries per thread (one 16-byte access,
+// four independent chains in flight).  Returns whether an entry of this thread
+// is not final.
 __device__ __forceinline__ bool sweep(int32_t* a, uint32_t n, const int32_t* lab, const int32_t* res, int N, int hops,
                                       uint32_t t, uint32_t stride, bool fresh)
 {
@@ -333,6 +348,38 @@ __device__ __forceinline__ bool sweep(int32_t* a, uint32_t n, const int32_t* lab
     return open;
 }
 
+// The region of the exit list that a workgroup works on, the workgroup's
+// first quad in it and the quads between its rounds (nb workgroups, a multiple
+// of the regions, blk one of them).
+struct ExitPart {
+    uint32_t n, at, t, stride;  // entries, index of the first in the list
+};
+__device__ __forceinline__ ExitPart exit_part(const uint32_t* claims, uint32_t cap_region, uint32_t regions,
+                                              uint32_t blk, uint32_t nb)
+{
+    const uint32_t r = blk & (regions - 1u);
+    const uint32_t req = __hip_atomic_load(&claims[kRegionStride * r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t step = regions == 1 ? 0 : 3;
+    return ExitPart{req < cap_region ? req : cap_region, r * cap_region, (blk >> step) * 256 + threadIdx.x,
+                    (nb >> step) * 256};
+}
+
+// First values of a part of the exit list: its vertices' label codes.
+__device__ __forceinline__ void exit_first(const ExitPart& p, const uint32_t* exits, int32_t* res, const int32_t* lab)
+{
+    const uint32_t nq = p.n >> 2;
+    const uint4* e4 = reinterpret_cast<const uint4*>(exits + p.at);
+    int4* r4 = reinterpret_cast<int4*>(res + p.at);
+    for (uint32_t q = p.t; q < nq; q += p.stride) {
+        const uint4 e = e4[q];
+        r4[q] = make_int4(lab[e.x], lab[e.y], lab[e.z], lab[e.w]);
+    }
+    if (p.t < (p.n & 3u)) {
+        const uint32_t i = p.at + (nq << 2) + p.t;
+        res[i] = lab[exits[i]];
+    }
+}
+
 // ------------------------------------------------------------------ launchers
 
 // Counters and header to zero; the two masks too on grids without tiles.
@@ -347,6 +394,12 @@ hipError_t launch_classify_tiled(const float* f, const Grid& g, bool minima, int
 // The same for a 3D field of another sample type (the default tile).
 hipError_t launch_classify_typed(int dtype, const void* f, const Grid& g, bool minima, int32_t* lab, int32_t* ptr,
                                  const Work& w, hipStream_t s);
+// Regions of the exit list of a grid of ntiles tiles, and entries per region.
+inline uint32_t exit_regions(int64_t ntiles) { return ntiles >= kRegionTiles ? kRegions : 1; }
+inline uint32_t region_capacity(int64_t cap, uint32_t regions)
+{
+    return regions == 1 ? (uint32_t)cap : (uint32_t)(cap / regions) & ~3u;
+}
 TileArgs tile_args(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, const Work& w, int ty, int tz);
 ArcArgs arc_args(const float* f, const Grid& g, const eg_out& o, const Work& w);
 uint32_t arc_blocks(int64_t N);

@@ -125,6 +125,7 @@ Work carve(void* base, int ndim, int64_t N, int64_t X, int64_t cap_sad, int64_t 
         w.smask = (uint64_t*)(p + o_sm);
         w.bsum = (uint32_t*)(p + o_bs);
         w.atmp = (uint4*)(p + o_at);
+        w.claims = w.bsum + kArcBlocks;
         w.exits = (uint32_t*)(p + o_ex);
         w.exres = (int32_t*)(p + o_er);
         w.keys = untiled ? (uint32_t*)(p + o_k) : nullptr;

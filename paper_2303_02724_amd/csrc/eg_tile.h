@@ -115,13 +115,13 @@ __device__ __forceinline__ void double_tile_chains(int (&cur)[VPT], int32_t* s_n
 // the wave (scalar).  The targets go to s_exv in rank order and cur[k] becomes
 // the tile-local code -(rank + 1), which the pointer doubling hands to every
 // vertex whose path leaves the tile there.  One atomic per tile claims the
-// tile's block of the list: thread 0 issues it here and first needs its value
+// tile's block of its region of the list: thread 0 issues it here and first needs its value
 // in place_exits, after the doubling, so the round trip of a device-wide
 // atomic overlaps the doubling instead of stalling the workgroup.  Writes
 // s_exv after a barrier, so the caller may alias it with the halo.
 template <int VPT>
 __device__ __forceinline__ uint32_t rank_exits(int (&cur)[VPT], uint32_t* s_tmp, uint32_t* s_exv,
-                                               uint32_t* __restrict__ ctr, uint32_t& claim)
+                                               uint32_t* __restrict__ counter, uint32_t& claim)
 {
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -134,7 +134,7 @@ __device__ __forceinline__ uint32_t rank_exits(int (&cur)[VPT], uint32_t* s_tmp,
     for (int k = 0; k < w; ++k) r0 += s_tmp[k];
     const uint32_t total = s_tmp[0] + s_tmp[1] + s_tmp[2] + s_tmp[3];
     claim = 0;
-    if (tid == 0 && total) claim = atomicAdd(&ctr[C_NEXIT], total);
+    if (tid == 0 && total) claim = atomicAdd(counter, total);
 #pragma unroll
     for (int k = 0; k < VPT; ++k) {
         const uint64_t bal = __ballot(cur[k] < 0);
@@ -155,15 +155,16 @@ __device__ __forceinline__ uint32_t rank_exits(int (&cur)[VPT], uint32_t* s_tmp,
 // tile's block does not fit; such a tile gives its vertices the vertex codes
 // of their exits' targets instead of list codes.  Returns whether it fit.
 __device__ __forceinline__ bool place_exits(uint32_t total, uint32_t claim, const uint32_t* s_exv, uint32_t* s_tmp,
-                                            uint32_t* __restrict__ exits, uint32_t cap_exit, uint32_t& base)
+                                            const TileArgs& a, uint32_t region, uint32_t& base)
 {
     const int tid = threadIdx.x;
     if (tid == 0) s_tmp[4] = claim;
     __syncthreads();
-    base = s_tmp[4];
+    const uint32_t first = s_tmp[4], cap = a.cap_region;
+    base = region * cap + first;
     for (uint32_t i = tid; i < total; i += 256)
-        if (base + i < cap_exit) exits[base + i] = s_exv[i];
-    return (uint64_t)base + total <= cap_exit;
+        if (first + i < cap) a.exits[base + i] = s_exv[i];
+    return (uint64_t)first + total <= cap;
 }
 
 // The offset that turns a tile-local exit code n < 0 into the label code of
@@ -387,7 +388,9 @@ __device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u,
     if (__ballot(nan) != 0 && __lane_id() == 0) atomicOr(&ctr[C_NAN], 1u);
     const int N = X * Y * Z;
     uint32_t claim;
-    const uint32_t nexit = rank_exits<VPT>(nxt, s_tmp, s_u, ctr, claim);  // the halo is no longer read
+    const uint32_t region = blockIdx.x & (a.regions - 1u);
+    uint32_t* counter = a.claims + kRegionStride * region;
+    const uint32_t nexit = rank_exits<VPT>(nxt, s_tmp, s_u, counter, claim);  // the halo is no longer read
     auto s_idx = [&](int k) { return ((k / YPT) * TY + wv + 4 * (k % YPT)) * TX + lx; };
 #pragma unroll
     for (int k = 0; k < VPT; ++k) s_nxt[s_idx(k)] = nxt[k];
@@ -398,7 +401,7 @@ __device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u,
     if (tid < TY * TZ) s_rowoff[tid] = (tid / TY) * SZ + (tid % TY) * SY;
     double_tile_chains<VPT, TILE, 1>(nxt, s_nxt, s_idx);
     uint32_t base;
-    const bool fit = place_exits(nexit, claim, s_u, s_tmp, a.exits, a.cap_exit, base);
+    const bool fit = place_exits(nexit, claim, s_u, s_tmp, a, region, base);
     const int xoff = exit_offset<VPT>(nxt, fit, base, s_u, N);
     const int tile0 = z0 * SZ + y0 * SY + x0;
 #pragma unroll
@@ -422,7 +425,7 @@ __device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u,
 // tile-local chains, which are resolved by pointer doubling.
 //
 // Steepest candidate.  A key and the code of its position, six bits that grow
-// in visiting order, make one 64-bit number, key << 31 | code << 3; as the
+// in visiting order, make one 64-bit number, key << 31 | code << 2; as the
 // bits of a double it is positive and finite (keys stay below kKeyTop), so
 // v_max_f64, which issues as fast as a 32-bit maximum, takes the larger key
 // and among equal keys the later position: the exact steepest candidate, its
@@ -435,7 +438,7 @@ __device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u,
 // 512^3, classification: 462 -> 421 us.
 //
 // Successor of a vertex as one 32-bit word per code, read from LDS with the
-// global offset in one 8-byte read:
+// global offset in one paired read:
 //   bits 0..5   faces of the tile the step crosses if the vertex lies on them
 //               (x-, x+, y-, y+, z-, z+)
 //   bits 6..31  tile-local offset in bytes of the chain array (signed)
@@ -452,8 +455,17 @@ __device__ __forceinline__ void store_row(int32_t* row, uint32_t lane_b, int32_t
     *reinterpret_cast<int32_t*>(reinterpret_cast<char*>(row) + lane_b) = v;
 }
 
-// A key with the code of its position, and the larger of two of them.
-__device__ __forceinline__ uint64_t coded(uint32_t key, uint32_t code) { return (uint64_t(key) << 31) | code; }
+// A key with the code of its position (an inline constant, at most 64: two
+// instructions, where the compiler's own 64-bit shift takes two moves more),
+// and the larger of two of them.
+template <uint32_t CODE>
+__device__ __forceinline__ uint64_t coded(uint32_t key)
+{
+    static_assert(CODE <= 64, "an inline constant");
+    uint32_t lo;
+    asm("v_lshl_or_b32 %0, %1, 31, %2" : "=v"(lo) : "v"(key), "n"(CODE));
+    return (uint64_t)(key >> 1) << 32 | lo;
+}
 __device__ __forceinline__ uint64_t later_max(uint64_t a, uint64_t b)
 {
     uint64_t r;
@@ -608,9 +620,10 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
     // by code: packed successor and global offset (row c of the thread reads
     // kCodeRow entries before or after, see `code_of`)
     constexpr int kCodeRow = 4;
-    uint2* s_succ = reinterpret_cast<uint2*>(s_tmp + 8) + kCodeRow;
+    uint32_t* s_succ = s_tmp + 8 + kCodeRow;  // [48] successors, then [48] offsets behind kCodes entries
+    constexpr int kCodes = 48 + 2 * kCodeRow;
     // by visiting step (wide samples): the same and the halo index offset
-    uint32_t* s_pack = s_tmp + 8 + 2 * (48 + 2 * kCodeRow);
+    uint32_t* s_pack = s_tmp + 8 + 2 * kCodes;
     int32_t* s_gdel = reinterpret_cast<int32_t*>(s_pack + 16);
     int32_t* s_hoff = reinterpret_cast<int32_t*>(s_pack + 32);
 
@@ -630,8 +643,8 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
         const int pos = MINMODE ? 47 - tid : tid;
         const int dz = (pos >> 4) - 1, dy = ((pos >> 2) & 3) - 1, dx = (pos & 3) - 1;
         const bool self = dz == 0 && dy == 0 && dx == 0;
-        s_succ[tid] = make_uint2(self ? (uint32_t)(4 * TILE) << 6 : succ_pack<TY, HY, HX>(dz, dy, dx),
-                                 (uint32_t)(dz * SZ + dy * SY + dx));
+        s_succ[tid] = self ? (uint32_t)(4 * TILE) << 6 : succ_pack<TY, HY, HX>(dz, dy, dx);
+        s_succ[kCodes + tid] = (uint32_t)(dz * SZ + dy * SY + dx);
     }
     if constexpr (SRC == SRC_WIDE) {
         if (tid <= K) {
@@ -762,9 +775,9 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
     constexpr auto at = [](int r, int dx) { return r < 0 ? dx + 1 : r < YPT ? 3 * r + 3 + dx : 3 * YPT + 2 + dx; };
     constexpr auto code_of = [](int r, int dx) -> uint32_t {
         const int c = 4 * (r + 1) + dx + 1;
-        return 8u * (uint32_t)(MINMODE ? 15 - c : c);
+        return 4u * (uint32_t)(MINMODE ? 15 - c : c);
     };
-    constexpr uint32_t BELOW = MINMODE ? 256u : 0u, OWN = 128u, ABOVE = MINMODE ? 0u : 256u;  // 8 * 16 * plane
+    constexpr uint32_t BELOW = MINMODE ? 128u : 0u, OWN = 64u, ABOVE = MINMODE ? 0u : 128u;  // 4 * 16 * plane
     uint32_t win[3][NP];
     auto load_plane = [&](uint32_t* w, int hz) {
         // one opaque address per plane, at position (-1, -1): the reads lie
@@ -778,45 +791,62 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
 #pragma unroll
             for (int dx = r == YPT ? 0 : -1; dx <= (r < 0 ? 0 : 1); ++dx) w[at(r, dx)] = p[(r + 1) * HX + dx + 1];
     };
-    // a plane's lower and upper maxima of every row of the thread: rows r - 1
-    // and r, columns -1 and 0; rows r and r + 1, columns 0 and 1
-    auto maxima = [&](const uint32_t* w, uint64_t* lower, uint64_t* upper) {
+    // a plane's lower and upper maxima of every row of the thread (rows r - 1
+    // and r, columns -1 and 0; rows r and r + 1, columns 0 and 1), and both
+    // together as candidates of the plane's own vertices
+    auto maxima = [&](const uint32_t* w, uint64_t* lower, uint64_t* upper, uint64_t* own) {
         uint64_t lp[YPT + 1], up[YPT + 1];
-#pragma unroll
-        for (int r = -1; r <= YPT; ++r) {
-            const uint64_t mid = coded(w[at(r, 0)], code_of(r, 0));
-            if (r < YPT) lp[r + 1] = later_max(coded(w[at(r, -1)], code_of(r, -1)), mid);
-            if (r >= 0) up[r] = later_max(mid, coded(w[at(r, 1)], code_of(r, 1)));
-        }
+        static_for<0, YPT + 2>([&](auto step) {
+            constexpr int r = decltype(step)::value - 1;
+            const uint64_t mid = coded<code_of(r, 0)>(w[at(r, 0)]);
+            if constexpr (r < YPT) lp[r + 1] = later_max(coded<code_of(r, -1)>(w[at(r, -1)]), mid);
+            if constexpr (r >= 0) up[r] = later_max(mid, coded<code_of(r, 1)>(w[at(r, 1)]));
+        });
 #pragma unroll
         for (int c = 0; c < YPT; ++c) {
             lower[c] = later_max(lp[c], lp[c + 1]);
             upper[c] = later_max(up[c], up[c + 1]);
+            own[c] = later_max(lower[c], upper[c]) | OWN;
+            upper[c] |= ABOVE;
         }
     };
     // low[c]: the lower maximum of the plane below; mid[c]: the maximum over
     // the planes below and own
     uint64_t low[YPT], mid[YPT];
-    auto advance = [&](const uint64_t* lower, const uint64_t* upper) {
+    auto advance = [&](const uint64_t* lower, const uint64_t* own) {
 #pragma unroll
         for (int c = 0; c < YPT; ++c) {
-            mid[c] = later_max(low[c] | BELOW, later_max(lower[c], upper[c]) | OWN);
-            low[c] = lower[c];
+            mid[c] = later_max(low[c], own[c]);
+            low[c] = lower[c] | BELOW;
         }
     };
     load_plane(win[0], 0);
     load_plane(win[1], 1);
     {
-        uint64_t lower[YPT], upper[YPT];
-        maxima(win[0], low, upper);
-        maxima(win[1], lower, upper);
-        advance(lower, upper);
+        uint64_t lower[YPT], upper[YPT], own[YPT];
+        maxima(win[0], low, upper, own);
+#pragma unroll
+        for (int c = 0; c < YPT; ++c) low[c] |= BELOW;
+        maxima(win[1], lower, upper, own);
+        advance(lower, own);
     }
 #pragma unroll
     for (int lz = 0; lz < TZ; ++lz) {
         load_plane(win[(lz + 2) % 3], lz + 2);
-        uint64_t lower[YPT], upper[YPT];
-        maxima(win[(lz + 2) % 3], lower, upper);
+        uint64_t lower[YPT], upper[YPT], own[YPT];
+        maxima(win[(lz + 2) % 3], lower, upper, own);
+        // the steepest candidates first, so that only their codes live on (and
+        // their keys, for wide samples)
+        uint32_t code[YPT];
+        [[maybe_unused]] uint32_t kbest[YPT];
+#pragma unroll
+        for (int c = 0; c < YPT; ++c) {
+            const uint64_t best = later_max(mid[c], upper[c]);
+            code[c] = (uint32_t)best;
+            asm("" : "+v"(code[c]));
+            if constexpr (SRC == SRC_WIDE) kbest[c] = (uint32_t)(best >> 31);
+        }
+        advance(lower, own);
         const int gz = z0 + lz;
 #pragma unroll
         for (int c = 0; c < YPT; ++c) {
@@ -838,22 +868,20 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
                 else
                     up = push_above<wins_tie>(up, u, uv);
             });
-            const uint64_t best = later_max(mid[c], upper[c] | ABOVE);
-            const uint32_t slot = (uint32_t)best & 0x1F8u;  // 8 * code
+            const uint32_t slot = code[c] & 0xFCu;  // 4 * code
             if (SRC == SRC_WIDE && !exact) {
                 // open: a neighbour meets the vertex, or two candidates lead;
                 // 32-bit keys are exact but for the two clamped ends
-                const uint32_t kbest = (uint32_t)(best >> 31);
                 uint32_t meet = ~0u;
-                int lead = uv == kbest;
+                int lead = uv == kbest[c];
                 static_for<0, K>([&](auto step) {
                     using RJ = Row<3, decltype(step)::value>;
                     const uint32_t u = win[(lz + 1 + RJ::dz) % 3][at(c + RJ::dy, RJ::dx)];
                     meet = min(meet, u ^ uv);
-                    lead += u == kbest;
+                    lead += u == kbest[c];
                 });
                 auto clamped = [](uint32_t k) { return k - 2u > kKeyTop - 4u; };
-                const bool tie = is32 ? clamped(uv) || clamped(kbest) : meet == 0u || lead > 1;
+                const bool tie = is32 ? clamped(uv) || clamped(kbest[c]) : meet == 0u || lead > 1;
                 open |= (in && tie ? 1u : 0u) << (c * TZ + lz);
             }
             // every quantity below without a branch (the connectivity table
@@ -861,15 +889,20 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
             // its own)
             const bool is_max = in && up == 0;
             const bool is_sad = in && eg_ubfe(s_conn[up >> 5], up, 1u) == 0u;
-            const uint2 succ = *reinterpret_cast<const uint2*>(
+            const uint32_t* entry = reinterpret_cast<const uint32_t*>(
                 reinterpret_cast<const char*>(s_succ + (MINMODE ? kCodeRow * c : -kCodeRow * c)) + slot);
+            uint32_t succ = entry[0], delta = entry[kCodes];
+            // both words are wanted on every lane: without this the second is
+            // read, and used, under a branch
+            asm("" : "+v"(succ), "+v"(delta));
             const int row0 = gz * SZ + gy * SY + x0;  // uniform
-            const int pv = row0 + lx + (int)succ.y;
+            const int pv = row0 + lx + (int)delta;
             const int li4 = 4 * ((lz * TY + ly) * TX) + (int)lane_b;  // byte offset in the chain array
             // leaves the tile iff it steps across a face the vertex lies on
             const uint32_t faces = bx | (ly == 0 ? 4u : 0u) | (ly == TY - 1 ? 8u : 0u) | (lz == 0 ? 16u : 0u) |
                                    (lz == TZ - 1 ? 32u : 0u);
-            int n = (faces & succ.x & 63u) ? -(pv + 1) : li4 + ((int)succ.x >> 6);
+            int leave = -(pv + 1), stay = li4 + ((int)succ >> 6);
+            int n = (faces & succ & 63u) ? leave : stay;
             if constexpr (!FULL) n = in ? n : 4 * TILE + li4;  // a vertex outside the grid ends its own chain
             if constexpr (PTR)
                 if (in) store_row(ptr + row0, lane_b, pv);
@@ -877,7 +910,6 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
             park_word(word, is_max, c * TZ + lz);
             park_word(word, is_sad, 32 + c * TZ + lz);
         }
-        advance(lower, upper);
     }
     if (SRC == SRC_WIDE && !exact) {
         // the open vertices again, on the samples themselves (the halo's keys
@@ -943,7 +975,9 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
     if (__ballot(nan) != 0 && __lane_id() == 0) atomicOr(&ctr[C_NAN], 1u);
     // exit targets go behind the chains, in LDS the halo no longer needs
     uint32_t claim;
-    const uint32_t nexit = rank_exits<VPT>(nxt, s_tmp, s_u + TILE, ctr, claim);
+    const uint32_t region = blockIdx.x & (a.regions - 1u);
+    uint32_t* counter = a.claims + kRegionStride * region;
+    const uint32_t nexit = rank_exits<VPT>(nxt, s_tmp, s_u + TILE, counter, claim);
 #pragma unroll
     for (int c = 0; c < YPT; ++c)
 #pragma unroll
@@ -958,7 +992,7 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
     double_tile_chains<VPT, TILE, 4>(nxt, s_nxt,
                                      [&](int k) { return ((k % TZ) * TY + ly0 + k / TZ) * TX + lx; });
     uint32_t base;
-    const bool fit = place_exits(nexit, claim, s_u + TILE, s_tmp, a.exits, a.cap_exit, base);
+    const bool fit = place_exits(nexit, claim, s_u + TILE, s_tmp, a, region, base);
     const int xoff = exit_offset<VPT>(nxt, fit, base, s_u + TILE, X * Y * Z);
     const int tile0 = z0 * SZ + y0 * SY + x0;
 #pragma unroll
@@ -978,35 +1012,39 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
     }
 }
 
+// LDS of a 3D tile's workgroup: the small tables first, where the reads' 8-bit
+// offsets reach them from address 0.
+template <int TY, int TZ>
+struct Tile3Lds {
+    uint32_t tmp[kTile3Words];
+    uint32_t conn[512];
+    uint32_t u[66 * (TY + 2) * (TZ + 2)];
+};
+
 // Full tiles (every vertex in the grid, the common case) run a variant without
 // per-vertex bounds tests; whether pointers are written is a compile-time
 // choice too, which keeps the output address out of the unrolled loop.
-template <bool MINMODE, int TY, int TZ, int SRC = SRC_F32>
-__device__ __forceinline__ void tile3d(const TileArgs& a, int b, uint32_t* s_u, uint32_t* s_conn, uint32_t* s_tmp)
+template <bool MINMODE, int TY, int TZ, bool PTR, int SRC>
+__device__ __forceinline__ void tile3d(const TileArgs& a, int b, Tile3Lds<TY, TZ>& s)
 {
     const int tx = b % a.tiles_x;
     const int rr = b / a.tiles_x;
     const int ty = rr % a.tiles_y;
     const int tz = rr / a.tiles_y;
     const bool full = (tx + 1) * 64 <= a.X && (ty + 1) * TY <= a.Y && (tz + 1) * TZ <= a.Z;
-    if (a.ptr) {
-        if (full)
-            tile3d_body<MINMODE, TY, TZ, true, true, SRC>(a, b, s_u, s_conn, s_tmp);
-        else
-            tile3d_body<MINMODE, TY, TZ, false, true, SRC>(a, b, s_u, s_conn, s_tmp);
-    } else {
-        if (full)
-            tile3d_body<MINMODE, TY, TZ, true, false, SRC>(a, b, s_u, s_conn, s_tmp);
-        else
-            tile3d_body<MINMODE, TY, TZ, false, false, SRC>(a, b, s_u, s_conn, s_tmp);
-    }
+    if (full)
+        tile3d_body<MINMODE, TY, TZ, true, PTR, SRC>(a, b, s.u, s.conn, s.tmp);
+    else
+        tile3d_body<MINMODE, TY, TZ, false, PTR, SRC>(a, b, s.u, s.conn, s.tmp);
 }
 
 // Tiles of one XCD are consecutive in memory: workgroups are dispatched to
-// the eight XCDs round-robin, so block b takes tile (b % 8) * (T / 8) + b / 8.
+// the eight XCDs round-robin, so XCD x = b % 8 takes the x-th of eight runs of
+// tiles (the first T % 8 runs are one tile longer).
 __device__ __forceinline__ int xcd_tile(int b, int ntiles)
 {
-    return (ntiles & 7) == 0 ? (b & 7) * (ntiles >> 3) + (b >> 3) : b;
+    const int x = b & 7;
+    return x * (ntiles >> 3) + min(x, ntiles & 7) + (b >> 3);
 }
 
 }  // namespace eg
