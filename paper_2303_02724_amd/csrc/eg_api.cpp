@@ -336,6 +336,9 @@ eg_status eg_paths_typed(int dtype, const void* field, int ndim, const int64_t* 
     p.header = gptr(paths->header);
     p.cap_paths = (uint32_t)paths->cap_paths;
     p.cap_vertices = (uint32_t)paths->cap_vertices;
+    // the exit list and its labels lie side by side and have served
+    p.rec = gptr((int32_t*)w.exits);
+    p.cap_rec = (w.exres - (int32_t*)w.exits) + w.cap_exit;
     ArcArgs a = arc_args(f, g, *out, w);
     a.dtype = dtype;
     const hipError_t e = launch_paths(a, p, (hipStream_t)stream);

@@ -310,16 +310,31 @@ __device__ __forceinline__ VKey<SRC> vertex_key(const ArcArgs& A, int v)
         return mode_key<MINMODE>(A.f[v]);
 }
 
+// Where a kernel has the keys of a neighbourhood once it is loaded.
+enum : int {
+    KEYS_AGAIN = 0,  // nowhere: those of a component are read again
+    KEYS_LDS = 1,    // in the thread's column of LDS
+    KEYS_REGS = 2,   // in registers: a rep takes a scan of all rows
+};
+
 // LDS of a block of the arc and path kernels: the rows' linear offsets, and
 // the keys (row j of thread t at keys[j][t]) where they are parked.
-template <int NDIM, bool PARK, int SRC_ = SRC_F32>
+template <int NDIM, int KEYS, int SRC_ = SRC_F32>
 struct RowLds {
     static constexpr int K = Rows<NDIM>::K;
     static constexpr int N = NDIM;
     static constexpr int SRC = SRC_;
-    static constexpr bool kPark = PARK;
-    VKey<SRC> keys[PARK ? K : 1][PARK ? kArcThreads<NDIM> : 1];
+    static constexpr int kKeys = KEYS;
+    VKey<SRC> keys[KEYS == KEYS_LDS ? K : 1][KEYS == KEYS_LDS ? kArcThreads<NDIM> : 1];
     int off[K];
+};
+
+// A saddle's neighbourhood: its upper-link mask, and the keys where they stay
+// in registers.
+template <class LDS>
+struct Hood {
+    LMask<LDS::N> up;
+    VKey<LDS::SRC> us[LDS::kKeys == KEYS_REGS ? LDS::K : 1];
 };
 
 template <class LDS>
@@ -345,7 +360,7 @@ __device__ __forceinline__ void load_rows(const ArcArgs& A, LDS& T)
 // 3.3), and the rows' keys into this thread's column (0 outside the grid,
 // below every vertex).
 template <int NDIM, bool MINMODE, class LDS>
-__device__ __forceinline__ LMask<NDIM> load_nbhd(const ArcArgs& A, int v, LDS& T)
+__device__ __forceinline__ Hood<LDS> load_nbhd(const ArcArgs& A, int v, LDS& T)
 {
     constexpr Rows<NDIM> R = make_rows_ce<NDIM>();
     constexpr int K = Rows<NDIM>::K;
@@ -362,6 +377,7 @@ __device__ __forceinline__ LMask<NDIM> load_nbhd(const ArcArgs& A, int v, LDS& T
         }
     }
     const VKey<LDS::SRC> uv = vertex_key<NDIM, MINMODE, LDS::SRC>(A, v);
+    Hood<LDS> h;
     // 32 rows per word, pushed from the highest row down
     constexpr int NW = (K + 31) / 32;
     uint32_t wd[NW];
@@ -380,7 +396,8 @@ __device__ __forceinline__ LMask<NDIM> load_nbhd(const ArcArgs& A, int v, LDS& T
         // no branch around the load: every row's load is in flight at once
         const VKey<LDS::SRC> x = vertex_key<NDIM, MINMODE, LDS::SRC>(A, in ? v + off : v);
         const VKey<LDS::SRC> u = in ? x : 0;
-        if constexpr (LDS::kPark) T.keys[j][threadIdx.x] = u;
+        if constexpr (LDS::kKeys == KEYS_LDS) T.keys[j][threadIdx.x] = u;
+        if constexpr (LDS::kKeys == KEYS_REGS) h.us[j] = u;
         constexpr bool wins = (j >= K / 2) != MINMODE;
         if constexpr (LDS::SRC == SRC_WIDE)  // a wide sample's key may be 0 itself
             wd[0] = (j == K - 1 ? 0u : 2u * wd[0]) | (in && (wins ? u >= uv : u > uv) ? 1u : 0u);
@@ -392,7 +409,8 @@ __device__ __forceinline__ LMask<NDIM> load_nbhd(const ArcArgs& A, int v, LDS& T
     LMask<NDIM> up = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) up |= LMask<NDIM>(wd[w]) << (w == 0 ? 0 : 32 * w);
-    return up;
+    h.up = up;
+    return h;
 }
 
 // The component of the lowest row of `rem`: a table of every mask up to 3D,
@@ -431,7 +449,7 @@ __device__ __forceinline__ LMask<NDIM> first_component(LMask<NDIM> rem)
 template <int NDIM, bool MINMODE, class LDS>
 __device__ __forceinline__ VKey<LDS::SRC> key_at(const ArcArgs& A, int v, int j, const LDS& T)
 {
-    if constexpr (LDS::kPark)
+    if constexpr (LDS::kKeys == KEYS_LDS)
         return T.keys[j][threadIdx.x];
     else
         return vertex_key<NDIM, MINMODE, LDS::SRC>(A, v + T.off[j]);
@@ -441,8 +459,20 @@ __device__ __forceinline__ VKey<LDS::SRC> key_at(const ArcArgs& A, int v, int j,
 // ascending vertex order, the later of two equal vertices the higher one, the
 // earlier in the minimum graph.
 template <int NDIM, bool MINMODE, class LDS>
-__device__ __forceinline__ int rep_of(const ArcArgs& A, int v, LMask<NDIM> comp, const LDS& T)
+__device__ __forceinline__ int rep_of(const ArcArgs& A, int v, const Hood<LDS>& h, LMask<NDIM> comp, const LDS& T)
 {
+    if constexpr (LDS::kKeys == KEYS_REGS) {
+        VKey<LDS::SRC> best_u = 0;
+        int best = 0;
+        static_for<0, LDS::K>([&](auto step) {
+            constexpr int j = MINMODE ? LDS::K - 1 - decltype(step)::value : decltype(step)::value;
+            if ((uint32_t)(comp >> j) & 1u && h.us[j] >= best_u) {
+                best_u = h.us[j];
+                best = j;
+            }
+        });
+        return v + T.off[best];
+    }
     // two rows a round (the second again the first when there is none left),
     // so that two reads are in flight
     VKey<LDS::SRC> best_u = 0;
@@ -467,12 +497,13 @@ __device__ __forceinline__ int rep_of(const ArcArgs& A, int v, LMask<NDIM> comp,
 // Calls f(rep) for every upper-link component of saddle v, in ascending order
 // of the components' smallest vertices (rows are in linear-index order).
 template <int NDIM, bool MINMODE, class LDS, class F>
-__device__ __forceinline__ void for_each_rep(const ArcArgs& A, int v, LMask<NDIM> rem, const LDS& T, F&& f)
+__device__ __forceinline__ void for_each_rep(const ArcArgs& A, int v, const Hood<LDS>& h, const LDS& T, F&& f)
 {
+    LMask<NDIM> rem = h.up;
     while (rem != 0) {
         const LMask<NDIM> comp = first_component<NDIM>(rem);
         rem &= ~comp;
-        f(rep_of<NDIM, MINMODE>(A, v, comp, T));
+        f(rep_of<NDIM, MINMODE>(A, v, h, comp, T));
     }
 }
 
@@ -480,11 +511,11 @@ __device__ __forceinline__ void for_each_rep(const ArcArgs& A, int v, LMask<NDIM
 // only after the next component's rep has been sought, so its load is not
 // waited for on its own.
 template <int NDIM, bool MINMODE, class LDS, class F>
-__device__ __forceinline__ void for_each_arc_label(const ArcArgs& A, int v, LMask<NDIM> up, const LDS& T, F&& f)
+__device__ __forceinline__ void for_each_arc_label(const ArcArgs& A, int v, const Hood<LDS>& h, const LDS& T, F&& f)
 {
     uint32_t last = 0;
     bool have = false;
-    for_each_rep<NDIM, MINMODE>(A, v, up, T, [&](int rep) {
+    for_each_rep<NDIM, MINMODE>(A, v, h, T, [&](int rep) {
         const uint32_t L = (uint32_t)A.lab[rep];
         if (have) f(last);
         last = L;
@@ -531,7 +562,7 @@ __device__ __forceinline__ void sort_few(uint32_t (&x)[8])
 }
 
 template <int NDIM, bool MINMODE, class LDS>
-__device__ __forceinline__ ArcList<NDIM> first_arcs(const ArcArgs& A, int v, LMask<NDIM> up, const LDS& T, int& beta)
+__device__ __forceinline__ ArcList<NDIM> first_arcs(const ArcArgs& A, int v, const Hood<LDS>& h, const LDS& T, int& beta)
 {
     constexpr int S = ArcList<NDIM>::S;
     // every component of a saddle up to 3D, nearly every saddle's above, has a
@@ -542,7 +573,7 @@ __device__ __forceinline__ ArcList<NDIM> first_arcs(const ArcArgs& A, int v, LMa
 #pragma unroll
     for (int k = 0; k < X; ++k) x[k] = ~0u;
     beta = 0;
-    for_each_arc_label<NDIM, MINMODE>(A, v, up, T, [&](uint32_t L) {
+    for_each_arc_label<NDIM, MINMODE>(A, v, h, T, [&](uint32_t L) {
         ++beta;
 #pragma unroll
         for (int k = 0; k < X; ++k) order2(x[k], L);
@@ -565,7 +596,7 @@ __device__ __forceinline__ ArcList<NDIM> first_arcs(const ArcArgs& A, int v, LMa
         // more components than places: the list again, label by label
 #pragma unroll
         for (int k = 0; k < S; ++k) r.lo[k] = ~0u;
-        for_each_arc_label<NDIM, MINMODE>(A, v, up, T, [&](uint32_t L) {
+        for_each_arc_label<NDIM, MINMODE>(A, v, h, T, [&](uint32_t L) {
             bool known = false;
 #pragma unroll
             for (int k = 0; k < S; ++k) known |= L == r.lo[k];
@@ -582,13 +613,13 @@ __device__ __forceinline__ ArcList<NDIM> first_arcs(const ArcArgs& A, int v, LMa
 // each: for saddles with more distinct arcs than the list holds (rare).  Calls
 // emit(k, label) for the k-th of them and returns their number.
 template <int NDIM, bool MINMODE, class LDS, class E>
-__device__ __forceinline__ uint32_t labels_above(const ArcArgs& A, int v, LMask<NDIM> up, const LDS& T, uint32_t last,
+__device__ __forceinline__ uint32_t labels_above(const ArcArgs& A, int v, const Hood<LDS>& h, const LDS& T, uint32_t last,
                                                  E&& emit)
 {
     uint32_t k = 0;
     for (;;) {
         uint32_t next = ~0u;
-        for_each_arc_label<NDIM, MINMODE>(A, v, up, T, [&](uint32_t L) {
+        for_each_arc_label<NDIM, MINMODE>(A, v, h, T, [&](uint32_t L) {
             if (L > last && L < next) next = L;
         });
         if (next == ~0u) return k;
@@ -613,14 +644,14 @@ __device__ __forceinline__ void arc_count_body(const ArcArgs& A, uint32_t blk, u
         // saddle ids come from the compaction; the check keeps a stage run
         // on a workspace without classification inside the grid
         const int v = min(max(A.saddles[i], 0), A.N - 1);
-        const LMask<NDIM> up = load_nbhd<NDIM, MINMODE>(A, v, T);
+        const auto h = load_nbhd<NDIM, MINMODE>(A, v, T);
         int beta;
-        const ArcList<NDIM> r = first_arcs<NDIM, MINMODE>(A, v, up, T, beta);
+        const ArcList<NDIM> r = first_arcs<NDIM, MINMODE>(A, v, h, T, beta);
         constexpr int S = ArcList<NDIM>::S;
         uint32_t n = 0;
 #pragma unroll
         for (int k = 0; k < S; ++k) n += r.lo[k] != ~0u;
-        if (r.more) n += labels_above<NDIM, MINMODE>(A, v, up, T, r.lo[S - 1], [](uint32_t, uint32_t) {});
+        if (r.more) n += labels_above<NDIM, MINMODE>(A, v, h, T, r.lo[S - 1], [](uint32_t, uint32_t) {});
         if (A.beta) A.beta[i] = beta;
         A.offsets[i + 1] = (int32_t)n;  // the count until k_arc_write turns it into an offset
         A.atmp[i] = make_uint4(r.lo[0], r.lo[1], r.lo[2], r.lo[3]);
@@ -674,6 +705,7 @@ __device__ __forceinline__ void arc_write_body(const ArcArgs& A, uint32_t blk, u
     chunk(saddle_count(A), nb, blk, lo, hi);
     const int tid = threadIdx.x;
     if (blk == 0 && tid == 0) A.offsets[0] = 0;
+    if (lo >= hi && blk != nb - 1) return;  // nothing to write, and not the last block
     uint32_t run, pairs;
     sums_before<BT>(A, 2, blk, tmp, run, pairs);
     const uint32_t first = run;
@@ -732,8 +764,8 @@ __device__ __forceinline__ void arc_write_body(const ArcArgs& A, uint32_t blk, u
                 if ((uint32_t)A.offsets[i + 1] - pos <= (uint32_t)S) continue;
                 const int v = min(max(A.saddles[i], 0), A.N - 1);
                 const uint32_t last = S > 4 ? A.atmp[A.cap_sad + i].w : A.atmp[i].w;
-                const LMask<NDIM> up = load_nbhd<NDIM, MINMODE>(A, v, T);
-                labels_above<NDIM, MINMODE>(A, v, up, T, last, [&](uint32_t k, uint32_t L) {
+                const auto h = load_nbhd<NDIM, MINMODE>(A, v, T);
+                labels_above<NDIM, MINMODE>(A, v, h, T, last, [&](uint32_t k, uint32_t L) {
                     if (pos + S + k < A.cap_arc) A.arcs[pos + S + k] = (int32_t)L;
                 });
             }
@@ -747,7 +779,7 @@ template <int NDIM, bool MINMODE, int SRC = SRC_F32>
 __global__ __launch_bounds__(kArcThreads<NDIM>)
     __attribute__((amdgpu_waves_per_eu(1, kArcWaves<NDIM>))) void k_arc_count(OneField sel)
 {
-    __shared__ RowLds<NDIM, kKeysInLds<NDIM>, SRC> T;
+    __shared__ RowLds<NDIM, kKeysInLds<NDIM> ? KEYS_LDS : KEYS_AGAIN, SRC> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
@@ -757,7 +789,7 @@ __global__ __launch_bounds__(kArcThreads<NDIM>)
 template <int NDIM, bool MINMODE, int SRC = SRC_F32>
 __global__ __launch_bounds__(kArcThreads<NDIM>) void k_arc_write(OneField sel)
 {
-    __shared__ RowLds<NDIM, false, SRC> T;
+    __shared__ RowLds<NDIM, KEYS_AGAIN, SRC> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
@@ -773,8 +805,8 @@ __global__ __launch_bounds__(256) void k_arc_batched(BatchFields sel)
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
     const int kind = __builtin_amdgcn_readfirstlane((A.ndim == 3 ? 2 : 0) + (A.minima ? 1 : 0));
-    using L3 = RowLds<3, !WRITE>;
-    using L2 = RowLds<2, !WRITE>;
+    using L3 = RowLds<3, WRITE ? KEYS_AGAIN : KEYS_LDS>;
+    using L2 = RowLds<2, WRITE ? KEYS_AGAIN : KEYS_LDS>;
     __shared__ L3 T3;
     L2& T2 = reinterpret_cast<L2&>(T3);
 #define EG_BODY(ND, MM)                               \
@@ -815,61 +847,101 @@ __device__ __forceinline__ bool walk(const ArcArgs& A, EG_GPTR(const int32_t) co
     }
 }
 
+// The count pass records the vertices it meets: step t of path c (c < kRecPaths)
+// of saddle i at rec[(t kRecPaths + c) n + i], n saddles, for as many steps as
+// the scratch holds.  The write pass then copies a saddle's paths, all of whose
+// loads are independent, instead of walking them a second time, one dependent
+// load a step (17 k paths in 256^3: 155 us for the two walks, 100 with the
+// copy; 35 k in 512^3: 261 and 165).  Saddles with more or longer paths are
+// walked again.
+constexpr uint32_t kRecPaths = 3;
+// Keys of the path kernels.  Walking wants waves, so 5D has no room to park
+// them, and reading a component's keys again costs more than scanning
+// registers at four waves per SIMD (32^5: 2.96 ms again, 3.9 parked, 2.6).
+template <int NDIM>
+constexpr int kPathKeys = NDIM <= 4 ? KEYS_LDS : NDIM == 5 ? KEYS_REGS : KEYS_AGAIN;
+constexpr uint32_t kRecSteps = 128;
+__device__ __forceinline__ uint32_t recorded_steps(const PathArgs& P, uint32_t n)
+{
+    const int64_t s = P.cap_rec / ((int64_t)kRecPaths * (n > 0 ? n : 1));
+    // with little room few saddles' paths fit, and recording costs more than
+    // it saves (201 x 190 x 333 noise, two steps: 1.50 -> 1.55 ms)
+    return s < 16 ? 0u : (uint32_t)(s < (int64_t)kRecSteps ? s : (int64_t)kRecSteps);
+}
+
 // Paths and path vertices of every saddle of the block's chunk (kept for the
-// write pass in the workspace); the block's sums go to rows 0 and 1, and whether
-// a walk met a pointer that leaves the grid or does not rise to row 2.
+// write pass in the workspace); the block's sums go to rows 1 and 2, and whether
+// a walk met a pointer that leaves the grid or does not rise to row 3 (row 0
+// also holds the exit list's counters).
 template <int NDIM, bool MINMODE, int SRC = SRC_F32>
-__global__ __launch_bounds__(kArcThreads<NDIM>) void k_path_count(OneField sel, PathArgs P)
+__global__ __launch_bounds__(kArcThreads<NDIM>) __attribute__((amdgpu_waves_per_eu(NDIM == 5 ? 4 : 1, 8))) void k_path_count(OneField sel, PathArgs P)
 {
     constexpr int BT = kArcThreads<NDIM>;
-    __shared__ RowLds<NDIM, false, SRC> T;
+    __shared__ RowLds<NDIM, kPathKeys<NDIM>, SRC> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
     load_rows(A, T);
     uint32_t lo, hi;
-    chunk(saddle_count(A), nb, blk, lo, hi);
+    const uint32_t n = saddle_count(A), steps = recorded_steps(P, n);
+    chunk(n, nb, blk, lo, hi);
     uint32_t sp = 0, sv = 0;
     bool bad = false;
     for (uint32_t i = lo + threadIdx.x; i < hi; i += BT) {
         const int v = A.saddles[i];
         uint32_t np = 0, nv = 0;
+        uint32_t len0 = 0, len1 = 0, longest = 0;
         if ((unsigned)v < (unsigned)A.N) {
-            const LMask<NDIM> up = load_nbhd<NDIM, MINMODE>(A, v, T);
-            for_each_rep<NDIM, MINMODE>(A, v, up, T, [&](int rep) {
+            const auto h = load_nbhd<NDIM, MINMODE>(A, v, T);
+            for_each_rep<NDIM, MINMODE>(A, v, h, T, [&](int rep) {
+                uint32_t len = 0;
+                int64_t at = (int64_t)np * n + i;
+                const uint32_t room = np < kRecPaths ? steps : 0;
+                bad |= !walk<NDIM, MINMODE, SRC>(A, P.ptr, rep, [&](int r) {
+                    if (len < room) P.rec[at] = r;
+                    at += (int64_t)kRecPaths * n;
+                    ++len;
+                });
+                len0 = np == 0 ? len : len0;
+                len1 = np == 1 ? len : len1;
+                longest = max(longest, len);
                 ++np;
-                ++nv;  // the saddle, then rep .. maximum
-                bad |= !walk<NDIM, MINMODE, SRC>(A, P.ptr, rep, [&](int) { ++nv; });
+                nv += len + 1;  // the saddle, then rep .. maximum
             });
         } else {
             bad = true;
         }
-        A.atmp[i] = make_uint4(np, nv, 0u, 0u);
+        // the first two paths' lengths (three paths: the third is the rest);
+        // none when the saddle has to be walked again
+        const bool copied = np <= kRecPaths && longest <= steps;
+        A.atmp[i] = make_uint4(np, nv, copied ? len0 : 0u, len1);
         sp += np;
         sv += nv;
     }
     block_sum2<BT>(sp, sv, tmp);
     const int any_bad = __syncthreads_or(bad);
     if (threadIdx.x == 0) {
-        A.bsum[blk] = sp;
-        A.bsum[kSumRow + blk] = sv;
-        A.bsum[2 * kSumRow + blk] = any_bad != 0;
+        A.bsum[kSumRow + blk] = sp;
+        A.bsum[2 * kSumRow + blk] = sv;
+        A.bsum[3 * kSumRow + blk] = any_bad != 0;
     }
 }
 
 template <int NDIM, bool MINMODE, int SRC = SRC_F32>
-__global__ __launch_bounds__(kArcThreads<NDIM>) void k_path_write(OneField sel, PathArgs P)
+__global__ __launch_bounds__(kArcThreads<NDIM>) __attribute__((amdgpu_waves_per_eu(NDIM == 5 ? 4 : 1, 8))) void k_path_write(OneField sel, PathArgs P)
 {
     constexpr int BT = kArcThreads<NDIM>;
-    __shared__ RowLds<NDIM, false, SRC> T;
+    __shared__ RowLds<NDIM, kPathKeys<NDIM>, SRC> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
     const ArcArgs A = sel.locate(blk, nb);  // a copy: loop loads cannot alias it
     load_rows(A, T);
     uint32_t lo, hi;
-    chunk(saddle_count(A), nb, blk, lo, hi);
+    const uint32_t n = saddle_count(A);
+    chunk(n, nb, blk, lo, hi);
+    if (lo >= hi && blk != nb - 1) return;  // nothing to write, and not the last block
     uint32_t runp, runv;
-    sums_before<BT>(A, 0, blk, tmp, runp, runv);
+    sums_before<BT>(A, 1, blk, tmp, runp, runv);
     for (uint32_t base = lo; base < hi; base += BT) {
         const uint32_t i = base + threadIdx.x;
         const bool valid = i < hi;
@@ -879,9 +951,31 @@ __global__ __launch_bounds__(kArcThreads<NDIM>) void k_path_write(OneField sel, 
         uint32_t at = runv + block_excl_scan<BT>(c.y, tmp, tv);
         const int v = valid ? A.saddles[i] : 0;
         if (valid) P.pair_offsets[i] = (int32_t)pk;
-        if (valid && (unsigned)v < (unsigned)A.N) {
-            const LMask<NDIM> up = load_nbhd<NDIM, MINMODE>(A, v, T);
-            for_each_rep<NDIM, MINMODE>(A, v, up, T, [&](int rep) {
+        if (valid && (unsigned)v < (unsigned)A.N && c.z != 0) {
+            // every path of the saddle is on record (a path has a vertex at least)
+            uint32_t left = c.y - c.x;  // recorded vertices of the paths to come
+            for (uint32_t k = 0; k < c.x; ++k) {
+                const uint32_t len = k == 0 ? c.z : k == 1 ? c.w : left;
+                left -= len;
+                if (pk <= P.cap_paths) P.path_offsets[pk] = (int32_t)at;
+                ++pk;
+                if (at < P.cap_vertices) P.vertices[at] = v;
+                ++at;
+                EG_GPTR(const int32_t) from = P.rec + ((int64_t)k * n + i);
+                for (uint32_t t = 0; t < len; t += 8) {
+                    int r[8];
+#pragma unroll
+                    for (uint32_t j = 0; j < 8; ++j)
+                        r[j] = from[(int64_t)min(t + j, len - 1) * (kRecPaths * (int64_t)n)];
+#pragma unroll
+                    for (uint32_t j = 0; j < 8; ++j)
+                        if (t + j < len && at + t + j < P.cap_vertices) P.vertices[at + t + j] = r[j];
+                }
+                at += len;
+            }
+        } else if (valid && (unsigned)v < (unsigned)A.N) {
+            const auto h = load_nbhd<NDIM, MINMODE>(A, v, T);
+            for_each_rep<NDIM, MINMODE>(A, v, h, T, [&](int rep) {
                 if (pk <= P.cap_paths) P.path_offsets[pk] = (int32_t)at;
                 ++pk;
                 if (at < P.cap_vertices) P.vertices[at] = v;
@@ -899,7 +993,7 @@ __global__ __launch_bounds__(kArcThreads<NDIM>) void k_path_write(OneField sel, 
     // arrays, and the header
     if (blk != nb - 1) return;
     uint32_t bad = 0;
-    for (uint32_t i = threadIdx.x; i < nb; i += BT) bad |= A.bsum[2 * kSumRow + i];
+    for (uint32_t i = threadIdx.x; i < nb; i += BT) bad |= A.bsum[3 * kSumRow + i];
     const int any_bad = __syncthreads_or((int)bad);
     if (threadIdx.x != 0) return;
     const uint32_t nsad = A.ctr[C_NSAD];
@@ -921,10 +1015,11 @@ static void launch_paths_t(const OneField& sel, const PathArgs& p, uint32_t nb, 
 hipError_t launch_paths(const ArcArgs& a, const PathArgs& p, hipStream_t s)
 {
     // walks are chains of dependent loads: one block per 256 saddle slots
-    // keeps as many in flight as there are saddles
+    // keeps as many in flight as there are saddles, and evens out their lengths
+    // (1.95 M saddles in noise: 1.36 ms in 8192 blocks, 1.52 in 4096)
     ArcArgs ap = a;
     const int64_t want = ((int64_t)a.cap_sad + 255) / 256;
-    const int64_t nbp = want < kArcBlocks ? want : kArcBlocks;
+    const int64_t nbp = want < kSumRow ? want : kSumRow;
     if (nbp > ap.arc_blocks) ap.arc_blocks = (int32_t)nbp;
     const OneField sel{ap};
     const uint32_t nb = (uint32_t)ap.arc_blocks;

@@ -182,6 +182,8 @@ struct PathArgs {
     EG_GPTR(int32_t) path_offsets;
     EG_GPTR(int32_t) vertices;
     EG_GPTR(int32_t) header;
+    EG_GPTR(int32_t) rec;  // scratch for the vertices the count pass meets (the exit list and its labels)
+    int64_t cap_rec;
     uint32_t cap_paths, cap_vertices;
 };
 

@@ -22,3 +22,32 @@ def test_dense_masks_and_block_sums(shape):
         n = f.size
         g = gpu_graph(f, minima, cap_max=n, cap_sad=n, cap_arc=8 * n)
         assert_same(g, O.extremum_graph(f, minima), KEYS + ["ptr"], ctx)
+
+
+def _few_saddles(kind):
+    """Fields with few saddles, so that the paths' vertices are recorded in the
+    first walk and copied in the second: a valley between two long slopes
+    (paths around and far beyond the recorded 128 steps), a smooth 3D field,
+    and a saddle with twenty paths (more than are recorded)."""
+    if kind == "twenty":
+        from tests.test_oracle_pins import twenty_arc_saddle
+        return twenty_arc_saddle()[0]
+    if kind == "smooth":
+        return W.gaussian_random_field((48, 50, 70), 9, corr_len=5.0, workers=4)
+    steps = int(kind)
+    x = np.abs(np.arange(2 * steps + 1, dtype=np.float32) - steps)
+    return np.stack([x, x - 0.5, x - 0.75])
+
+
+@pytest.mark.parametrize("kind", ["smooth", "twenty", "126", "127", "128", "129", "1500"])
+def test_recorded_paths(kind):
+    from paper_2303_02724_amd import eg
+    import torch
+    f = np.ascontiguousarray(_few_saddles(kind), dtype=np.float32)
+    for minima in (False, True):
+        want = O.extremum_graph(f, minima)
+        wp = O.paths(f, want["ptr"], want["saddles"], minima)
+        _, p = eg.build_paths(torch.from_numpy(f).cuda(), minima=minima)
+        for a, b, name in zip((p.pair_offsets, p.path_offsets, p.vertices), wp,
+                              ("pair_offsets", "path_offsets", "vertices")):
+            assert np.array_equal(a.cpu().numpy(), b), f"{kind} minima={minima} {name}"
