@@ -214,6 +214,39 @@ __host__ __device__ constexpr int slab_inner()  // vertices per tile plane
     return s;
 }
 
+// The steepest row is found by groups: the rows (and the vertex itself) that
+// share their offsets along the first axes differ by {0,1}^Q along the last Q,
+// so a group is a corner and 2^Q fixed offsets from it.  Each group's maximum
+// is formed as its keys are compared for the mask; the last group that holds
+// the highest key is picked, and only its keys are looked at again, from LDS
+// (5D: 87 instructions where comparing all 62 rows with the maximum took 159).
+// Groups and positions are numbered in linear-index order.
+template <int NDIM>
+struct Groups {
+    static constexpr int Q = NDIM == 6 ? 3 : 2;
+    static constexpr int IN = 1 << Q;            // rows per group
+    static constexpr int G = 1 << (NDIM - Q);    // groups per half
+    static constexpr int H = (1 << NDIM) - 1;    // rows per half
+    static constexpr int of_row(int j)
+    {
+        return j >= H ? G + ((j - H + 1) >> Q) : G - 1 - ((H - j) >> Q);
+    }
+    // offset (-1, 0, 1) along axis i of position k of group g
+    static __host__ __device__ constexpr int offset(int g, int k, int i)
+    {
+        const int high = g >= G ? g - G : G - 1 - g;
+        const int bit = i < NDIM - Q ? (high >> (NDIM - Q - 1 - i)) & 1 : (k >> (NDIM - 1 - i)) & 1;
+        return g >= G ? bit : i < NDIM - Q ? -bit : bit - 1;
+    }
+    // LDS offset of position k from the group's corner (position 0)
+    static constexpr int inner(int k)
+    {
+        int d = 0;
+        for (int i = NDIM - Q; i < NDIM; ++i) d += ((k >> (NDIM - 1 - i)) & 1) * slab_hs<NDIM>(i);
+        return d;
+    }
+};
+
 struct SlabArgs {
     int32_t zc;                  // planes along axis 0 per block
     int32_t zblocks;             // blocks along axis 0: ceil(dims[0] / zc)
@@ -223,7 +256,7 @@ struct SlabArgs {
 };
 
 template <int NDIM, bool MINMODE>
-__global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restrict__ keys, Grid g, LinkTable t,
+__global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restrict__ keys, Grid g,
                                                        SlabArgs a, int32_t* __restrict__ lab,
                                                        int32_t* __restrict__ ptr, uint64_t* __restrict__ mmask,
                                                        uint64_t* __restrict__ smask)
@@ -242,9 +275,24 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
         return b;
     }();
     __shared__ uint32_t s_ring[3 * S];
-    __shared__ int32_t s_glin[K];
+    using GR = Groups<NDIM>;
+    static_assert(2 * GR::G * GR::IN <= 256 && 6 * GR::G <= 256, "the tables are filled in one step");
+    __shared__ int32_t s_lin[2 * GR::G * GR::IN];  // linear offset of every position
+    __shared__ int32_t s_corner[3][2 * GR::G];     // a group's corner in the ring, by the slot of plane z-1
     const int tid = threadIdx.x;
-    for (int i = tid; i < K; i += blockDim.x) s_glin[i] = t.lin[i];
+    if (tid < 2 * GR::G * GR::IN) {
+        int lin = 0;
+#pragma unroll
+        for (int i = 0; i < NDIM; ++i) lin += GR::offset(tid / GR::IN, tid % GR::IN, i) * a.st[i];
+        s_lin[tid] = lin;
+    }
+    if (tid < 6 * GR::G) {
+        const int below = tid / (2 * GR::G), grp = tid % (2 * GR::G);
+        int d = B;
+#pragma unroll
+        for (int i = 1; i < NDIM; ++i) d += GR::offset(grp, 0, i) * slab_hs<NDIM>(i);
+        s_corner[below][grp] = (below + 1 + GR::offset(grp, 0, 0)) % 3 * S + d;
+    }
 
     int rest = blockIdx.x;
     const int zb = rest % a.zblocks;
@@ -342,13 +390,15 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
                 const uint32_t* p = R.d[j][0] < 0 ? p0 : R.d[j][0] > 0 ? p2 : p1;
                 return p[d];
             };
-            // the upper-link mask, and the highest key of the closed
-            // neighbourhood (rows outside the grid hold key 0 < uv)
+            // the upper-link mask, and the highest key of every group (rows
+            // outside the grid hold key 0 < uv)
             // 32 rows per word, pushed from the highest row down so that row
             // j ends in bit j % 32 of word j / 32 (two instructions a row)
             constexpr int NW = (K + 31) / 32;
             uint32_t wd[NW];
-            uint32_t top = uv;
+            uint32_t gm[2 * GR::G];
+#pragma unroll
+            for (int i = 0; i < 2 * GR::G; ++i) gm[i] = i == GR::G || i == GR::G - 1 ? uv : 0u;
             static_for<0, K>([&](auto step) {
                 constexpr int j = K - 1 - decltype(step)::value;
                 constexpr bool wins = (j >= K / 2) != MINMODE;
@@ -357,36 +407,31 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
                     wd[j / 32] = first_above<wins>(u, uv);
                 else
                     wd[j / 32] = push_above<wins>(wd[j / 32], u, uv);
-                top = max(top, u);
+                gm[GR::of_row(j)] = max(gm[GR::of_row(j)], u);
             });
             Mask<NDIM> up = 0;
 #pragma unroll
             for (int w = 0; w < NW; ++w) up |= Mask<NDIM>(wd[w]) << (32 * w);
-            // the steepest target: the last vertex holding `top` in the order
-            // in which later vertices win ties (v itself between the halves)
-            int best_j = -1;
-            auto visit = [&](int j) {
-                if (key(j) == top) best_j = j;
-            };
-            auto self = [&]() {
-                if (uv == top) best_j = -1;
-            };
-            if (!MINMODE) {
+            // the steepest target: the last position holding the highest key,
+            // the first in the minimum graph
+            uint32_t top = gm[0];
 #pragma unroll
-                for (int j = 0; j < K / 2; ++j) visit(j);
-                self();
+            for (int i = 1; i < 2 * GR::G; ++i) top = max(top, gm[i]);
+            int grp = 0, pos = 0;
 #pragma unroll
-                for (int j = K / 2; j < K; ++j) visit(j);
-            } else {
+            for (int i = 0; i < 2 * GR::G; ++i) {
+                const int k = MINMODE ? 2 * GR::G - 1 - i : i;
+                grp = gm[k] == top ? k : grp;
+            }
+            const uint32_t* corner = s_ring + s_corner[sp][grp] + center;
 #pragma unroll
-                for (int j = K - 1; j >= K / 2; --j) visit(j);
-                self();
-#pragma unroll
-                for (int j = K / 2 - 1; j >= 0; --j) visit(j);
+            for (int i = 0; i < GR::IN; ++i) {
+                const int k = MINMODE ? GR::IN - 1 - i : i;
+                pos = corner[GR::inner(k)] == top ? k : pos;
             }
             is_max = up == 0;
             if (!is_max) is_sad = !link_connected<NDIM>(up);
-            const int best = best_j < 0 ? v : v + s_glin[best_j];
+            const int best = v + s_lin[grp * GR::IN + pos];
             lab[v] = is_max ? v : -(best + 1);
             if (ptr) ptr[v] = best;
         }
@@ -420,7 +465,7 @@ static void launch_classify_t(const float* f, const Grid& g, const LinkTable& t,
         a.zblocks = (int)((D0 + zc - 1) / zc);
         a.rows_per_plane = a.st[0] / g.dims[NDIM - 1];
         const int64_t blocks = tiles * a.zblocks;
-        hipLaunchKernelGGL((k_classify_slab<NDIM, MINMODE>), dim3((unsigned)blocks), dim3(256), 0, s, w.keys, g, t,
+        hipLaunchKernelGGL((k_classify_slab<NDIM, MINMODE>), dim3((unsigned)blocks), dim3(256), 0, s, w.keys, g,
                            a, lab, ptr, w.mmask, w.smask);
     } else {
         const int blocks = (int)((g.N + 255) / 256);

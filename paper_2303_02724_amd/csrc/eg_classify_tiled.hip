@@ -80,7 +80,7 @@ __device__ __forceinline__ void final_tile(const TileArgs& a, int b, const int32
 template <int TY, int TZ>
 __global__ __launch_bounds__(256) void k_final_tiled(TileArgs a, const int32_t* __restrict__ res)
 {
-    final_tile<TY, TZ>(a, xcd_tile(blockIdx.x, a.ntiles), res, &a.ctr[C_OPEN]);
+    final_tile<TY, TZ>(a, xcd_run(blockIdx.x, a.ntiles), res, &a.ctr[C_OPEN]);
 }
 
 // The same pass over the tiles of every 2D (or every 3D) field of a batch:
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                                                                                             int count)
 {
     __shared__ __align__(8) Tile3Lds<TY, TZ> s;
-    tile3d<MINMODE, TY, TZ, PTR, SRC_F32>(a, first + xcd_tile(blockIdx.x, count), s);
+    tile3d<MINMODE, TY, TZ, PTR, SRC_F32>(a, first + xcd_run(blockIdx.x, count), s);
 }
 
 template <bool MINMODE, int TY>
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(256) void k_classify2d(TileArgs a, int first, int c
     __shared__ uint32_t s_u[66 * (TY + 2)];
     __shared__ int32_t s_nxt[64 * TY];
     __shared__ uint32_t s_tmp[8];
-    tile_nd<2, MINMODE, TY, 1>(a, first + xcd_tile(blockIdx.x, count), s_u, s_nxt, nullptr, s_tmp);
+    tile_nd<2, MINMODE, TY, 1>(a, first + xcd_run(blockIdx.x, count), s_u, s_nxt, nullptr, s_tmp);
 }
 
 TileArgs tile_args(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, const Work& w, int ty, int tz)

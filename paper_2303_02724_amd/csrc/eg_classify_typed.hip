@@ -19,7 +19,7 @@ template <bool MINMODE, bool PTR, int SRC>
 __global__ __launch_bounds__(256) void k_classify3d_typed(TileArgs a)
 {
     __shared__ __align__(8) Tile3Lds<kTile3Y, kTile3Z> s;
-    tile3d<MINMODE, kTile3Y, kTile3Z, PTR, SRC>(a, xcd_tile(blockIdx.x, a.ntiles), s);
+    tile3d<MINMODE, kTile3Y, kTile3Z, PTR, SRC>(a, xcd_run(blockIdx.x, a.ntiles), s);
 }
 
 hipError_t launch_classify_typed(int dtype, const void* f, const Grid& g, bool minima, int32_t* lab, int32_t* ptr,

@@ -306,6 +306,15 @@ __device__ __forceinline__ uint32_t first_above(uint32_t u, uint32_t c)
     return r;
 }
 
+// Workgroups are dispatched to the eight XCDs round-robin: workgroup b of n
+// takes item xcd_run(b, n), so that each XCD works on a run of consecutive
+// items (the first n % 8 runs are one item longer).
+__device__ __forceinline__ int xcd_run(int b, int n)
+{
+    const int x = b & 7;
+    return x * (n >> 3) + min(x, n & 7) + (b >> 3);
+}
+
 // Links between label entries (see the codes below and eg_classify.hip): at
 // device scope when `fresh`.
 __device__ __forceinline__ int link_at(const int32_t* p, bool fresh)

@@ -1038,13 +1038,4 @@ __device__ __forceinline__ void tile3d(const TileArgs& a, int b, Tile3Lds<TY, TZ
         tile3d_body<MINMODE, TY, TZ, false, PTR, SRC>(a, b, s.u, s.conn, s.tmp);
 }
 
-// Tiles of one XCD are consecutive in memory: workgroups are dispatched to
-// the eight XCDs round-robin, so XCD x = b % 8 takes the x-th of eight runs of
-// tiles (the first T % 8 runs are one tile longer).
-__device__ __forceinline__ int xcd_tile(int b, int ntiles)
-{
-    const int x = b & 7;
-    return x * (ntiles >> 3) + min(x, ntiles & 7) + (b >> 3);
-}
-
 }  // namespace eg
