@@ -15,8 +15,8 @@
 
 namespace eg {
 
-// Counters and header; on grids without tiles (whose masks are written bit by
-// bit) the words of both masks too.
+// Counters and header; on 1D grids (whose masks are written bit by bit) the
+// words of both masks too.
 __global__ __launch_bounds__(256) void k_init(uint32_t* __restrict__ ctr, uint32_t* __restrict__ claims,
                                               int32_t* __restrict__ header, uint64_t* __restrict__ a,
                                               uint64_t* __restrict__ b, int64_t n)
@@ -35,8 +35,7 @@ __global__ __launch_bounds__(256) void k_init(uint32_t* __restrict__ ctr, uint32
 
 hipError_t launch_init(const Grid& g, const Work& w, int32_t* header, hipStream_t s)
 {
-    const bool tiled = g.ndim == 2 || g.ndim == 3;
-    const int64_t n = tiled ? 0 : w.words;
+    const int64_t n = g.ndim == 1 ? w.words : 0;
     const int64_t want = (n + 255) / 256;
     const int blocks = (int)(want < 1 ? 1 : want < 4096 ? want : 4096);
     hipLaunchKernelGGL(k_init, dim3(blocks), dim3(256), 0, s, w.ctr, w.claims, header, w.mmask, w.smask, n);
@@ -182,8 +181,11 @@ __global__ __launch_bounds__(256) void k_classify_generic(const uint32_t* __rest
 //   with the neighbourhood read from LDS instead of through the caches (62
 //   gathers per vertex in 5D, 126 in 6D, leave a kernel that reads them from
 //   memory bound by the memory pipeline, not by arithmetic).  A block owns a
-//   tile of the hyperplanes orthogonal to axis 0 (2x4x32 vertices in 4D,
-//   2x2x2x32 in 5D, 2x2x2x2x16 in 6D, one per thread) and a run of zc
+//   tile of the hyperplanes orthogonal to axis 0 (4x4x16 vertices in 4D,
+//   2x2x4x16 in 5D, 2x2x2x2x16 in 6D, one per thread: rows of 16 lose less on
+//   ragged axes and have less halo than rows of 32 and fill a halfword of the
+//   masks, stored without atomics; 41 x 64 x 60 x 65 FIG4A -> FIG4B us) and a
+//   run of zc
 //   consecutive planes along axis 0.  It keeps three
 //   consecutive planes of the tile plus a one-vertex halo in a ring in LDS
 //   (positions outside the grid hold key 0, below every vertex, so every row
@@ -192,7 +194,7 @@ __global__ __launch_bounds__(256) void k_classify_generic(const uint32_t* __rest
 template <int NDIM>
 __host__ __device__ constexpr int slab_e(int i)  // interior extent along axis i (1..n-1)
 {
-    return i == NDIM - 1 ? (NDIM == 6 ? 16 : 32) : (NDIM == 4 && i == 2) ? 4 : 2;
+    return i == NDIM - 1 ? 16 : NDIM == 4 ? 4 : NDIM == 5 && i == 3 ? 4 : 2;
 }
 template <int NDIM>
 __host__ __device__ constexpr int slab_hs(int i)  // LDS stride of axis i in a halo plane
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
     constexpr int PER = (S + 255) / 256;
     constexpr int EX = slab_e<NDIM>(NDIM - 1);
     static_assert(slab_inner<NDIM>() == 256, "one interior vertex per thread");
-    static_assert(64 % EX == 0, "a wave holds whole rows of the tile");
+    static_assert(EX == 16, "a row of the tile is a halfword of its mask word");
     // halo index of interior position (0,..,0), the smallest a row may reach
     constexpr int B = [] {
         int b = 0;
@@ -435,9 +437,27 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
             lab[v] = is_max ? v : -(best + 1);
             if (ptr) ptr[v] = best;
         }
-        const int64_t word = mine ? (int64_t)(z * a.rows_per_plane + rin) * XW + (x >> 6) : -1;
-        mask_or(is_max, word, x & 63, mmask);
-        mask_or(is_sad, word, x & 63, smask);
+        // every row of the tile is one halfword of each mask, stored by its
+        // first lane; the last tile of a row also clears what is left of the
+        // row's last word (in one store when it opens the word)
+        const uint64_t bm = __ballot(is_max), bs = __ballot(is_sad);
+        if (mine && tid % EX == 0) {
+            const int64_t row = (int64_t)(z * a.rows_per_plane + rin) * XW;
+            const uint32_t m = (uint32_t)(bm >> __lane_id()) & 0xFFFFu, sd = (uint32_t)(bs >> __lane_id()) & 0xFFFFu;
+            const int h = x >> 4;
+            const bool last = x + EX >= X;
+            if (last && (h & 3) == 0) {
+                mmask[row + (h >> 2)] = m;
+                smask[row + (h >> 2)] = sd;
+            } else {
+                uint16_t* mh = reinterpret_cast<uint16_t*>(mmask + row);
+                uint16_t* sh = reinterpret_cast<uint16_t*>(smask + row);
+                mh[h] = (uint16_t)m;
+                sh[h] = (uint16_t)sd;
+                if (last)
+                    for (int k = h + 1; k < 4 * XW; ++k) mh[k] = sh[k] = 0;
+            }
+        }
         sp = s1;
     }
 }

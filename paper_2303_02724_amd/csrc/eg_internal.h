@@ -393,7 +393,7 @@ __device__ __forceinline__ void exit_first(const ExitPart& p, const uint32_t* ex
 
 // ------------------------------------------------------------------ launchers
 
-// Counters and header to zero; the two masks too on grids without tiles.
+// Counters and header to zero; the two masks too on 1D grids.
 hipError_t launch_init(const Grid& g, const Work& w, int32_t* header, hipStream_t s);
 hipError_t launch_classify(const float* f, const Grid& g, const LinkTable& t, bool minima, int32_t* lab,
                            int32_t* ptr, const Work& w, const Tuning& tu, hipStream_t s);

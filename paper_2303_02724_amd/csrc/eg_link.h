@@ -46,21 +46,36 @@ __host__ __device__ constexpr W axis_bits(int i)
 }
 
 // every superset (within the n axes) of a subset in a
-template <int NDIM, class W>
-__host__ __device__ inline W supersets(W a)
+template <int NDIM>
+__host__ __device__ inline uint32_t supersets(uint32_t a)
 {
 #pragma unroll
-    for (int i = 0; i < NDIM; ++i) a |= (a & ~axis_bits<W>(i)) << (1 << i);
+    for (int i = 0; i < NDIM; ++i) a |= (a & ~axis_bits<uint32_t>(i)) << (1 << i);
     return a;
 }
 
 // every subset of a subset in a (the empty one included)
-template <int NDIM, class W>
-__host__ __device__ inline W subsets(W a)
+template <int NDIM>
+__host__ __device__ inline uint32_t subsets(uint32_t a)
 {
 #pragma unroll
-    for (int i = 0; i < NDIM; ++i) a |= (a & axis_bits<W>(i)) >> (1 << i);
+    for (int i = 0; i < NDIM; ++i) a |= (a & axis_bits<uint32_t>(i)) >> (1 << i);
     return a;
+}
+
+// The same for 6 axes: the first five stay within either half of the word, the
+// last joins the halves (no 64-bit shifts).
+template <int NDIM>
+__host__ __device__ inline uint64_t supersets(uint64_t a)
+{
+    const uint32_t lo = supersets<5>((uint32_t)a), hi = supersets<5>((uint32_t)(a >> 32));
+    return (uint64_t)(hi | lo) << 32 | lo;
+}
+template <int NDIM>
+__host__ __device__ inline uint64_t subsets(uint64_t a)
+{
+    const uint32_t lo = subsets<5>((uint32_t)a), hi = subsets<5>((uint32_t)(a >> 32));
+    return (uint64_t)hi << 32 | (lo | hi);
 }
 
 // the complements of the subsets in a: bit s -> bit 2^n - 1 - s
@@ -94,8 +109,15 @@ __host__ __device__ inline void to_subsets(M rows, typename SubsetWord<NDIM>::ty
 template <int NDIM, class W>
 __host__ __device__ inline void grow(W ml, W mu, W& cl, W& cu)
 {
-    cl = ml ? top_bit(ml) : W(0);  // the lowest row of the -b half has the largest b
-    cu = ml ? W(0) : mu & (~mu + 1);
+    // the first round: the lowest row of the -b half has the largest b, and
+    // nothing of the other half has been reached; without a -b half the lowest
+    // row is the seed itself
+    cl = ml ? top_bit(ml) : W(0);
+    cu = subsets<NDIM>(complements<NDIM>(cl)) & mu;
+    cu = ml ? cu : mu & (~mu + 1);
+    cl = supersets<NDIM>(cl) & ml;
+    cl = subsets<NDIM>(cl | complements<NDIM>(cu)) & ml;
+    if (cu == mu && cl == ml) return;
     while (true) {
         // each closure starts from the rows the previous one reached, so a
         // round follows several edges (superset, then subset or across, ...)
