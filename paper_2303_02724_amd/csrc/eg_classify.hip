@@ -310,7 +310,13 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
     const int z1 = min(z0 + a.zc, g.dims[0]);
 
     // the halo positions this thread loads: offset inside a plane of the
-    // grid, or -1 outside the grid
+    // grid, or -1 outside the grid.  Planes below 2^29 vertices are read
+    // through a raw buffer of exactly one plane, whose loads return 0 (the key
+    // of positions outside the grid) past its end: a position outside has an
+    // offset there, a plane outside the grid a buffer of no bytes.  So a load
+    // takes no instruction beside itself, and nothing waits for it before the
+    // plane is stored.
+    const bool small = a.st[0] < (1 << 29);
     int goff[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -325,7 +331,7 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
             in &= (c >= 0) & (c < g.dims[i]);
             off += c * a.st[i];
         }
-        goff[k] = in ? off : -1;
+        goff[k] = !in ? (small ? 0x7fffffff : -1) : small ? 4 * off : off;
     }
     // this thread's interior vertex: its halo index minus B, and its offset
     // inside a plane of the grid
@@ -352,6 +358,13 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
     auto fetch = [&](int z) {
         const bool zok = z >= 0 && z < g.dims[0];
         const int zoff = zok ? z * a.st[0] : 0;
+        if (small) {
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint32_t*>(keys + zoff), (short)0, zok ? 4 * a.st[0] : 0, 0x00020000);
+#pragma unroll
+            for (int k = 0; k < PER; ++k) r[k] = __builtin_amdgcn_raw_buffer_load_b32(rs, goff[k], 0, 0);
+            return;
+        }
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const bool ok = zok && goff[k] >= 0;
