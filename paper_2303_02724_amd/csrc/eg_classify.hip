@@ -181,12 +181,14 @@ __global__ __launch_bounds__(256) void k_classify_generic(const uint32_t* __rest
 //   with the neighbourhood read from LDS instead of through the caches (62
 //   gathers per vertex in 5D, 126 in 6D, leave a kernel that reads them from
 //   memory bound by the memory pipeline, not by arithmetic).  A block owns a
-//   tile of the hyperplanes orthogonal to axis 0 (4x4x16 vertices in 4D,
-//   2x2x4x16 in 5D, 2x2x2x2x16 in 6D, one per thread: rows of 16 lose less on
-//   ragged axes and have less halo than rows of 32 and fill a halfword of the
-//   masks, stored without atomics; 41 x 64 x 60 x 65 FIG4A -> FIG4B us) and a
-//   run of zc
-//   consecutive planes along axis 0.  It keeps three
+//   tile of the hyperplanes orthogonal to axis 0 (4x8x8 vertices in 4D,
+//   2x4x4x8 in 5D, 2x2x2x4x8 in 6D, one per thread: short rows lose less on
+//   ragged axes, have less halo and fill a byte of the masks, stored without
+//   atomics) and a run of zc consecutive planes along axis 0.  Rows of 32 (and
+//   atomics on the masks) against rows of 8: 41 x 64 x 60 x 65 186 and 125 us,
+//   30 x 31 x 29 x 30 x 33 1380 and 616; in 6D rows of 16 left two waves per
+//   SIMD to the LDS instead of three: 16^6 598 and 497.  Blocks of 512 threads
+//   were slower everywhere (more waves to a barrier).  It keeps three
 //   consecutive planes of the tile plus a one-vertex halo in a ring in LDS
 //   (positions outside the grid hold key 0, below every vertex, so every row
 //   of the table may be read), and slides it along axis 0: while one plane is
@@ -194,7 +196,10 @@ __global__ __launch_bounds__(256) void k_classify_generic(const uint32_t* __rest
 template <int NDIM>
 __host__ __device__ constexpr int slab_e(int i)  // interior extent along axis i (1..n-1)
 {
-    return i == NDIM - 1 ? 16 : NDIM == 4 ? 4 : NDIM == 5 && i == 3 ? 4 : 2;
+    if (i == NDIM - 1) return 8;
+    if (NDIM == 4) return i == 2 ? 8 : 4;
+    if (NDIM == 5) return i == 1 ? 2 : 4;
+    return i == 4 ? 4 : 2;
 }
 template <int NDIM>
 __host__ __device__ constexpr int slab_hs(int i)  // LDS stride of axis i in a halo plane
@@ -269,7 +274,7 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
     constexpr int PER = (S + 255) / 256;
     constexpr int EX = slab_e<NDIM>(NDIM - 1);
     static_assert(slab_inner<NDIM>() == 256, "one interior vertex per thread");
-    static_assert(EX == 16, "a row of the tile is a halfword of its mask word");
+    static_assert(EX == 8, "a row of the tile is a byte of its mask word");
     // halo index of interior position (0,..,0), the smallest a row may reach
     constexpr int B = [] {
         int b = 0;
@@ -450,25 +455,25 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
             lab[v] = is_max ? v : -(best + 1);
             if (ptr) ptr[v] = best;
         }
-        // every row of the tile is one halfword of each mask, stored by its
+        // every row of the tile is one byte of each mask's word, stored by its
         // first lane; the last tile of a row also clears what is left of the
         // row's last word (in one store when it opens the word)
         const uint64_t bm = __ballot(is_max), bs = __ballot(is_sad);
         if (mine && tid % EX == 0) {
             const int64_t row = (int64_t)(z * a.rows_per_plane + rin) * XW;
-            const uint32_t m = (uint32_t)(bm >> __lane_id()) & 0xFFFFu, sd = (uint32_t)(bs >> __lane_id()) & 0xFFFFu;
-            const int h = x >> 4;
+            const uint32_t m = (uint8_t)(bm >> __lane_id()), sd = (uint8_t)(bs >> __lane_id());
+            const int h = x / EX;
             const bool last = x + EX >= X;
-            if (last && (h & 3) == 0) {
-                mmask[row + (h >> 2)] = m;
-                smask[row + (h >> 2)] = sd;
+            if (last && h % 8 == 0) {
+                mmask[row + h / 8] = m;
+                smask[row + h / 8] = sd;
             } else {
-                uint16_t* mh = reinterpret_cast<uint16_t*>(mmask + row);
-                uint16_t* sh = reinterpret_cast<uint16_t*>(smask + row);
-                mh[h] = (uint16_t)m;
-                sh[h] = (uint16_t)sd;
+                uint8_t* mp = reinterpret_cast<uint8_t*>(mmask + row);
+                uint8_t* sdp = reinterpret_cast<uint8_t*>(smask + row);
+                mp[h] = (uint8_t)m;
+                sdp[h] = (uint8_t)sd;
                 if (last)
-                    for (int k = h + 1; k < 4 * XW; ++k) mh[k] = sh[k] = 0;
+                    for (int k = h + 1; k < 8 * XW; ++k) mp[k] = sdp[k] = 0;
             }
         }
         sp = s1;
