@@ -577,34 +577,51 @@ __global__ __launch_bounds__(256) void k_exit_jump(TileArgs a, int32_t* res, int
 }
 
 // Per-vertex labels of the grids without tiles: every code names a vertex.
-// Almost every field is done after one sweep; k_final_rest finishes the others.
 // Each XCD resolves a run of consecutive vertices, so that the links of
 // neighbouring vertices, which stay close, meet in its L2.
-__global__ __launch_bounds__(256) void k_final(int32_t* lab, int32_t N, uint32_t* __restrict__ ctr, int hops)
+struct LabelRun {
+    int32_t* lab;
+    uint32_t n, t, stride;
+};
+__device__ __forceinline__ LabelRun label_run(int32_t* lab, int32_t N)
 {
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
     // runs of whole quads; the last run ends with the vertices left over
-    const uint32_t x = blockIdx.x & 7u, q = (uint32_t)N >> 5;
-    const uint32_t lo = 4u * q * x, n = x == 7u ? (uint32_t)N - lo : 4u * q;
-    const bool open = sweep(lab + lo, n, lab, lab, N, hops, (blockIdx.x >> 3) * blockDim.x + threadIdx.x,
-                            (gridDim.x >> 3) * blockDim.x, false);
-    if (__ballot(open) != 0 && __lane_id() == 0) atomicOr(&ctr[C_MORE], 1u);
-    if (t == 0) ctr[C_PASSES] = 1;
+    const uint32_t x = blockIdx.x & 7u, q = (uint32_t)N >> 5, lo = 4u * q * x;
+    return LabelRun{lab + lo, x == 7u ? (uint32_t)N - lo : 4u * q, (blockIdx.x >> 3) * blockDim.x + threadIdx.x,
+                    (gridDim.x >> 3) * blockDim.x};
 }
 
-__global__ __launch_bounds__(256) void k_final_rest(int32_t* lab, int32_t N, uint32_t* __restrict__ ctr, int hops,
-                                                    int sweeps)
+// The first pass follows four links, so that no wave waits for the longest of
+// its 256 paths; the second starts from entries that are all that much further
+// on (4D labels 114 -> 72 us; three or six links are as good, and 5D and 6D,
+// whose paths are short or bound by their bytes, stay as they were).  Both give
+// a workgroup the same entries, so it leaves itself a note whether any are
+// open: a flag for all of them, set by an atomic or a store of every wave, cost
+// 90 to 290 us at one address.
+constexpr int kFirstHops = 4;
+__global__ __launch_bounds__(256) void k_final(int32_t* lab, int32_t N, uint32_t* __restrict__ ctr,
+                                               uint32_t* __restrict__ open_flags)
 {
-    if (__hip_atomic_load(&ctr[C_MORE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+    const LabelRun r = label_run(lab, N);
+    const int open = __syncthreads_or(sweep(r.lab, r.n, lab, lab, N, kFirstHops, r.t, r.stride, false));
+    if (threadIdx.x == 0) open_flags[blockIdx.x] = open != 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctr[C_PASSES] = 1;
+}
+
+__global__ __launch_bounds__(256) void k_final_rest(int32_t* lab, int32_t N, uint32_t* __restrict__ ctr,
+                                                    const uint32_t* __restrict__ open_flags, int hops, int sweeps)
+{
+    if (open_flags[blockIdx.x] == 0) return;
+    const LabelRun r = label_run(lab, N);
     bool open = true;
     int k = 0;
     for (; __ballot(open) != 0 && k < sweeps; ++k)
-        open = sweep(lab, (uint32_t)N, lab, lab, N, hops, t, gridDim.x * blockDim.x, true);
+        open = sweep(r.lab, r.n, lab, lab, N, hops, r.t, r.stride, k > 0);
     const bool left = __ballot(open) != 0;
     if (__lane_id() != 0) return;
     if (left) atomicOr(&ctr[C_OPEN], 1u);
-    atomicMax(&ctr[C_PASSES], 1u + (uint32_t)k);
+    // a diagnostic: waves that needed one sweep need not queue at the counter
+    if (k > 1 || (blockIdx.x == 0 && threadIdx.x == 0)) atomicMax(&ctr[C_PASSES], 1u + (uint32_t)k);
 }
 
 hipError_t launch_labels(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, hipStream_t s)
@@ -628,10 +645,11 @@ hipError_t launch_labels(const Grid& g, int32_t* lab, const Work& w, const Tunin
     }
     const int64_t want = ((int64_t)N / 4 + 255) / 256;
     const int blocks = (int)(want < 2048 ? (want / 8 + 1) * 8 : 2048);  // a multiple of the XCDs
-    hipLaunchKernelGGL(k_final, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, tu.hops);
+    uint32_t* flags = w.bsum + kSumRow;  // free until stage (d)
+    hipLaunchKernelGGL(k_final, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, flags);
     // every block of this launch fits the GPU at once, so that all entries
     // advance together
-    hipLaunchKernelGGL(k_final_rest, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, tu.hops, sweeps);
+    hipLaunchKernelGGL(k_final_rest, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, flags, tu.hops, sweeps);
     return hipGetLastError();
 }
 

@@ -75,7 +75,6 @@ enum : int {
     C_NMAX = 1,
     C_NSAD = 2,
     C_PASSES = 6,  // per-vertex label passes (untiled grids)
-    C_MORE = 16,   // untiled grids: labels left over by the first per-vertex pass
     C_OPEN = 17,   // labels left over by the last label kernel (an internal error)
     C_SLOTS = 64,
 };
