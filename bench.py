@@ -75,7 +75,7 @@ def parse():
 
 # sources that define each profiled kernel (or the whole path): a counter
 # summary stays valid only while these files are unchanged
-KERNEL_SOURCES = {"k_classify": ("eg_classify_tiled.hip", "eg_internal.h", "eg_rows.h")}
+KERNEL_SOURCES = {"k_classify": ("eg_classify_tiled.hip", "eg_tile.h", "eg_sample.h", "eg_internal.h", "eg_rows.h")}
 
 
 def path_sources():

@@ -59,8 +59,8 @@ typedef enum eg_status {
     EG_ERR_CAPACITY = 5,  /* device header: an output capacity was too small; counts are the required sizes */
     EG_ERR_HIP = 6,       /* host: a HIP launch failed */
     EG_ERR_SCRATCH = 7,   /* host: eg_build_noalloc: the field needs more than its fixed scratch */
-    EG_ERR_UNRESOLVED = 8 /* device header: a label was still a code after the last label pass
-                             (an internal error: the pass count covers every path; outputs undefined) */
+    EG_ERR_UNRESOLVED = 8 /* device header: a label was still a code after the last label kernel
+                             (an internal error: its sweeps cover every path; outputs undefined) */
 } eg_status;
 
 /* eg_out.flags */
@@ -74,7 +74,7 @@ typedef enum eg_status {
 #define EG_H_NSAD 2   /* number of saddles (required size of saddles[], saddle_beta[]) */
 #define EG_H_NARC 3   /* number of arcs (required size of arc_maxima[]); -1 if unknown */
 #define EG_H_NPAIRS 4 /* number of (saddle, upper-link component) pairs, the sum of beta; -1 if unknown */
-#define EG_H_PASSES 5 /* per-vertex label passes that ran */
+#define EG_H_PASSES 5 /* most label sweeps any vertex of an untiled grid took (diagnostic) */
 #define EG_H_EXITS 6  /* tile exit-list entries the labels used (diagnostic) */
 #define EG_H_SLOTS 8
 
@@ -117,7 +117,7 @@ typedef struct eg_out {
  * bit-identical results.
  *   EG_TUNE_TILE3(v)  3D tile: 0 = 64x8x8, 1 = 64x4x16, 2 = 64x8x4
  *   EG_TUNE_TILE2(v)  2D tile: 0 = 64x32, 1 = 64x16
- *   EG_TUNE_HOPS(h)   links followed per label pass: 0 = 64; 16, 32, 64 or 128
+ *   EG_TUNE_HOPS(h)   links followed per label sweep: 0 = 64; 16, 32, 64 or 128
  *   EG_TUNE_EXITS(e)  most exit-list entries: 0 = the default capacity, e = 1..30
  *                     caps it at 2^e (a test hook for the path that tiles whose
  *                     exits do not fit take: labels by vertex codes instead)
@@ -383,7 +383,8 @@ eg_status eg_build_batched(const void* host_plan, void* stream);
  * through the simulated-perturbation order (Sec. 3.3: u below v iff f[u] <
  * f[v] compared in the sample type, or equal and u < v), so a field of any
  * type is first turned into a float32 field with exactly the same order, its
- * order surrogate, and eg_build then runs unchanged on that:
+ * order surrogate, and eg_build then runs unchanged on that (a 3D field can also
+ * be built without one, by eg_build_typed below):
  *
  *   EG_F32                  a copy
  *   EG_I8, EG_U8, EG_I16,   the value converted to float32 (exact, ties kept)

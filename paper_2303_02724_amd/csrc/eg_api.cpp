@@ -71,13 +71,13 @@ eg_status check_one(const float* field, int ndim, const int64_t* dims, const eg_
 }
 
 // Stage (a) + (c): pointers, maxima and saddle candidates (resets counters).
-hipError_t stage_classify(const float* field, const Grid& g, const LinkTable& t, const eg_out& o, const Work& w,
-                          const Tuning& tu, hipStream_t s)
+hipError_t stage_classify(const float* field, const Grid& g, const eg_out& o, const Work& w, const Tuning& tu,
+                          hipStream_t s)
 {
     const bool minima = (o.flags & EG_MINIMA) != 0;
     hipError_t e = launch_init(g, w, o.header, s);
     if (e != hipSuccess) return e;
-    return launch_classify(field, g, t, minima, o.labels, o.ptr, w, tu, s);
+    return launch_classify(field, g, minima, o.labels, o.ptr, w, tu, s);
 }
 
 // Stage (b): labels by pointer jumping, in place.
@@ -131,13 +131,11 @@ eg_status run_stages(int stages, const float* field, int ndim, const int64_t* di
     Work w;
     const eg_status st = check_one(field, ndim, dims, out, &g, &w);
     if (st != EG_OK) return st;
-    LinkTable t;
-    make_table(g, &t);
     Tuning tu;
     decode_tuning(out->tuning, &tu);
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipSuccess;
-    if (stages & S_CLASSIFY) e = stage_classify(field, g, t, *out, w, tu, s);
+    if (stages & S_CLASSIFY) e = stage_classify(field, g, *out, w, tu, s);
     if (e == hipSuccess && (stages & S_LABEL)) e = stage_label(g, *out, w, tu, s);
     if (e == hipSuccess && (stages & S_ARCS)) e = stage_arcs(field, g, *out, w, s);
     return e == hipSuccess ? EG_OK : EG_ERR_HIP;

@@ -42,7 +42,7 @@ hipError_t launch_init(const Grid& g, const Work& w, int32_t* header, hipStream_
     return hipGetLastError();
 }
 
-// Visit the closed neighbourhood of v in the order in which later vertices
+// Visit the closed neighbourhood of v (1D) in the order in which later vertices
 // win ties; fills the upper-link mask and the steepest-ascent target.  The
 // rows are unrolled, one load per row under the row's own branch; a row's
 // linear offset and the boundary bits that rule it out follow from the
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(256) void k_keys(const float* __restrict__ f, int N
 }
 
 template <int NDIM, bool MINMODE>
-__global__ __launch_bounds__(256) void k_classify_generic(const uint32_t* __restrict__ keys, Grid g, LinkTable t,
+__global__ __launch_bounds__(256) void k_classify_generic(const uint32_t* __restrict__ keys, Grid g,
                                                           int32_t* __restrict__ lab, int32_t* __restrict__ ptr,
                                                           uint64_t* __restrict__ mmask, uint64_t* __restrict__ smask)
 {
@@ -481,8 +481,8 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
 }
 
 template <int NDIM, bool MINMODE>
-static void launch_classify_t(const float* f, const Grid& g, const LinkTable& t, int32_t* lab, int32_t* ptr,
-                              const Work& w, hipStream_t s)
+static void launch_classify_t(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, const Work& w,
+                              hipStream_t s)
 {
     const int64_t kwant = ((int64_t)g.N + 255) / 256;
     const int kblocks = (int)(kwant < 8192 ? kwant : 8192);
@@ -507,26 +507,24 @@ static void launch_classify_t(const float* f, const Grid& g, const LinkTable& t,
                            a, lab, ptr, w.mmask, w.smask);
     } else {
         const int blocks = (int)((g.N + 255) / 256);
-        hipLaunchKernelGGL((k_classify_generic<NDIM, MINMODE>), dim3(blocks), dim3(256), 0, s, w.keys, g, t, lab,
-                           ptr, w.mmask, w.smask);
+        hipLaunchKernelGGL((k_classify_generic<NDIM, MINMODE>), dim3(blocks), dim3(256), 0, s, w.keys, g, lab, ptr,
+                           w.mmask, w.smask);
     }
 }
 
-hipError_t launch_classify(const float* f, const Grid& g, const LinkTable& t, bool minima, int32_t* lab,
-                           int32_t* ptr, const Work& w, const Tuning& tu, hipStream_t s)
+hipError_t launch_classify(const float* f, const Grid& g, bool minima, int32_t* lab, int32_t* ptr, const Work& w,
+                           const Tuning& tu, hipStream_t s)
 {
     if (g.ndim == 2 || g.ndim == 3) return launch_classify_tiled(f, g, minima, lab, ptr, w, tu, s);
-#define EG_CASE(N)                                                \
-    case N:                                                       \
-        if (minima)                                               \
-            launch_classify_t<N, true>(f, g, t, lab, ptr, w, s);  \
-        else                                                      \
-            launch_classify_t<N, false>(f, g, t, lab, ptr, w, s); \
+#define EG_CASE(N)                                             \
+    case N:                                                    \
+        if (minima)                                            \
+            launch_classify_t<N, true>(f, g, lab, ptr, w, s);  \
+        else                                                   \
+            launch_classify_t<N, false>(f, g, lab, ptr, w, s); \
         break;
     switch (g.ndim) {
         EG_CASE(1)
-        EG_CASE(2)
-        EG_CASE(3)
         EG_CASE(4)
         EG_CASE(5)
         EG_CASE(6)

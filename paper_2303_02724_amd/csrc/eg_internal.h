@@ -79,14 +79,6 @@ enum : int {
     C_SLOTS = 64,
 };
 
-// Neighbour table for one grid, passed by value as a kernel argument (the
-// rows' mutual adjacency is a compile-time table, eg_rows.h).
-struct LinkTable {
-    int32_t k;                 // number of rows, 2(2^n - 1)
-    int32_t lin[kMaxNb];       // linear index offset of row j
-    uint32_t forb[kMaxNb];     // boundary bits that rule row j out (see boundary_bits)
-};
-
 struct Grid {
     int32_t ndim;
     int32_t N;
@@ -215,21 +207,11 @@ struct BatchPlan {
 // Host: table rows for ndim (Alg. 1), independent of dims.  Returns k.  The
 // adjacency of row j is adj[j * W .. j * W + W), W = (k + 63) / 64 words.
 int make_rows(int ndim, int8_t (*off)[EG_MAX_NDIM], uint64_t* adj);
-// Host: full kernel table for a grid.
-void make_table(const Grid& g, LinkTable* t);
 // Host: carve (or size, when base == nullptr) the workspace of a grid with N
 // vertices.
 Work carve(void* base, int ndim, int64_t N, int64_t X, int64_t cap_sad, int64_t exit_cap = 0);
 // Exit-list capacity for a grid of N vertices (label codes need N + cap < 2^31).
 int64_t exit_capacity(int64_t N);
-// Bits needed to hold any vertex id of a grid with N vertices.
-inline int id_bits(int64_t N)
-{
-    int b = 1;
-    while ((int64_t(1) << b) < N) ++b;
-    return b;
-}
-
 // ------------------------------------------------------------------ device
 
 // Keys lie in [1, 0xFFFFFFFE] in both modes (non-NaN values map into
@@ -394,8 +376,8 @@ __device__ __forceinline__ void exit_first(const ExitPart& p, const uint32_t* ex
 
 // Counters and header to zero; the two masks too on 1D grids.
 hipError_t launch_init(const Grid& g, const Work& w, int32_t* header, hipStream_t s);
-hipError_t launch_classify(const float* f, const Grid& g, const LinkTable& t, bool minima, int32_t* lab,
-                           int32_t* ptr, const Work& w, const Tuning& tu, hipStream_t s);
+hipError_t launch_classify(const float* f, const Grid& g, bool minima, int32_t* lab, int32_t* ptr, const Work& w,
+                           const Tuning& tu, hipStream_t s);
 // Classification of the 2D/3D tiles [first, first + count) (tiles in C order:
 // tile rows along axis 0 are contiguous ranges); count < 0: every tile.
 hipError_t launch_classify_tiled(const float* f, const Grid& g, bool minima, int32_t* lab, int32_t* ptr,

@@ -113,71 +113,12 @@ constexpr Conn3 make_conn3()
 }
 
 #if defined(__HIPCC__)
-// Row adjacency in constant memory, one table per dimension, for the kernels
-// that test link connectivity by a bit-parallel search (the 2D/3D tiles use
-// precomputed connectivity bits instead).  Internal linkage: every source file
-// that uses a table holds its own copy.
-template <int NDIM>
-struct AdjTable {
-    Mask<NDIM> adj[Rows<NDIM>::K];
-};
-template <int NDIM>
-constexpr AdjTable<NDIM> make_adj()
-{
-    constexpr Rows<NDIM> r = make_rows_ce<NDIM>();
-    AdjTable<NDIM> t{};
-    for (int j = 0; j < Rows<NDIM>::K; ++j) t.adj[j] = r.adj[j];
-    return t;
-}
-namespace {
-__constant__ AdjTable<1> c_adj1 = make_adj<1>();
-__constant__ AdjTable<2> c_adj2 = make_adj<2>();
-__constant__ AdjTable<3> c_adj3 = make_adj<3>();
-__constant__ AdjTable<4> c_adj4 = make_adj<4>();
-__constant__ AdjTable<5> c_adj5 = make_adj<5>();
-__constant__ AdjTable<6> c_adj6 = make_adj<6>();
-}  // namespace
-
-template <int NDIM>
-__device__ __forceinline__ const Mask<NDIM>* adj_table()
-{
-    if constexpr (NDIM == 1) return c_adj1.adj;
-    else if constexpr (NDIM == 2) return c_adj2.adj;
-    else if constexpr (NDIM == 3) return c_adj3.adj;
-    else if constexpr (NDIM == 4) return c_adj4.adj;
-    else if constexpr (NDIM == 5) return c_adj5.adj;
-    else return c_adj6.adj;
-}
-
 // Index of the lowest set bit of a non-empty mask.
 __device__ __forceinline__ int lowest_bit(uint64_t m) { return __ffsll((unsigned long long)m) - 1; }
 __device__ __forceinline__ int lowest_bit(unsigned __int128 m)
 {
     const uint64_t lo = (uint64_t)m;
     return lo ? __ffsll((unsigned long long)lo) - 1 : 64 + __ffsll((unsigned long long)(uint64_t)(m >> 64)) - 1;
-}
-
-// Index of the highest set bit of a non-empty mask.
-__device__ __forceinline__ int highest_bit(uint64_t m) { return 63 - __clzll((long long)m); }
-__device__ __forceinline__ int highest_bit(unsigned __int128 m)
-{
-    const uint64_t hi = (uint64_t)(m >> 64);
-    return hi ? 127 - __clzll((long long)hi) : 63 - __clzll((long long)(uint64_t)m);
-}
-
-// Component of `seed` inside `mask` (BFS over link edges, bit-parallel).
-template <class M>
-__device__ __forceinline__ M closure(M seed, M mask, const M* adj)
-{
-    M comp = seed, frontier = seed;
-    while (frontier != 0) {
-        const int j = lowest_bit(frontier);
-        frontier &= frontier - 1;
-        const M nb = adj[j] & mask & ~comp;
-        comp |= nb;
-        frontier |= nb;
-    }
-    return comp;
 }
 #endif
 

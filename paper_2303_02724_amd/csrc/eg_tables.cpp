@@ -38,31 +38,6 @@ int make_rows(int ndim, int8_t (*off)[EG_MAX_NDIM], uint64_t* adj)
     }
 }
 
-void make_table(const Grid& g, LinkTable* t)
-{
-    int8_t off[kMaxNb][EG_MAX_NDIM];
-    std::memset(t, 0, sizeof(*t));
-    const int k = make_rows(g.ndim, off, nullptr);
-    int64_t stride[EG_MAX_NDIM];
-    int64_t s = 1;
-    for (int i = g.ndim - 1; i >= 0; --i) {
-        stride[i] = s;
-        s *= g.dims[i];
-    }
-    t->k = k;
-    for (int j = 0; j < k; ++j) {
-        int64_t lin = 0;
-        uint32_t forb = 0;
-        for (int i = 0; i < g.ndim; ++i) {
-            lin += off[j][i] * stride[i];
-            if (off[j][i] < 0) forb |= 1u << (2 * i);
-            if (off[j][i] > 0) forb |= 1u << (2 * i + 1);
-        }
-        t->lin[j] = (int32_t)lin;
-        t->forb[j] = forb;
-    }
-}
-
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 bool decode_tuning(uint32_t t, Tuning* out)

@@ -1,0 +1,49 @@
+"""GPU parity at the edges of the slab tiles, the exit list's regions and the
+untiled label passes: last axes around the slab tiles' rows of 8 and the
+64-vertex mask word, grids of enough tiles for eight regions with room for all,
+some or none of their exits, and paths longer than the first label pass
+follows, around the entries a workgroup holds."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2303_02724_amd import workloads as W
+from tests.gpu_util import KEYS, assert_same, gpu_graph
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("lead", [(3, 5, 9), (5, 2, 3, 5), (2, 3, 2, 3, 5)], ids=["4d", "5d", "6d"])
+@pytest.mark.parametrize("x", [1, 7, 8, 9, 15, 63, 64, 65])
+def test_slab_rows_of_eight(lead, x):
+    f = W.random_field((*lead, x), 60 + x, "uniform")
+    f[..., ::3] = np.round(f[..., ::3] * 4) / 4  # ties too
+    for minima in (False, True):
+        ctx = f"shape={f.shape} minima={minima}"
+        print(ctx, flush=True)
+        g = gpu_graph(f, minima, cap_max=f.size, cap_sad=f.size, cap_arc=8 * f.size)
+        assert_same(g, O.extremum_graph(f, minima), KEYS + ["ptr"], ctx)
+
+
+@pytest.mark.parametrize("shape", [(1030, 1027), (65, 66, 515)], ids=["2d", "3d"])
+@pytest.mark.parametrize("exits_log2", [None, 1, 6, 12, 16])
+def test_eight_exit_regions(shape, exits_log2):
+    from paper_2303_02724_amd import eg
+    f = W.gaussian_random_field(shape, 7, corr_len=6.0, workers=4)
+    tuning = 0 if exits_log2 is None else eg.tuning(exits_log2=exits_log2)
+    for minima in (False, True):
+        ctx = f"shape={shape} exits<=2^{exits_log2} minima={minima}"
+        print(ctx, flush=True)
+        assert_same(gpu_graph(f, minima, tuning=tuning), O.extremum_graph(f, minima), KEYS + ["ptr"], ctx)
+
+
+@pytest.mark.parametrize("shape", [(4,), (5,), (6,), (1023,), (70001,), (2, 2, 2, 1500), (1500, 2, 2, 3),
+                                   (700, 1, 1, 1, 3), (1, 1, 1, 1, 2, 900)], ids=lambda s: "x".join(map(str, s)))
+def test_long_untiled_paths(shape):
+    i = np.arange(int(np.prod(shape)), dtype=np.float32)
+    peaks = np.abs(i - 0.4 * i.size)  # one slope down and one up: a maximum at either end
+    for f in (i.reshape(shape), peaks.astype(np.float32).reshape(shape)):
+        for minima in (False, True):
+            ctx = f"shape={shape} minima={minima}"
+            print(ctx, flush=True)
+            assert_same(gpu_graph(f, minima), O.extremum_graph(f, minima), KEYS + ["ptr"], ctx)
