@@ -129,9 +129,10 @@ hipError_t launch_final_tiled_batched(const BatchPlan* dplan, const BatchPlan& h
 
 // The tiles [first, first + count): every tile of the grid, or the tile rows
 // of one slab of a streamed build.  Five waves per SIMD, as many as the LDS of
-// the default tile allows: only the variant for ragged tiles that writes
-// pointers needs more than the 96 registers that this leaves, and spills (the
-// classification at 512^3 is 6 % slower with its 105 registers and four waves).
+// the default tile allows, leave 96 registers; its variants spill up to nine
+// (full tiles about two, by the bytes that they write beyond their outputs),
+// which costs less than the wave does (512^3: 6 % slower with 105 registers
+// and four waves).
 template <bool MINMODE, int TY, int TZ, bool PTR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_classify3d(TileArgs a, int first,
                                                                                             int count)
