@@ -30,8 +30,8 @@ namespace eg {
 // takes a list capped by the tuning word or a grid near 2^31 vertices) follow
 // their path to its end, one link per tile on it; a path has fewer than N
 // links, which bounds the walk whatever the label array holds.
-template <int TY, int TZ>
-__device__ __forceinline__ void final_tile(const TileArgs& a, int b, const int32_t* __restrict__ res, uint32_t* flag)
+template <int TY, int TZ, bool WHOLE>
+__device__ __forceinline__ void final_rows(const TileArgs& a, int b, const int32_t* __restrict__ res, uint32_t* flag)
 {
     constexpr int YPT = TY / 4;
     const int X = a.X, Y = a.Y, Z = a.Z;
@@ -49,15 +49,13 @@ __device__ __forceinline__ void final_tile(const TileArgs& a, int b, const int32
     bool notdone = false;
     int vid[VPT], x[VPT];
     // every load of the thread first, then the exit-list look-ups, then the
-    // stores: loads and stores of the same array would otherwise serialise;
-    // the codes and labels stream through once, so both bypass the caches'
-    // normal retention (the exit list stays cached for the look-ups)
+    // stores: loads and stores of the same array would otherwise serialise
 #pragma unroll
     for (int k = 0; k < VPT; ++k) {
         const int gy = ty * TY + wv + 4 * (k / TZ), gz = tz * TZ + (k % TZ);
         const bool in = gx < X && gy < Y && gz < Z;
         vid[k] = in ? gz * SZ + gy * SY + gx : -1;
-        x[k] = in ? __builtin_nontemporal_load(&lab[vid[k]]) : 0;
+        x[k] = in ? (WHOLE ? __builtin_nontemporal_load(&lab[vid[k]]) : lab[vid[k]]) : 0;
     }
 #pragma unroll
     for (int k = 0; k < VPT; ++k)
@@ -73,8 +71,28 @@ __device__ __forceinline__ void final_tile(const TileArgs& a, int b, const int32
     }
 #pragma unroll
     for (int k = 0; k < VPT; ++k)
-        if (vid[k] >= 0) __builtin_nontemporal_store(x[k], &lab[vid[k]]);
+        if (vid[k] >= 0) {
+            if (WHOLE)
+                __builtin_nontemporal_store(x[k], &lab[vid[k]]);
+            else
+                lab[vid[k]] = x[k];
+        }
     if (__ballot(notdone) != 0 && __lane_id() == 0) atomicOr(flag, 1u);
+}
+
+// Rows of whole 128-byte lines stream past the caches' normal retention (codes
+// and labels are used once; 512^3 210 -> 206 us).  Other rows share their first
+// and last lines, and their waves' accesses straddle lines, whose halves should
+// meet in the cache rather than go to memory by themselves: 256 fields of any
+// sizes in a batch 536 -> 345 us (3D) and 339 -> 219 (2D); whole builds of
+// 301 x 384 x 449 float64 samples 607 -> 575 us, of 201 x 190 x 333 258 -> 245.
+template <int TY, int TZ>
+__device__ __forceinline__ void final_tile(const TileArgs& a, int b, const int32_t* __restrict__ res, uint32_t* flag)
+{
+    if ((a.X & 31) == 0)
+        final_rows<TY, TZ, true>(a, b, res, flag);
+    else
+        final_rows<TY, TZ, false>(a, b, res, flag);
 }
 
 template <int TY, int TZ>
