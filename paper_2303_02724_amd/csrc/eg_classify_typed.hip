@@ -7,7 +7,7 @@
 // leave the order open and classifies those again on the samples.  Ranking the
 // whole field into a float32 order surrogate first (eg_order_field, which the
 // other dimensions and batches still take) sorts it: 5.8 of 6.6 ms of a build
-// of 301 x 384 x 449 smooth float64 samples, which now takes 0.61 ms.  The
+// of 301 x 384 x 449 smooth float64 samples, which now takes 0.57 ms.  The
 // exact tiles matter where the sort had few passes: 256^3 equal float64
 // samples 0.32 ms ranked, 0.57 with every vertex looked at again, 0.20 as it
 // is; small int64 plateaus 0.48, 0.65 and 0.29.
