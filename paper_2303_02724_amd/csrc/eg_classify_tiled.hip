@@ -186,7 +186,7 @@ TileArgs tile_args(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, co
     a.tiles_y = (a.Y + ty - 1) / ty;
     const int tiles_z = (a.Z + tz - 1) / tz;
     a.ntiles = a.tiles_x * a.tiles_y * tiles_z;
-    a.regions = exit_regions(a.ntiles);
+    a.regions = exit_regions(g);
     a.cap_region = region_capacity(w.cap_exit, a.regions);
     return a;
 }

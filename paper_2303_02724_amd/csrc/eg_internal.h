@@ -35,7 +35,10 @@ constexpr int kArcBlocks = 4096;    // most blocks per field of the stage (d) ke
 // everything else the classification gained.  And the kernels that resolve a
 // region run on its XCD, whose tiles are neighbours, so their gathers meet in
 // one L2.  Below kRegionTiles tiles an uneven split could fill one region, so
-// there is only one.
+// there is only one.  The tiles counted are those of the default shape: the
+// list's layout follows from the grid alone, so that stages which run with
+// other tiles (a tuning word changed between them, the fixed tile of the typed
+// classification) agree on it.
 constexpr int kRegions = 8;
 constexpr int kRegionTiles = 512;
 constexpr int kRegionStride = 32;  // counters lie 128 bytes apart
@@ -386,8 +389,15 @@ hipError_t launch_classify_tiled(const float* f, const Grid& g, bool minima, int
 // The same for a 3D field of another sample type (the default tile).
 hipError_t launch_classify_typed(int dtype, const void* f, const Grid& g, bool minima, int32_t* lab, int32_t* ptr,
                                  const Work& w, hipStream_t s);
-// Regions of the exit list of a grid of ntiles tiles, and entries per region.
-inline uint32_t exit_regions(int64_t ntiles) { return ntiles >= kRegionTiles ? kRegions : 1; }
+// Regions of the exit list of a 2D or 3D grid, and entries per region.
+inline uint32_t exit_regions(const Grid& g)
+{
+    const int64_t tx = (g.dims[g.ndim - 1] + int64_t(63)) / 64;
+    const int64_t rows = g.ndim == 3 ? (g.dims[1] + int64_t(kTile3Y - 1)) / kTile3Y *
+                                           ((g.dims[0] + int64_t(kTile3Z - 1)) / kTile3Z)
+                                     : (g.dims[0] + int64_t(kTile2Y - 1)) / kTile2Y;
+    return tx * rows >= kRegionTiles ? kRegions : 1;
+}
 inline uint32_t region_capacity(int64_t cap, uint32_t regions)
 {
     return regions == 1 ? (uint32_t)cap : (uint32_t)(cap / regions) & ~3u;

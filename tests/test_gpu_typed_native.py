@@ -83,3 +83,30 @@ def test_typed_entry_refuses_what_it_does_not_read():
     for dtype in (eg.DTYPES[torch.float64], -1, 10):
         st = eg.lib().eg_build_typed(dtype, ctypes.c_void_p(t.data_ptr()), 2, b._dims, None, ctypes.byref(b.out))
         assert st == eg.EG_ERR_ARG
+
+
+# default tiles on one side of 512 (eight exit regions), the named tile's on
+# the other: 256 and 512 (64x8x4), 392 and 784, 600 and 300 (64x4x16)
+@pytest.mark.parametrize("dt", ["float64", "uint8", "float32"])
+@pytest.mark.parametrize("shape,tile3", [((64, 128, 128), 2), ((112, 112, 128), 2), ((1200, 4, 256), 1),
+                                         ((128, 128, 128), 2)], ids=["256-512", "392-784", "600-300", "512-1024"])
+def test_tiles_of_the_tuning_word_and_exit_regions(shape, tile3, dt):
+    rng = np.random.Generator(np.random.PCG64(17))  # noise: half of a tile's faces are exits
+    f = rng.integers(0, 256, size=shape).astype(dt) if dt == "uint8" else rng.standard_normal(shape).astype(dt)
+    t = torch.from_numpy(f).to("cuda:0")
+    n = f.size
+    caps = {"cap_max": n, "cap_sad": n, "cap_arc": 4 * n}
+    for minima in (False, True):
+        want = O.extremum_graph(f, minima)
+        for tile in (tile3, 0):
+            ctx = f"dtype={dt} shape={shape} tile3={tile} minima={minima}"
+            print(ctx, flush=True)
+            b = eg.Builder(shape, minima=minima, want_ptr=True, tuning=eg.tuning(tile3=tile), **caps)
+            assert_same(_np(b, b.run(t)), want, KEYS + ["ptr"], ctx)
+        # stage by stage, the tile changed in between
+        print(f"{ctx} tile changed between stages", flush=True)
+        b.launch(t, stage="classify")
+        b.out.tuning = eg.tuning(tile3=tile3)
+        b.launch(t, stage="label")
+        b.launch(t, stage="arcs")
+        assert_same(_np(b, b.finish()), want, KEYS + ["ptr"], f"{ctx} tile changed between stages")
