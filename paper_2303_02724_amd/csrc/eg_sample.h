@@ -126,6 +126,18 @@ __device__ __forceinline__ uint64_t exact_of(uint64_t x) { return x; }
 __device__ __forceinline__ uint64_t exact_of(int32_t x) { return (uint32_t)x ^ 0x80000000u; }
 __device__ __forceinline__ uint64_t exact_of(uint32_t x) { return x; }
 
+// The zero of a tile's distance keys (x - base, in [1, kKeyTop - 1]) for a tile
+// whose first sample is `first`: 2^31 below it, so that samples on either side
+// of it are in reach, but kept inside the range of 64 bits.  No distance in
+// reach then wraps: from 2^64 - 1 (one below 0) every x but the largest keeps
+// its order as x + 1, and 2^64 - 1 itself becomes 0, out of reach; from at most
+// 2^64 - kKeyTop, an x below the base is at least kKeyTop away.
+__host__ __device__ constexpr uint64_t near_base(uint64_t first)
+{
+    constexpr uint64_t half = uint64_t(1) << 31, top = uint64_t(0) - kKeyTop;
+    return first < half ? ~uint64_t(0) : first - half < top ? first - half : top;
+}
+
 // Whether samples with this sample's tile_key are all equal to it (a
 // sufficient test for the integers).
 __device__ __forceinline__ bool key_is_exact(double x) { return (double)(float)x == x; }

@@ -492,9 +492,10 @@ __device__ __forceinline__ constexpr uint32_t succ_pack(int dz, int dy, int dx)
 // row), then the two edge columns of every row; all loads first.  Positions
 // outside the grid get the key 0.  `nan`: a sample is a NaN; returns whether
 // equal keys of this tile mean equal samples.  For the wide types that holds
-// where the exact keys lie within 2^31 of the tile's first vertex's (then
-// their distances are the keys), or where every sample is a float32 (or short
-// of the clamped ends, for 32-bit integers); uses s_flag[0..3].
+// where the exact keys lie within about 2^31 of the tile's first vertex's
+// (then their distances from near_base are the keys), or where every sample is
+// a float32 (or short of the clamped ends, for 32-bit integers); uses
+// s_flag[0..3].
 template <class T, bool MINMODE, int TY, int TZ, bool FULL>
 __device__ __forceinline__ bool stage_samples(const TileArgs& a, int x0, int y0, int z0, uint32_t* s_u,
                                               uint32_t* s_flag, bool& nan)
@@ -535,7 +536,7 @@ __device__ __forceinline__ bool stage_samples(const TileArgs& a, int x0, int y0,
         if (tid < EDGES) *edge = ein ? tile_key<MINMODE>(eval) : 0u;
         return true;
     } else {
-        const uint64_t base = exact_of(f[(int64_t)(z0 * Y + y0) * X + x0]) - (uint64_t(1) << 31);
+        const uint64_t base = near_base(exact_of(f[(int64_t)(z0 * Y + y0) * X + x0]));
         uint32_t near[RPW];
         bool far = false, round = false;
         auto look = [&](T x, bool in) {

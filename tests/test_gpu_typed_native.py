@@ -110,3 +110,23 @@ def test_tiles_of_the_tuning_word_and_exit_regions(shape, tile3, dt):
         b.launch(t, stage="label")
         b.launch(t, stage="arcs")
         assert_same(_np(b, b.finish()), want, KEYS + ["ptr"], f"{ctx} tile changed between stages")
+
+
+@pytest.mark.parametrize("dt", ["int64", "uint64", "int32", "uint32"])
+def test_tiles_of_the_two_limits_alone(dt):
+    """Nothing between the ends of the type in any tile, either end first."""
+    lo, hi = int(np.iinfo(dt).min), int(np.iinfo(dt).max)
+    rng = np.random.Generator(np.random.PCG64(23))
+    for vals in ((lo, hi), (lo, lo + 1, hi - 1, hi), (lo, lo + 2 ** 20, hi)):
+        vals = np.array(vals, dtype=dt)
+        for shape in ((5, 6, 7), (9, 17, 130)):
+            for first in (0, -1):
+                f = vals[rng.integers(0, vals.size, size=shape)]
+                f[::8, ::8, ::64] = vals[first]  # the first sample of every tile
+                n = f.size
+                for minima in (False, True):
+                    ctx = f"dtype={dt} {len(vals)} values, {vals[first]} first, shape={shape} minima={minima}"
+                    print(ctx, flush=True)
+                    b = eg.Builder(shape, minima=minima, want_ptr=True, cap_max=n, cap_sad=n, cap_arc=6 * n)
+                    assert_same(_np(b, b.run(torch.from_numpy(f).to("cuda:0"))), O.extremum_graph(f, minima),
+                                KEYS + ["ptr"], ctx)
