@@ -141,9 +141,9 @@ __host__ __device__ constexpr uint64_t near_base(uint64_t first)
 // Whether samples with this sample's tile_key are all equal to it (a
 // sufficient test for the integers).
 __device__ __forceinline__ bool key_is_exact(double x) { return (double)(float)x == x; }
-__device__ __forceinline__ bool key_is_exact(int64_t x)
+__host__ __device__ constexpr bool key_is_exact(int64_t x)
 {
-    return (uint64_t)(x + (int64_t(1) << 24)) <= (uint64_t(1) << 25);
+    return (uint64_t)x + (uint64_t(1) << 24) <= (uint64_t(1) << 25);
 }
 __device__ __forceinline__ bool key_is_exact(uint64_t x) { return x <= (uint64_t(1) << 24); }
 __device__ __forceinline__ bool key_is_exact(uint32_t x) { return x - 2u <= kKeyTop - 4u; }

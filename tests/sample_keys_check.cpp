@@ -9,6 +9,11 @@
 
 #include "eg_sample.h"
 
+// constant expressions: an overflow in them would not compile
+static_assert(eg::key_is_exact(int64_t(1) << 24) && eg::key_is_exact(-(int64_t(1) << 24)), "the last exact ones");
+static_assert(!eg::key_is_exact((int64_t(1) << 24) + 1) && !eg::key_is_exact(-(int64_t(1) << 24) - 1), "one further");
+static_assert(!eg::key_is_exact(INT64_MAX) && !eg::key_is_exact(INT64_MIN), "both ends");
+
 int main()
 {
     // values around the ends, the middle and the steps of 2^31 and kKeyTop
