@@ -165,7 +165,10 @@ def _fetch(t: torch.Tensor) -> list:
     n = t.numel()
     buf = getattr(_host, "buf", None)
     if buf is None or buf.numel() < n:
-        buf = _host.buf = torch.empty(max(64, n), dtype=torch.int32, pin_memory=True)
+        # it outlives the torch modes of the call that makes it: an inference
+        # tensor could not be written later, nor a default device's be pinned
+        with torch.inference_mode(False):
+            buf = _host.buf = torch.empty(max(64, n), dtype=torch.int32, device="cpu", pin_memory=True)
     buf[:n].copy_(t, non_blocking=True)
     torch.cuda.current_stream(t.device).synchronize()
     return buf[:n].tolist()
