@@ -488,12 +488,16 @@ class Builder:
         if getattr(self, "pcaps", None) is None or self.p_pair.numel() < self.caps["cap_sad"] + 1:
             npairs = max(0, self.header_values()[H_NPAIRS])
             self._alloc_paths(max(1, npairs), max(64, 32 * npairs))
-        for _ in range(max_retries + 1):
+        tries = 0
+        while tries <= max_retries:
             self.launch_paths(field)
             both = _fetch(torch.cat((self.header, self.p_header)))
             h, ph = both[:H_SLOTS], both[H_SLOTS:]
             if ph[P_STATUS] == EG_ERR_CAPACITY and h[H_NSAD] <= self.caps["cap_sad"]:
-                self._alloc_paths(max(self.pcaps[0], ph[P_PATHS]), max(self.pcaps[1], ph[P_VERTICES]))
+                # growing to the pairs that the build has counted (the buffers
+                # are those of a smaller graph) is no retry
+                tries += self.pcaps[0] >= h[H_NPAIRS]
+                self._alloc_paths(max(self.pcaps[0], h[H_NPAIRS], ph[P_PATHS]), max(self.pcaps[1], ph[P_VERTICES]))
                 continue
             if ph[P_STATUS] != EG_OK:
                 raise EGError(ph[P_STATUS], f"paths header={ph}")

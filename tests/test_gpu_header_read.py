@@ -45,3 +45,19 @@ def test_first_read_under_a_torch_mode(first):
         assert b.paths(t).pair_offsets.numel() == len(want["saddles"]) + 1
 
     _in_new_thread(calls)
+
+
+def test_paths_of_a_larger_graph_without_retries():
+    """Path buffers sized for an earlier field grow to the pairs that the build
+    has counted, which is no retry."""
+    small = W.gaussian_mixture((60, 70), 5, n_gauss=2)
+    large = W.random_field((60, 70), 6, "uniform")
+    b = eg.Builder(small.shape, want_ptr=True, cap_max=small.size, cap_sad=small.size, cap_arc=4 * small.size)
+    for f in (small, large):
+        t = torch.from_numpy(f).cuda()
+        b.run(t)
+        p = b.paths(t, max_retries=0)
+        want = O.extremum_graph(f)
+        for a, w in zip((p.pair_offsets, p.path_offsets, p.vertices), O.paths(f, want["ptr"], want["saddles"])):
+            assert (a.cpu().numpy() == w).all()
+    assert p.path_offsets.numel() > 64
