@@ -255,6 +255,7 @@ struct Groups {
 };
 
 struct SlabArgs {
+    int32_t first;               // number of the launch's first block
     int32_t zc;                  // planes along axis 0 per block
     int32_t zblocks;             // blocks along axis 0: ceil(dims[0] / zc)
     int32_t nt[EG_MAX_NDIM];     // tiles along axes 1..n-1
@@ -301,7 +302,7 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
         s_corner[below][grp] = (below + 1 + GR::offset(grp, 0, 0)) % 3 * S + d;
     }
 
-    int rest = blockIdx.x;
+    int rest = a.first + (int)blockIdx.x;
     const int zb = rest % a.zblocks;
     rest /= a.zblocks;
     int t0[NDIM];  // first coordinate of the tile along axes 1..n-1
@@ -480,6 +481,8 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
     }
 }
 
+constexpr int64_t kSlabBlocks = int64_t(1) << 23;  // most blocks of one launch
+
 template <int NDIM, bool MINMODE>
 static void launch_classify_t(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, const Work& w,
                               hipStream_t s)
@@ -502,9 +505,16 @@ static void launch_classify_t(const float* f, const Grid& g, int32_t* lab, int32
         a.zc = (int)zc;
         a.zblocks = (int)((D0 + zc - 1) / zc);
         a.rows_per_plane = a.st[0] / g.dims[NDIM - 1];
-        const int64_t blocks = tiles * a.zblocks;
-        hipLaunchKernelGGL((k_classify_slab<NDIM, MINMODE>), dim3((unsigned)blocks), dim3(256), 0, s, w.keys, g,
-                           a, lab, ptr, w.mmask, w.smask);
+        const int64_t blocks = tiles * a.zblocks;  // fewer than 2^31: every tile holds a vertex
+        // a launch holds fewer than 2^32 threads; where the axes between the
+        // first and the last are short, most of a tile's threads have no
+        // vertex (X vertices in a row along the last axis: 32 X threads in 4D)
+        for (int64_t done = 0; done < blocks; done += kSlabBlocks) {
+            a.first = (int)done;
+            const int64_t n = std::min<int64_t>(blocks - done, kSlabBlocks);
+            hipLaunchKernelGGL((k_classify_slab<NDIM, MINMODE>), dim3((unsigned)n), dim3(256), 0, s, w.keys, g, a, lab,
+                               ptr, w.mmask, w.smask);
+        }
     } else {
         const int blocks = (int)((g.N + 255) / 256);
         hipLaunchKernelGGL((k_classify_generic<NDIM, MINMODE>), dim3(blocks), dim3(256), 0, s, w.keys, g, lab, ptr,

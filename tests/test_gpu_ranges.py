@@ -47,3 +47,24 @@ def test_long_untiled_paths(shape):
             ctx = f"shape={shape} minima={minima}"
             print(ctx, flush=True)
             assert_same(gpu_graph(f, minima), O.extremum_graph(f, minima), KEYS + ["ptr"], ctx)
+
+
+def test_slab_of_more_threads_than_a_launch_holds():
+    """A 4D grid of one long row takes 32 threads per vertex: more blocks than
+    one launch, the last of them ragged.  The same row as a 1D grid, whose
+    kernels hold one thread per vertex, has the same graph."""
+    import torch
+    from paper_2303_02724_amd import eg
+    n = 2 ** 27 + 37
+    f = torch.arange(n, device="cuda:0", dtype=torch.int32).remainder_(1000).sub_(500).abs_().to(torch.float32)
+    f[-20:] += 3
+    want = None
+    for shape in ((n,), (1, 1, 1, n)):
+        print(shape, flush=True)
+        r = eg.build(f.view(shape), want_ptr=True, cap_max=1 << 18, cap_sad=1 << 18, cap_arc=1 << 20)
+        got = [r.labels.view(-1), r.ptr.view(-1), r.maxima, r.saddles, r.saddle_beta, r.arc_offsets, r.arc_maxima]
+        if want is None:
+            want = got
+            assert r.maxima.numel() > n // 1000
+        else:
+            assert all(torch.equal(a, b) for a, b in zip(got, want))
