@@ -559,12 +559,35 @@ hipError_t launch_classify(const float* f, const Grid& g, bool minima, int32_t* 
 // ever stored says something true about the same path, so any value read is
 // usable.  A sweep follows at most `hops` links per entry and stores how far
 // it came; a wave with an entry left over sweeps again, now through links that
-// the other waves have advanced too (all waves at once: each sweep multiplies
-// the reach), so no launch has to follow for paths longer than one sweep.  No
-// wave waits for another: one that ran alone would still walk its paths to
-// their ends, at least `hops` links a sweep, which bounds its sweeps
+// the other waves have advanced too (each sweep multiplies the reach as long as
+// all waves keep pace), so no launch has to follow for paths longer than one
+// sweep.  No wave waits for another: one that ran alone would still walk its
+// paths to their ends, at least `hops` links a sweep, which bounds its sweeps
 // (sweeps_for).  Later sweeps read the links at device scope: a plain load
 // could return the same old line of a cache every time.
+//
+// A path through the entries of waves that do not keep pace is walked there
+// link by link.  With eight waves a SIMD the hardware serves the oldest first,
+// and the youngest, whose entries lay side by side, made two sweeps while the
+// others made 150: 57.6 ms for the labels of a 1D slope of 2^24 vertices, 24.7 in
+// 4D (2 x 2 x 2 x 2^20), 13.9 for 2 x 2 x 2^25.  So where paths can be that long
+// there are four waves a SIMD, which advance together, and their quads are dealt
+// out in the bit-reversed order of the waves' numbers (spread), so that the
+// entries of older waves lie next to those of any that lag.  They now take 3.0,
+// 1.3 and 1.5 ms, in five sweeps (3.2, 1.3 and 1.9 with a launch for every sweep;
+// at 2^23 vertices in 1D 1.8 against 1.6); the waves' number alone 4.0 ms in 1D,
+// the order alone 3.6.  Storing at device scope too made no difference.
+
+constexpr int kEvenBlocks = 1024;  // four waves a SIMD
+
+// Blocks over n entries, four a thread, whose waves' quads are spread: a power
+// of two and a multiple of the XCDs (and of the exit list's regions).
+static int even_blocks(int64_t n)
+{
+    int blocks = 8;
+    while (blocks < kEvenBlocks && blocks * int64_t(1024) < n) blocks *= 2;
+    return blocks;
+}
 
 // The exit list's base and its regions are 16-byte aligned (the workspace is
 // carved in 256-byte steps, regions hold a multiple of four entries).
@@ -573,9 +596,10 @@ __global__ __launch_bounds__(256) void k_exit_init(TileArgs a, int32_t* __restri
     exit_first(exit_part(a.claims, a.cap_region, a.regions, blockIdx.x, gridDim.x), a.exits, res, a.lab);
 }
 
-__global__ __launch_bounds__(256) void k_exit_jump(TileArgs a, int32_t* res, int N, int hops, int sweeps)
+__global__ __launch_bounds__(256) void k_exit_jump(TileArgs a, int32_t* res, int N, int hops, int sweeps, bool even)
 {
-    const ExitPart p = exit_part(a.claims, a.cap_region, a.regions, blockIdx.x, gridDim.x);
+    ExitPart p = exit_part(a.claims, a.cap_region, a.regions, blockIdx.x, gridDim.x);
+    if (even) p.t = spread(p.t >> 6, p.stride >> 6) * 64u + (threadIdx.x & 63u);
     const int32_t* lab = a.lab;
     int32_t* part = res + p.at;
     bool open = sweep(part, p.n, lab, res, N, hops, p.t, p.stride, false);
@@ -595,8 +619,9 @@ __device__ __forceinline__ LabelRun label_run(int32_t* lab, int32_t N)
 {
     // runs of whole quads; the last run ends with the vertices left over
     const uint32_t x = blockIdx.x & 7u, q = (uint32_t)N >> 5, lo = 4u * q * x;
-    return LabelRun{lab + lo, x == 7u ? (uint32_t)N - lo : 4u * q, (blockIdx.x >> 3) * blockDim.x + threadIdx.x,
-                    (gridDim.x >> 3) * blockDim.x};
+    // waves of the run (four a block), and this one's number
+    const uint32_t n = gridDim.x >> 1, w = (blockIdx.x >> 3) * 4u + (threadIdx.x >> 6);
+    return LabelRun{lab + lo, x == 7u ? (uint32_t)N - lo : 4u * q, spread(w, n) * 64u + (threadIdx.x & 63u), n * 64u};
 }
 
 // The first pass follows four links, so that no wave waits for the longest of
@@ -648,15 +673,19 @@ hipError_t launch_labels(const Grid& g, int32_t* lab, const Work& w, const Tunin
         // the jump reads entries that other threads have already advanced,
         // which shortens long chains: it needs every entry initialised first
         hipLaunchKernelGGL(k_exit_init, dim3(eblocks), dim3(256), 0, s, a, w.exres);
-        hipLaunchKernelGGL(k_exit_jump, dim3(eblocks), dim3(256), 0, s, a, w.exres, N, tu.hops, sweeps);
+        // paths through thousands of tiles need an axis as long (or a field
+        // made for it); elsewhere eight waves a SIMD in order are 2 to 3 us
+        // faster (labels of 201 x 190 x 333 noise 46 and 49 us, 512^3 393 and 396)
+        constexpr int kLongAxis = 1024;  // tiles
+        const int axis = std::max({a.tiles_x, a.tiles_y, a.ntiles / (a.tiles_x * a.tiles_y)});
+        const bool even = axis >= kLongAxis;
+        hipLaunchKernelGGL(k_exit_jump, dim3(even ? even_blocks(w.cap_exit) : eblocks), dim3(256), 0, s, a, w.exres, N,
+                           tu.hops, sweeps, even);
         return launch_final_tiled(g, lab, w, tu, s);
     }
-    const int64_t want = ((int64_t)N / 4 + 255) / 256;
-    const int blocks = (int)(want < 2048 ? (want / 8 + 1) * 8 : 2048);  // a multiple of the XCDs
+    const int blocks = even_blocks(N);
     uint32_t* flags = w.bsum + kSumRow;  // free until stage (d)
     hipLaunchKernelGGL(k_final, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, flags);
-    // every block of this launch fits the GPU at once, so that all entries
-    // advance together
     hipLaunchKernelGGL(k_final_rest, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, flags, tu.hops, sweeps);
     return hipGetLastError();
 }

@@ -343,6 +343,9 @@ __device__ __forceinline__ bool sweep(int32_t* a, uint32_t n, const int32_t* lab
     return open;
 }
 
+// Number i of n (a power of two) with its bits reversed.
+__device__ __forceinline__ uint32_t spread(uint32_t i, uint32_t n) { return (__brev(i) >> 1) >> __clz(n); }
+
 // The region of the exit list that a workgroup works on, the workgroup's
 // first quad in it and the quads between its rounds (nb workgroups, a multiple
 // of the regions, blk one of them).

@@ -68,3 +68,35 @@ def test_slab_of_more_threads_than_a_launch_holds():
             assert r.maxima.numel() > n // 1000
         else:
             assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("shape", [(2 ** 22 + 5,), (2, 2, 2, 2 ** 19 + 1)], ids=["1d", "4d"])
+def test_long_slopes_take_few_sweeps(shape):
+    """Every vertex on one slope, more of them than the label kernels hold at
+    once: the sweeps multiply the reach, they do not walk (150 sweeps where the
+    youngest waves held one end of every run)."""
+    import torch
+    from paper_2303_02724_amd import eg
+    n = int(np.prod(shape))
+    f = torch.arange(n, device="cuda:0", dtype=torch.float32).view(shape)
+    r = eg.build(f)
+    assert torch.all(r.labels == n - 1)
+    assert r.passes <= 30, r.passes
+
+
+@pytest.mark.parametrize("shape", [(3, 65537), (3, 70001), (32769, 5), (2, 3, 66001), (8200, 3, 9)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("exits_log2", [None, 9])
+def test_exit_lists_of_long_axes(shape, exits_log2):
+    """1024 tiles along an axis and more: the exits' sweeps are dealt out another
+    way than on other grids."""
+    from paper_2303_02724_amd import eg
+    tuning = 0 if exits_log2 is None else eg.tuning(exits_log2=exits_log2)
+    slope = np.arange(int(np.prod(shape)), dtype=np.float32).reshape(shape)
+    slope = slope if max(shape) == shape[-1] else np.ascontiguousarray(slope[::-1])
+    for f in (slope, W.gaussian_mixture(shape, 8, n_gauss=6, noise=1e-2)):
+        for minima in (False, True):
+            ctx = f"shape={shape} exits<=2^{exits_log2} minima={minima}"
+            print(ctx, flush=True)
+            g = gpu_graph(f, minima, tuning=tuning, cap_max=f.size, cap_sad=f.size, cap_arc=4 * f.size)
+            assert_same(g, O.extremum_graph(f, minima), KEYS + ["ptr"], ctx)
