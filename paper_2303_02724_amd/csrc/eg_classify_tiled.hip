@@ -152,20 +152,19 @@ hipError_t launch_final_tiled_batched(const BatchPlan* dplan, const BatchPlan& h
 // which costs less than the wave does (512^3: 6 % slower with 105 registers
 // and four waves).
 template <bool MINMODE, int TY, int TZ, bool PTR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_classify3d(TileArgs a, int first,
-                                                                                            int count)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_classify3d(TileArgs a, int count)
 {
     __shared__ __align__(8) Tile3Lds<TY, TZ> s;
-    tile3d<MINMODE, TY, TZ, PTR, SRC_F32>(a, first + xcd_run(blockIdx.x, count), s);
+    tile3d<MINMODE, TY, TZ, PTR, SRC_F32>(a, (int)a.first + xcd_run(blockIdx.x, count), s);
 }
 
 template <bool MINMODE, int TY>
-__global__ __launch_bounds__(256) void k_classify2d(TileArgs a, int first, int count)
+__global__ __launch_bounds__(256) void k_classify2d(TileArgs a, int count)
 {
     __shared__ uint32_t s_u[66 * (TY + 2)];
     __shared__ int32_t s_nxt[64 * TY];
     __shared__ uint32_t s_tmp[8];
-    tile_nd<2, MINMODE, TY, 1>(a, first + xcd_run(blockIdx.x, count), s_u, s_nxt, nullptr, s_tmp);
+    tile_nd<2, MINMODE, TY, 1>(a, (int)a.first + xcd_run(blockIdx.x, count), s_u, s_nxt, nullptr, s_tmp);
 }
 
 TileArgs tile_args(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, const Work& w, int ty, int tz)
@@ -261,29 +260,29 @@ hipError_t launch_classify_batched(const BatchPlan* dplan, const BatchPlan& hpla
 }
 
 template <int TY, int TZ>
-static void launch_3d(const TileArgs& a, bool minima, int first, int count, hipStream_t s)
+static void launch_3d(const TileArgs& a, bool minima, int count, hipStream_t s)
 {
     const dim3 g(count), b(256);
     if (minima) {
         if (a.ptr)
-            hipLaunchKernelGGL((k_classify3d<true, TY, TZ, true>), g, b, 0, s, a, first, count);
+            hipLaunchKernelGGL((k_classify3d<true, TY, TZ, true>), g, b, 0, s, a, count);
         else
-            hipLaunchKernelGGL((k_classify3d<true, TY, TZ, false>), g, b, 0, s, a, first, count);
+            hipLaunchKernelGGL((k_classify3d<true, TY, TZ, false>), g, b, 0, s, a, count);
     } else {
         if (a.ptr)
-            hipLaunchKernelGGL((k_classify3d<false, TY, TZ, true>), g, b, 0, s, a, first, count);
+            hipLaunchKernelGGL((k_classify3d<false, TY, TZ, true>), g, b, 0, s, a, count);
         else
-            hipLaunchKernelGGL((k_classify3d<false, TY, TZ, false>), g, b, 0, s, a, first, count);
+            hipLaunchKernelGGL((k_classify3d<false, TY, TZ, false>), g, b, 0, s, a, count);
     }
 }
 
 template <int TY>
-static void launch_2d(const TileArgs& a, bool minima, int first, int count, hipStream_t s)
+static void launch_2d(const TileArgs& a, bool minima, int count, hipStream_t s)
 {
     if (minima)
-        hipLaunchKernelGGL((k_classify2d<true, TY>), dim3(count), dim3(256), 0, s, a, first, count);
+        hipLaunchKernelGGL((k_classify2d<true, TY>), dim3(count), dim3(256), 0, s, a, count);
     else
-        hipLaunchKernelGGL((k_classify2d<false, TY>), dim3(count), dim3(256), 0, s, a, first, count);
+        hipLaunchKernelGGL((k_classify2d<false, TY>), dim3(count), dim3(256), 0, s, a, count);
 }
 
 hipError_t launch_final_tiled(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, hipStream_t s)
@@ -314,26 +313,27 @@ hipError_t launch_classify_tiled(const float* f, const Grid& g, bool minima, int
 {
     int ty, tz;
     tile_shape(tu, g.ndim, &ty, &tz);
-    const TileArgs a = tile_args(f, g, lab, ptr, w, ty, tz);
+    TileArgs a = tile_args(f, g, lab, ptr, w, ty, tz);
     if (count < 0) {
         first = 0;
         count = a.ntiles;
     }
     if (first < 0 || first + count > a.ntiles) return hipErrorInvalidValue;
     if (count == 0) return hipSuccess;
-    const int f0 = (int)first, n = (int)count;
+    a.first = (uint32_t)first;
+    const int n = (int)count;
     if (g.ndim == 3) {
         if (tu.tile3 == 1)
-            launch_3d<4, 16>(a, minima, f0, n, s);
+            launch_3d<4, 16>(a, minima, n, s);
         else if (tu.tile3 == 2)
-            launch_3d<8, 4>(a, minima, f0, n, s);
+            launch_3d<8, 4>(a, minima, n, s);
         else
-            launch_3d<8, 8>(a, minima, f0, n, s);
+            launch_3d<8, 8>(a, minima, n, s);
     } else if (g.ndim == 2) {
         if (tu.tile2 == 1)
-            launch_2d<16>(a, minima, f0, n, s);
+            launch_2d<16>(a, minima, n, s);
         else
-            launch_2d<32>(a, minima, f0, n, s);
+            launch_2d<32>(a, minima, n, s);
     } else {
         return hipErrorInvalidValue;
     }

@@ -30,7 +30,8 @@ constexpr int kSumRow = 8192;  // entries per row of the stage (d) block sums
 constexpr int kArcBlocks = 4096;    // most blocks per field of the stage (d) kernels
 // The exit list of a grid of many tiles is split into regions, one for each of
 // the eight XCDs (workgroups are dispatched to them round-robin).  A tile
-// claims its block with an atomic on its region's counter: one counter for all
+// claims its block with an atomic on its region's counter (in turn, over all
+// launches of a grid, so that the regions fill evenly): one counter for all
 // serialised the tiles' claims at 12.5 ns each, 410 us at 512^3, which hid
 // everything else the classification gained.  And the kernels that resolve a
 // region run on its XCD, whose tiles are neighbours, so their gathers meet in
@@ -140,7 +141,8 @@ struct TileArgs {
     int32_t X, Y, Z, tiles_x, tiles_y, ntiles;
     uint32_t cap_region;       // entries per region
     uint32_t regions;          // 1 or kRegions
-    uint32_t dtype, pad0;      // dtype: the samples behind f (eg_dtype)
+    uint32_t dtype;            // the samples behind f (eg_dtype)
+    uint32_t first;            // workgroups of the grid before this launch's (the slabs of a streamed build)
 };
 
 // Everything stage (d) needs to know about its field.

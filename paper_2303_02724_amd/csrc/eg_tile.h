@@ -388,7 +388,7 @@ __device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u,
     if (__ballot(nan) != 0 && __lane_id() == 0) atomicOr(&ctr[C_NAN], 1u);
     const int N = X * Y * Z;
     uint32_t claim;
-    const uint32_t region = blockIdx.x & (a.regions - 1u);
+    const uint32_t region = (a.first + blockIdx.x) & (a.regions - 1u);
     uint32_t* counter = a.claims + kRegionStride * region;
     const uint32_t nexit = rank_exits<VPT>(nxt, s_tmp, s_u, counter, claim);  // the halo is no longer read
     auto s_idx = [&](int k) { return ((k / YPT) * TY + wv + 4 * (k % YPT)) * TX + lx; };
@@ -977,7 +977,7 @@ __device__ __forceinline__ void tile3d_body(const TileArgs& a, int b, uint32_t* 
     if (__ballot(nan) != 0 && __lane_id() == 0) atomicOr(&ctr[C_NAN], 1u);
     // exit targets go behind the chains, in LDS the halo no longer needs
     uint32_t claim;
-    const uint32_t region = blockIdx.x & (a.regions - 1u);
+    const uint32_t region = (a.first + blockIdx.x) & (a.regions - 1u);
     uint32_t* counter = a.claims + kRegionStride * region;
     const uint32_t nexit = rank_exits<VPT>(nxt, s_tmp, s_u + TILE, counter, claim);
 #pragma unroll

@@ -65,3 +65,24 @@ def test_streamed_rejects_bad_arguments():
     b5 = eg.Builder((4, 4, 4, 4))
     with pytest.raises(eg.EGError):
         b5.launch_streamed(_pinned(np.zeros((4, 4, 4, 4), np.float32)), 2)  # 4D is not streamed
+
+
+def _region_claims(b, n, words):
+    """Exit-list entries claimed in each of the eight regions: the counters lie
+    128 bytes apart behind the 4096 block sums that follow the workspace's
+    counters and its two masks."""
+    at = b.out.workspace - b.ws.data_ptr() + 256 + 2 * ((8 * words + 255) // 256 * 256) + 4 * 4096
+    return [int(b.ws[at + 128 * r:at + 128 * r + 4].view(torch.int32)) for r in range(8)]
+
+
+def test_streamed_slabs_of_one_tile_fill_every_exit_region():
+    """A narrow volume streamed a tile row at a time, whose exits would fill one
+    region twice over: every slab's one workgroup takes the next region."""
+    shape = (4096, 8, 64)
+    f = np.arange(np.prod(shape), dtype=np.float32).reshape(shape)
+    b = eg.Builder(shape)
+    r = b.run_streamed(_pinned(f), 8)
+    assert torch.all(r.labels == f.size - 1)
+    claims = _region_claims(b, f.size, shape[0] * shape[1])
+    assert sum(claims) == r.counts["exits"] > f.size // 16
+    assert max(claims) <= f.size // 16, claims
