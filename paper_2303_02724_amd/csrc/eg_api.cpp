@@ -279,6 +279,7 @@ eg_status eg_batch_plan(int count, const float* const* fields, const int* ndims,
         tile_shape(P->tuning, g.ndim, &ty, &tz);
         BatchField& B = F[k];
         B.ta = tile_args(fields[i], g, o.labels, o.ptr, w, ty, tz);
+        if (exits_capped(w, g.N)) P->capped = 1;
         B.arc = arc_args(fields[i], g, o, w);
         B.ndim = g.ndim;
         B.minima = (o.flags & EG_MINIMA) ? 1 : 0;

@@ -8,6 +8,7 @@
 namespace eg {
 
 constexpr int kBatchBlocksPerField = 48;  // a multiple of the exit list's regions
+constexpr int kBatchRestBlocks = 64;      // a power of two
 
 __global__ __launch_bounds__(256) void k_binit(const BatchPlan* __restrict__ plan)
 {
@@ -36,14 +37,24 @@ __global__ __launch_bounds__(256) void k_bexit_jump(const BatchPlan* __restrict_
     const BatchField F = plan->fields[blockIdx.y];  // a copy: loop loads cannot alias it
     const ExitPart p = exit_part(F.ta.claims, F.ta.cap_region, F.ta.regions, blockIdx.x, gridDim.x);
     const int hops = plan->tuning.hops;
-    const int sweeps = sweeps_for(plan->tuning, F.N);
+    const bool capped = plan->capped != 0;
+    const int sweeps = capped ? min(sweeps_for(plan->tuning, F.N), kCappedSweeps) : sweeps_for(plan->tuning, F.N);
     const int32_t* lab = F.ta.lab;
     int32_t* res = F.exres;
     int32_t* part = res + p.at;
     bool open = sweep(part, p.n, lab, res, F.N, hops, p.t, p.stride, false);
     for (int k = 1; __ballot(open) != 0 && k < sweeps; ++k)
         open = sweep(part, p.n, lab, res, F.N, hops, p.t, p.stride, true);
-    if (__ballot(open) != 0 && __lane_id() == 0) atomicOr(&plan->bctr[C_OPEN], 1u);
+    if (__ballot(open) != 0 && __lane_id() == 0) atomicOr(&plan->bctr[capped ? C_CODES : C_OPEN], 1u);
+}
+
+// What the tile-ordered pass left open where lists are capped.
+__global__ __launch_bounds__(256) void k_bcodes_rest(const BatchPlan* __restrict__ plan)
+{
+    if (plan->bctr[C_CODES] == 0) return;
+    const BatchField F = plan->fields[blockIdx.y];
+    codes_rest(F.ta.lab, F.exres, F.N, plan->tuning.hops, sweeps_for(plan->tuning, F.N), blockIdx.x, gridDim.x,
+               F.ta.ctr, &plan->bctr[C_OPEN]);
 }
 
 hipError_t launch_batched_init(const BatchPlan* dplan, const BatchPlan& hplan, hipStream_t s)
@@ -59,6 +70,10 @@ hipError_t launch_batched_rest(const BatchPlan* dplan, const BatchPlan& hplan, h
     hipLaunchKernelGGL(k_bexit_jump, grid, dim3(256), 0, s, dplan);
     const hipError_t e = launch_final_tiled_batched(dplan, hplan, s);
     if (e != hipSuccess) return e;
+    if (hplan.capped) {
+        const dim3 rest(kBatchRestBlocks, hplan.count);
+        hipLaunchKernelGGL(k_bcodes_rest, rest, dim3(256), 0, s, dplan);
+    }
     return launch_arcs_batched(dplan, hplan, s);
 }
 

@@ -596,7 +596,9 @@ __global__ __launch_bounds__(256) void k_exit_init(TileArgs a, int32_t* __restri
     exit_first(exit_part(a.claims, a.cap_region, a.regions, blockIdx.x, gridDim.x), a.exits, res, a.lab);
 }
 
-__global__ __launch_bounds__(256) void k_exit_jump(TileArgs a, int32_t* res, int N, int hops, int sweeps, bool even)
+// Entries left over after `sweeps` sweeps raise ctr[flag_slot].
+__global__ __launch_bounds__(256) void k_exit_jump(TileArgs a, int32_t* res, int N, int hops, int sweeps, bool even,
+                                                   int flag_slot)
 {
     ExitPart p = exit_part(a.claims, a.cap_region, a.regions, blockIdx.x, gridDim.x);
     if (even) p.t = spread(p.t >> 6, p.stride >> 6) * 64u + (threadIdx.x & 63u);
@@ -605,7 +607,19 @@ __global__ __launch_bounds__(256) void k_exit_jump(TileArgs a, int32_t* res, int
     bool open = sweep(part, p.n, lab, res, N, hops, p.t, p.stride, false);
     for (int k = 1; __ballot(open) != 0 && k < sweeps; ++k)
         open = sweep(part, p.n, lab, res, N, hops, p.t, p.stride, true);
-    if (__ballot(open) != 0 && __lane_id() == 0) atomicOr(&a.ctr[C_OPEN], 1u);
+    if (__ballot(open) != 0 && __lane_id() == 0) atomicOr(&a.ctr[flag_slot], 1u);
+}
+
+// Capped exit lists: labels that the tile-ordered pass left open, by sweeps over
+// all of them (labels of a 2 x 2^20 slope with a list of two entries 0.47 ms; 1.95
+// when every vertex walked to the end of its path).  A short list may itself
+// lead through tiles whose codes only these sweeps advance, so its own stop
+// early (kCappedSweeps) and leave such entries as they are.
+__global__ __launch_bounds__(256) void k_codes_rest(int32_t* lab, const int32_t* res, int32_t N,
+                                                    uint32_t* __restrict__ ctr, int hops, int sweeps)
+{
+    if (ctr[C_CODES] == 0) return;
+    codes_rest(lab, res, N, hops, sweeps, blockIdx.x, gridDim.x, ctr, &ctr[C_OPEN]);
 }
 
 // Per-vertex labels of the grids without tiles: every code names a vertex.
@@ -679,9 +693,14 @@ hipError_t launch_labels(const Grid& g, int32_t* lab, const Work& w, const Tunin
         constexpr int kLongAxis = 1024;  // tiles
         const int axis = std::max({a.tiles_x, a.tiles_y, a.ntiles / (a.tiles_x * a.tiles_y)});
         const bool even = axis >= kLongAxis;
+        const bool capped = exits_capped(w, N);
+        const int slot = capped ? C_CODES : C_OPEN;
         hipLaunchKernelGGL(k_exit_jump, dim3(even ? even_blocks(w.cap_exit) : eblocks), dim3(256), 0, s, a, w.exres, N,
-                           tu.hops, sweeps, even);
-        return launch_final_tiled(g, lab, w, tu, s);
+                           tu.hops, capped ? std::min(sweeps, kCappedSweeps) : sweeps, even, slot);
+        const hipError_t e = launch_final_tiled(g, lab, w, tu, capped ? tu.hops : N, slot, s);
+        if (e != hipSuccess || !capped) return e;
+        hipLaunchKernelGGL(k_codes_rest, dim3(even_blocks(N)), dim3(256), 0, s, lab, w.exres, N, w.ctr, tu.hops, sweeps);
+        return hipGetLastError();
     }
     const int blocks = even_blocks(N);
     uint32_t* flags = w.bsum + kSumRow;  // free until stage (d)

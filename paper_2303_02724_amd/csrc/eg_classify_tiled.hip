@@ -26,12 +26,13 @@ namespace eg {
 // Label pass over a tiled grid, one workgroup per tile: the exit codes of a
 // tile's vertices point into that tile's own block of the exit list, which
 // stays in cache while the tile's rows stream through.  Every list entry is
-// final by now.  Vertex codes (a tile whose exits did not fit the list, which
-// takes a list capped by the tuning word or a grid near 2^31 vertices) follow
-// their path to its end, one link per tile on it; a path has fewer than N
-// links, which bounds the walk whatever the label array holds.
+// final by now.  Vertex codes (a tile whose exits did not fit its region of the
+// list) follow their path, one link per tile on it: to its end where the list
+// as a whole has room (few tiles overflow their region then; a path has fewer
+// than N links, which bounds the walk whatever the label array holds), `hops`
+// links where it is capped, and the sweeps of k_codes_rest do what is left.
 template <int TY, int TZ, bool WHOLE>
-__device__ __forceinline__ void final_rows(const TileArgs& a, int b, const int32_t* __restrict__ res, uint32_t* flag)
+__device__ __forceinline__ void final_rows(const TileArgs& a, int b, const int32_t* __restrict__ res, int hops, uint32_t* flag)
 {
     constexpr int YPT = TY / 4;
     const int X = a.X, Y = a.Y, Z = a.Z;
@@ -64,7 +65,7 @@ __device__ __forceinline__ void final_rows(const TileArgs& a, int b, const int32
     for (int k = 0; k < VPT; ++k) {
         if (x[k] < 0) {
             int y = x[k];
-            for (int h = 0; y < 0 && h < N; ++h) y = y >= -N ? lab[-y - 1] : res[-y - 1 - N];
+            for (int h = 0; y < 0 && h < hops; ++h) y = y >= -N ? lab[-y - 1] : res[-y - 1 - N];
             x[k] = y;
             notdone |= y < 0;
         }
@@ -87,18 +88,19 @@ __device__ __forceinline__ void final_rows(const TileArgs& a, int b, const int32
 // sizes in a batch 536 -> 345 us (3D) and 339 -> 219 (2D); whole builds of
 // 301 x 384 x 449 float64 samples 607 -> 575 us, of 201 x 190 x 333 258 -> 245.
 template <int TY, int TZ>
-__device__ __forceinline__ void final_tile(const TileArgs& a, int b, const int32_t* __restrict__ res, uint32_t* flag)
+__device__ __forceinline__ void final_tile(const TileArgs& a, int b, const int32_t* __restrict__ res, int hops, uint32_t* flag)
 {
     if ((a.X & 31) == 0)
-        final_rows<TY, TZ, true>(a, b, res, flag);
+        final_rows<TY, TZ, true>(a, b, res, hops, flag);
     else
-        final_rows<TY, TZ, false>(a, b, res, flag);
+        final_rows<TY, TZ, false>(a, b, res, hops, flag);
 }
 
 template <int TY, int TZ>
-__global__ __launch_bounds__(256) void k_final_tiled(TileArgs a, const int32_t* __restrict__ res)
+__global__ __launch_bounds__(256) void k_final_tiled(TileArgs a, const int32_t* __restrict__ res, int hops,
+                                                         int flag_slot)
 {
-    final_tile<TY, TZ>(a, xcd_run(blockIdx.x, a.ntiles), res, &a.ctr[C_OPEN]);
+    final_tile<TY, TZ>(a, xcd_run(blockIdx.x, a.ntiles), res, hops, &a.ctr[flag_slot]);
 }
 
 // The same pass over the tiles of every 2D (or every 3D) field of a batch:
@@ -120,7 +122,9 @@ __global__ __launch_bounds__(256) void k_final_tiled_batched(const BatchPlan* __
     }
     const int f = __builtin_amdgcn_readfirstlane(lo);
     const TileArgs a = fs[f].ta;
-    final_tile<TY, TZ>(a, (int)(item - fs[f].tile_base), fs[f].exres, &plan->bctr[C_OPEN]);
+    const bool capped = plan->capped != 0;
+    final_tile<TY, TZ>(a, (int)(item - fs[f].tile_base), fs[f].exres, capped ? plan->tuning.hops : fs[f].N,
+                       &plan->bctr[capped ? C_CODES : C_OPEN]);
 }
 
 hipError_t launch_final_tiled_batched(const BatchPlan* dplan, const BatchPlan& hplan, hipStream_t s)
@@ -285,23 +289,24 @@ static void launch_2d(const TileArgs& a, bool minima, int count, hipStream_t s)
         hipLaunchKernelGGL((k_classify2d<false, TY>), dim3(count), dim3(256), 0, s, a, count);
 }
 
-hipError_t launch_final_tiled(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, hipStream_t s)
+hipError_t launch_final_tiled(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, int hops, int flag_slot,
+                              hipStream_t s)
 {
     int ty, tz;
     tile_shape(tu, g.ndim, &ty, &tz);
     const TileArgs a = tile_args(nullptr, g, lab, nullptr, w, ty, tz);
     if (g.ndim == 3) {
         if (tu.tile3 == 1)
-            hipLaunchKernelGGL((k_final_tiled<4, 16>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres);
+            hipLaunchKernelGGL((k_final_tiled<4, 16>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres, hops, flag_slot);
         else if (tu.tile3 == 2)
-            hipLaunchKernelGGL((k_final_tiled<8, 4>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres);
+            hipLaunchKernelGGL((k_final_tiled<8, 4>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres, hops, flag_slot);
         else
-            hipLaunchKernelGGL((k_final_tiled<8, 8>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres);
+            hipLaunchKernelGGL((k_final_tiled<8, 8>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres, hops, flag_slot);
     } else if (g.ndim == 2) {
         if (tu.tile2 == 1)
-            hipLaunchKernelGGL((k_final_tiled<16, 1>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres);
+            hipLaunchKernelGGL((k_final_tiled<16, 1>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres, hops, flag_slot);
         else
-            hipLaunchKernelGGL((k_final_tiled<32, 1>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres);
+            hipLaunchKernelGGL((k_final_tiled<32, 1>), dim3(a.ntiles), dim3(256), 0, s, a, w.exres, hops, flag_slot);
     } else {
         return hipErrorInvalidValue;
     }

@@ -26,6 +26,7 @@ namespace eg {
 
 constexpr int kMaxNb = 126;         // 2(2^6 - 1)
 constexpr int kJumpHops = 64;       // default links per pointer-jumping pass
+constexpr int kCappedSweeps = 4;    // most sweeps over a capped exit list
 constexpr int kSumRow = 8192;  // entries per row of the stage (d) block sums
 constexpr int kArcBlocks = 4096;    // most blocks per field of the stage (d) kernels
 // The exit list of a grid of many tiles is split into regions, one for each of
@@ -78,7 +79,8 @@ enum : int {
     C_NAN = 0,
     C_NMAX = 1,
     C_NSAD = 2,
-    C_PASSES = 6,  // per-vertex label passes (untiled grids)
+    C_PASSES = 6,  // sweeps over the labels of untiled grids and of capped exit lists
+    C_CODES = 16,  // capped exit lists: the tile-ordered pass left labels open
     C_OPEN = 17,   // labels left over by the last label kernel (an internal error)
     C_SLOTS = 64,
 };
@@ -201,7 +203,7 @@ struct BatchPlan {
     // owns fields [class_field[c], class_field[c + 1]) and tiles
     // [class_tile[c], class_tile[c + 1])
     int32_t class_field[5];
-    int32_t pad1;
+    int32_t capped;              // some field's exit list is capped (exits_capped)
     int64_t class_tile[5];
     EG_GPTR(uint32_t) bctr;      // [C_SLOTS] batch counters (label flags)
     EG_GPTR(BatchField) fields;  // device address of fields[] (right after this header)
@@ -217,6 +219,10 @@ int make_rows(int ndim, int8_t (*off)[EG_MAX_NDIM], uint64_t* adj);
 Work carve(void* base, int ndim, int64_t N, int64_t X, int64_t cap_sad, int64_t exit_cap = 0);
 // Exit-list capacity for a grid of N vertices (label codes need N + cap < 2^31).
 int64_t exit_capacity(int64_t N);
+// Whether the list of a grid of N vertices holds less than the entries that its
+// tiles may want: capped by the tuning word, or by the codes' room on a grid
+// near 2^31 vertices.
+inline bool exits_capped(const Work& w, int64_t N) { return w.cap_exit < (N / 2 > 4096 ? N / 2 : 4096); }
 // ------------------------------------------------------------------ device
 
 // Keys lie in [1, 0xFFFFFFFE] in both modes (non-NaN values map into
@@ -345,7 +351,8 @@ __device__ __forceinline__ bool sweep(int32_t* a, uint32_t n, const int32_t* lab
     return open;
 }
 
-// Number i of n (a power of two) with its bits reversed.
+// Number i of n (a power of two) with its bits reversed (why the sweeps are
+// dealt out in that order: eg_classify.hip).
 __device__ __forceinline__ uint32_t spread(uint32_t i, uint32_t n) { return (__brev(i) >> 1) >> __clz(n); }
 
 // The region of the exit list that a workgroup works on, the workgroup's
@@ -362,6 +369,23 @@ __device__ __forceinline__ ExitPart exit_part(const uint32_t* claims, uint32_t c
     const uint32_t step = regions == 1 ? 0 : 3;
     return ExitPart{req < cap_region ? req : cap_region, r * cap_region, (blk >> step) * 256 + threadIdx.x,
                     (nb >> step) * 256};
+}
+
+// Sweeps over all n labels until none is open, by workgroup blk of nb (a power
+// of two); counts them in ctr[C_PASSES] and raises *left if some stay open.
+__device__ __forceinline__ void codes_rest(int32_t* lab, const int32_t* res, int32_t n, int hops, int sweeps,
+                                           uint32_t blk, uint32_t nb, uint32_t* ctr, uint32_t* left)
+{
+    const uint32_t waves = 4u * nb;
+    const uint32_t t = spread(4u * blk + (threadIdx.x >> 6), waves) * 64u + (threadIdx.x & 63u);
+    bool open = true;
+    int k = 0;
+    for (; __ballot(open) != 0 && k < sweeps; ++k)
+        open = sweep(lab, (uint32_t)n, lab, res, n, hops, t, 64u * waves, k > 0);
+    const bool rest = __ballot(open) != 0;
+    if (__lane_id() != 0) return;
+    if (rest) atomicOr(left, 1u);
+    if (k > 1 || (blk == 0 && threadIdx.x == 0)) atomicMax(&ctr[C_PASSES], (uint32_t)k);
 }
 
 // First values of a part of the exit list: its vertices' label codes.
@@ -420,10 +444,12 @@ hipError_t launch_batched_rest(const BatchPlan* dplan, const BatchPlan& hplan, h
 //   x < -N            "same label as exit-list entry -x-1-N"
 __device__ __forceinline__ int exit_list_code(int N, uint32_t idx) { return -(N + 1 + (int)idx); }
 hipError_t launch_labels(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, hipStream_t s);
-// Tile-ordered per-vertex label pass (2D/3D grids); raises ctr[C_OPEN] if some
-// vertex is not final.
-hipError_t launch_final_tiled(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, hipStream_t s);
-// The tile-ordered pass over every field of a batch; raises bctr[C_OPEN].
+// Tile-ordered per-vertex label pass (2D/3D grids); raises ctr[flag_slot] if some
+// vertex is not final after `hops` links.
+hipError_t launch_final_tiled(const Grid& g, int32_t* lab, const Work& w, const Tuning& tu, int hops, int flag_slot,
+                              hipStream_t s);
+// The tile-ordered pass over every field of a batch; raises bctr[C_OPEN]
+// (bctr[C_CODES] where lists are capped).
 hipError_t launch_final_tiled_batched(const BatchPlan* dplan, const BatchPlan& hplan, hipStream_t s);
 // Stage (d) of one field: ascending maxima and saddles from the bitmasks,
 // the arcs of every saddle, the CSR and the header.

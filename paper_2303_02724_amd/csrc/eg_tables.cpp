@@ -61,7 +61,7 @@ int64_t exit_capacity(int64_t N)
     // of a tile's boundary layer (a quarter of all vertices for 64x8x8 tiles)
     // on smooth fields.  An overflowing tile falls back to vertex codes, so
     // this bounds memory, not correctness.
-    int64_t cap = std::max<int64_t>(N / 2, 4096);
+    int64_t cap = std::max<int64_t>(N / 2, 4096);  // see exits_capped
     const int64_t room = (int64_t(1) << 31) - 1 - N;
     return std::max<int64_t>(0, std::min(cap, room));
 }

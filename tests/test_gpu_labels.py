@@ -59,3 +59,18 @@ def test_batch_exit_list_overflow():
                    "saddles": r.saddles.cpu().numpy(), "saddle_beta": r.saddle_beta.cpu().numpy(),
                    "arc_offsets": r.arc_offsets.cpu().numpy(), "arc_maxima": r.arc_maxima.cpu().numpy()}
             assert_same(got, O.extremum_graph(f, minima), KEYS, f"batch exits<=8 {f.shape} minima={minima}")
+
+
+@pytest.mark.parametrize("exits_log2", [1, 12])
+def test_long_slopes_with_capped_lists_take_few_sweeps(exits_log2):
+    """A slope through 16385 tiles whose list holds next to nothing, alone and in
+    a batch: the labels are swept, not walked one link per tile."""
+    import torch
+    fs = [torch.arange(n, dtype=torch.float32, device="cuda:0").expand(2, -1).contiguous()
+          for n in (2 ** 20 + 3, 2 ** 17)]
+    tuning = eg.tuning(exits_log2=exits_log2)
+    alone = eg.build(fs[0], tuning=tuning)
+    batch = eg.BatchBuilder([f.shape for f in fs], tuning=tuning).run(fs)
+    for f, r in ((fs[0], alone), *zip(fs, batch)):
+        assert torch.all(r.labels == f.numel() - 1)
+        assert 0 < r.passes <= 30, r.passes
