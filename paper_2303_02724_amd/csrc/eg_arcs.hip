@@ -877,6 +877,11 @@ constexpr uint32_t kRecPaths = 3;
 // registers at four waves per SIMD (32^5: 2.96 ms again, 3.9 parked, 2.6).
 template <int NDIM>
 constexpr int kPathKeys = NDIM <= 4 ? KEYS_LDS : NDIM == 5 ? KEYS_REGS : KEYS_AGAIN;
+// Threads per block of the path kernels.  A chunk is whole rounds of 256
+// saddles, one round on most fields: blocks of 128 threads, as k_arc_count has
+// in 5D, walk a round's paths in two turns (noise of 12^5 87 us, of 16 x 17 x 18 x
+// 19 x 5 93, of 25 x 24 x 26 x 27 x 23 536; 56, 63 and 520 in blocks of 256).
+constexpr int kPathThreads = 256;
 constexpr uint32_t kRecSteps = 128;
 __device__ __forceinline__ uint32_t recorded_steps(const PathArgs& P, uint32_t n)
 {
@@ -891,9 +896,9 @@ __device__ __forceinline__ uint32_t recorded_steps(const PathArgs& P, uint32_t n
 // a walk met a pointer that leaves the grid or does not rise to row 3 (row 0
 // also holds the exit list's counters).
 template <int NDIM, bool MINMODE, int SRC = SRC_F32>
-__global__ __launch_bounds__(kArcThreads<NDIM>) __attribute__((amdgpu_waves_per_eu(NDIM == 5 ? 4 : 1, 8))) void k_path_count(OneField sel, PathArgs P)
+__global__ __launch_bounds__(kPathThreads) __attribute__((amdgpu_waves_per_eu(NDIM == 5 ? 4 : 1, 8))) void k_path_count(OneField sel, PathArgs P)
 {
-    constexpr int BT = kArcThreads<NDIM>;
+    constexpr int BT = kPathThreads;
     __shared__ RowLds<NDIM, kPathKeys<NDIM>, SRC> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
@@ -945,9 +950,9 @@ __global__ __launch_bounds__(kArcThreads<NDIM>) __attribute__((amdgpu_waves_per_
 }
 
 template <int NDIM, bool MINMODE, int SRC = SRC_F32>
-__global__ __launch_bounds__(kArcThreads<NDIM>) __attribute__((amdgpu_waves_per_eu(NDIM == 5 ? 4 : 1, 8))) void k_path_write(OneField sel, PathArgs P)
+__global__ __launch_bounds__(kPathThreads) __attribute__((amdgpu_waves_per_eu(NDIM == 5 ? 4 : 1, 8))) void k_path_write(OneField sel, PathArgs P)
 {
-    constexpr int BT = kArcThreads<NDIM>;
+    constexpr int BT = kPathThreads;
     __shared__ RowLds<NDIM, kPathKeys<NDIM>, SRC> T;
     __shared__ uint32_t tmp[8];
     uint32_t blk, nb;
@@ -1025,8 +1030,8 @@ __global__ __launch_bounds__(kArcThreads<NDIM>) __attribute__((amdgpu_waves_per_
 template <int NDIM, bool MINMODE, int SRC = SRC_F32>
 static void launch_paths_t(const OneField& sel, const PathArgs& p, uint32_t nb, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_path_count<NDIM, MINMODE, SRC>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel, p);
-    hipLaunchKernelGGL((k_path_write<NDIM, MINMODE, SRC>), dim3(nb), dim3(kArcThreads<NDIM>), 0, s, sel, p);
+    hipLaunchKernelGGL((k_path_count<NDIM, MINMODE, SRC>), dim3(nb), dim3(kPathThreads), 0, s, sel, p);
+    hipLaunchKernelGGL((k_path_write<NDIM, MINMODE, SRC>), dim3(nb), dim3(kPathThreads), 0, s, sel, p);
 }
 
 hipError_t launch_paths(const ArcArgs& a, const PathArgs& p, hipStream_t s)

@@ -51,3 +51,19 @@ def test_recorded_paths(kind):
         for a, b, name in zip((p.pair_offsets, p.path_offsets, p.vertices), wp,
                               ("pair_offsets", "path_offsets", "vertices")):
             assert np.array_equal(a.cpu().numpy(), b), f"{kind} minima={minima} {name}"
+
+
+@pytest.mark.parametrize("shape", [(4, 4, 4, 4, 5), (9, 9, 9, 9, 9)], ids=["one-round", "several-blocks"])
+def test_paths_of_5d_noise(shape):
+    """Blocks of the 5D path kernels hold other numbers of threads than those
+    of the 5D arc kernels."""
+    from paper_2303_02724_amd import eg
+    import torch
+    f = W.random_field(shape, 19, "uniform")
+    for minima in (False, True):
+        want = O.extremum_graph(f, minima)
+        wp = O.paths(f, want["ptr"], want["saddles"], minima)
+        _, p = eg.build_paths(torch.from_numpy(f).cuda(), minima=minima)
+        for a, b, name in zip((p.pair_offsets, p.path_offsets, p.vertices), wp,
+                              ("pair_offsets", "path_offsets", "vertices")):
+            assert np.array_equal(a.cpu().numpy(), b), f"{shape} minima={minima} {name}"
