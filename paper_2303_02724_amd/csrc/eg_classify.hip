@@ -188,38 +188,68 @@ __global__ __launch_bounds__(256) void k_classify_generic(const uint32_t* __rest
 //   atomics on the masks) against rows of 8: 41 x 64 x 60 x 65 186 and 125 us,
 //   30 x 31 x 29 x 30 x 33 1380 and 616; in 6D rows of 16 left two waves per
 //   SIMD to the LDS instead of three: 16^6 598 and 497.  Blocks of 512 threads
-//   were slower everywhere (more waves to a barrier).  It keeps three
-//   consecutive planes of the tile plus a one-vertex halo in a ring in LDS
-//   (positions outside the grid hold key 0, below every vertex, so every row
-//   of the table may be read), and slides it along axis 0: while one plane is
-//   classified, the loads of the plane after next are in flight.
-template <int NDIM>
+//   were slower everywhere (more waves to a barrier).  Where the axes between
+//   the first and the last are so short that most of such a tile lies outside
+//   the grid, the tile is wide: 2x4x32, 2x2x2x32 or 2x2x2x2x16 (classification
+//   of noise, rows of 8 and wide: 2 x 2 x 2 x 10^6 464 and 145 us, 200 x 200 x 1
+//   x 200 495 and 219, 2 x 2 x 2 x 2 x 300 000 224 and 97, 2 x 2 x 2 x 2 x 2 x
+//   100 000 227 and 168).  A block keeps three consecutive planes of the tile plus
+//   a one-vertex halo in a ring in LDS (positions outside the grid hold key 0,
+//   below every vertex, so every row of the table may be read), and slides it
+//   along axis 0: while one plane is classified, the loads of the plane after
+//   next are in flight.
+template <int NDIM, bool WIDE>
 __host__ __device__ constexpr int slab_e(int i)  // interior extent along axis i (1..n-1)
 {
+    if (WIDE) return i == NDIM - 1 ? (NDIM == 6 ? 16 : 32) : NDIM == 4 && i == 2 ? 4 : 2;
     if (i == NDIM - 1) return 8;
     if (NDIM == 4) return i == 2 ? 8 : 4;
     if (NDIM == 5) return i == 1 ? 2 : 4;
     return i == 4 ? 4 : 2;
 }
-template <int NDIM>
+template <int NDIM, bool WIDE>
 __host__ __device__ constexpr int slab_hs(int i)  // LDS stride of axis i in a halo plane
 {
     int s = 1;
-    for (int k = NDIM - 1; k > i; --k) s *= slab_e<NDIM>(k) + 2;
+    for (int k = NDIM - 1; k > i; --k) s *= slab_e<NDIM, WIDE>(k) + 2;
     return s;
 }
-template <int NDIM>
+template <int NDIM, bool WIDE>
 __host__ __device__ constexpr int slab_size()  // keys per halo plane
 {
-    return slab_hs<NDIM>(0);
+    return slab_hs<NDIM, WIDE>(0);
 }
-template <int NDIM>
+template <int NDIM, bool WIDE>
 __host__ __device__ constexpr int slab_inner()  // vertices per tile plane
 {
     int s = 1;
-    for (int k = 1; k < NDIM; ++k) s *= slab_e<NDIM>(k);
+    for (int k = 1; k < NDIM; ++k) s *= slab_e<NDIM, WIDE>(k);
     return s;
 }
+template <int NDIM, bool WIDE>
+int64_t slab_tiles(const Grid& g, int32_t* nt)
+{
+    int64_t n = 1;
+    for (int i = 1; i < NDIM; ++i) {
+        nt[i] = (g.dims[i] + slab_e<NDIM, WIDE>(i) - 1) / slab_e<NDIM, WIDE>(i);
+        n *= nt[i];
+    }
+    return n;
+}
+
+// A row of the tile is one piece of its mask word.
+template <int EX>
+struct MaskPiece {
+    using type = uint8_t;
+};
+template <>
+struct MaskPiece<16> {
+    using type = uint16_t;
+};
+template <>
+struct MaskPiece<32> {
+    using type = uint32_t;
+};
 
 // The steepest row is found by groups: the rows (and the vertex itself) that
 // share their offsets along the first axes differ by {0,1}^Q along the last Q,
@@ -228,7 +258,7 @@ __host__ __device__ constexpr int slab_inner()  // vertices per tile plane
 // the highest key is picked, and only its keys are looked at again, from LDS
 // (5D: 87 instructions where comparing all 62 rows with the maximum took 159).
 // Groups and positions are numbered in linear-index order.
-template <int NDIM>
+template <int NDIM, bool WIDE>
 struct Groups {
     static constexpr int Q = NDIM == 6 ? 3 : 2;
     static constexpr int IN = 1 << Q;            // rows per group
@@ -249,7 +279,7 @@ struct Groups {
     static constexpr int inner(int k)
     {
         int d = 0;
-        for (int i = NDIM - Q; i < NDIM; ++i) d += ((k >> (NDIM - 1 - i)) & 1) * slab_hs<NDIM>(i);
+        for (int i = NDIM - Q; i < NDIM; ++i) d += ((k >> (NDIM - 1 - i)) & 1) * slab_hs<NDIM, WIDE>(i);
         return d;
     }
 };
@@ -263,7 +293,7 @@ struct SlabArgs {
     int32_t rows_per_plane;      // rows of X vertices in one plane (st[0] / X)
 };
 
-template <int NDIM, bool MINMODE>
+template <int NDIM, bool MINMODE, bool WIDE>
 __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restrict__ keys, Grid g,
                                                        SlabArgs a, int32_t* __restrict__ lab,
                                                        int32_t* __restrict__ ptr, uint64_t* __restrict__ mmask,
@@ -271,19 +301,20 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
 {
     constexpr int K = Rows<NDIM>::K;
     constexpr Rows<NDIM> R = make_rows_ce<NDIM>();
-    constexpr int S = slab_size<NDIM>();
+    constexpr int S = slab_size<NDIM, WIDE>();
     constexpr int PER = (S + 255) / 256;
-    constexpr int EX = slab_e<NDIM>(NDIM - 1);
-    static_assert(slab_inner<NDIM>() == 256, "one interior vertex per thread");
-    static_assert(EX == 8, "a row of the tile is a byte of its mask word");
+    constexpr int EX = slab_e<NDIM, WIDE>(NDIM - 1);
+    static_assert(slab_inner<NDIM, WIDE>() == 256, "one interior vertex per thread");
+    static_assert(EX == 8 || EX == 16 || EX == 32, "a row of the tile is a piece of its mask word");
+    using Piece = typename MaskPiece<EX>::type;
     // halo index of interior position (0,..,0), the smallest a row may reach
     constexpr int B = [] {
         int b = 0;
-        for (int i = 1; i < NDIM; ++i) b += slab_hs<NDIM>(i);
+        for (int i = 1; i < NDIM; ++i) b += slab_hs<NDIM, WIDE>(i);
         return b;
     }();
     __shared__ uint32_t s_ring[3 * S];
-    using GR = Groups<NDIM>;
+    using GR = Groups<NDIM, WIDE>;
     static_assert(2 * GR::G * GR::IN <= 256 && 6 * GR::G <= 256, "the tables are filled in one step");
     __shared__ int32_t s_lin[2 * GR::G * GR::IN];  // linear offset of every position
     __shared__ int32_t s_corner[3][2 * GR::G];     // a group's corner in the ring, by the slot of plane z-1
@@ -298,7 +329,7 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
         const int below = tid / (2 * GR::G), grp = tid % (2 * GR::G);
         int d = B;
 #pragma unroll
-        for (int i = 1; i < NDIM; ++i) d += GR::offset(grp, 0, i) * slab_hs<NDIM>(i);
+        for (int i = 1; i < NDIM; ++i) d += GR::offset(grp, 0, i) * slab_hs<NDIM, WIDE>(i);
         s_corner[below][grp] = (below + 1 + GR::offset(grp, 0, 0)) % 3 * S + d;
     }
 
@@ -310,7 +341,7 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
     for (int i = NDIM - 1; i >= 1; --i) {
         const int q = rest % a.nt[i];
         rest /= a.nt[i];
-        t0[i] = q * slab_e<NDIM>(i);
+        t0[i] = q * slab_e<NDIM, WIDE>(i);
     }
     const int z0 = zb * a.zc;
     const int z1 = min(z0 + a.zc, g.dims[0]);
@@ -331,7 +362,7 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
         int off = 0;
 #pragma unroll
         for (int i = NDIM - 1; i >= 1; --i) {
-            const int he = slab_e<NDIM>(i) + 2;
+            const int he = slab_e<NDIM, WIDE>(i) + 2;
             const int c = t0[i] + h % he - 1;
             h /= he;
             in &= (c >= 0) & (c < g.dims[i]);
@@ -347,11 +378,11 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
         int r = tid;
 #pragma unroll
         for (int i = NDIM - 1; i >= 1; --i) {
-            const int e = r % slab_e<NDIM>(i);
-            r /= slab_e<NDIM>(i);
+            const int e = r % slab_e<NDIM, WIDE>(i);
+            r /= slab_e<NDIM, WIDE>(i);
             const int c = t0[i] + e;
             mine &= c < g.dims[i];
-            center += e * slab_hs<NDIM>(i);
+            center += e * slab_hs<NDIM, WIDE>(i);
             vin += c * a.st[i];
         }
     }
@@ -407,7 +438,7 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
             auto key = [&](int j) {
                 int d = B;
 #pragma unroll
-                for (int i = 1; i < NDIM; ++i) d += R.d[j][i] * slab_hs<NDIM>(i);
+                for (int i = 1; i < NDIM; ++i) d += R.d[j][i] * slab_hs<NDIM, WIDE>(i);
                 const uint32_t* p = R.d[j][0] < 0 ? p0 : R.d[j][0] > 0 ? p2 : p1;
                 return p[d];
             };
@@ -456,25 +487,26 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
             lab[v] = is_max ? v : -(best + 1);
             if (ptr) ptr[v] = best;
         }
-        // every row of the tile is one byte of each mask's word, stored by its
+        // every row of the tile is one piece of each mask's word, stored by its
         // first lane; the last tile of a row also clears what is left of the
         // row's last word (in one store when it opens the word)
         const uint64_t bm = __ballot(is_max), bs = __ballot(is_sad);
         if (mine && tid % EX == 0) {
             const int64_t row = (int64_t)(z * a.rows_per_plane + rin) * XW;
-            const uint32_t m = (uint8_t)(bm >> __lane_id()), sd = (uint8_t)(bs >> __lane_id());
+            const Piece m = (Piece)(bm >> __lane_id()), sd = (Piece)(bs >> __lane_id());
+            constexpr int PW = 64 / EX;  // pieces of a word
             const int h = x / EX;
             const bool last = x + EX >= X;
-            if (last && h % 8 == 0) {
-                mmask[row + h / 8] = m;
-                smask[row + h / 8] = sd;
+            if (last && h % PW == 0) {
+                mmask[row + h / PW] = m;
+                smask[row + h / PW] = sd;
             } else {
-                uint8_t* mp = reinterpret_cast<uint8_t*>(mmask + row);
-                uint8_t* sdp = reinterpret_cast<uint8_t*>(smask + row);
-                mp[h] = (uint8_t)m;
-                sdp[h] = (uint8_t)sd;
+                Piece* mp = reinterpret_cast<Piece*>(mmask + row);
+                Piece* sdp = reinterpret_cast<Piece*>(smask + row);
+                mp[h] = m;
+                sdp[h] = sd;
                 if (last)
-                    for (int k = h + 1; k < 8 * XW; ++k) mp[k] = sdp[k] = 0;
+                    for (int k = h + 1; k < PW * XW; ++k) mp[k] = sdp[k] = 0;
             }
         }
         sp = s1;
@@ -482,6 +514,31 @@ __global__ __launch_bounds__(256) void k_classify_slab(const uint32_t* __restric
 }
 
 constexpr int64_t kSlabBlocks = int64_t(1) << 23;  // most blocks of one launch
+
+template <int NDIM, bool MINMODE, bool WIDE>
+static void launch_slab(const Grid& g, int32_t* lab, int32_t* ptr, const Work& w, hipStream_t s)
+{
+    SlabArgs a{};
+    a.st[NDIM - 1] = 1;
+    for (int i = NDIM - 2; i >= 0; --i) a.st[i] = a.st[i + 1] * g.dims[i + 1];
+    const int64_t tiles = slab_tiles<NDIM, WIDE>(g, a.nt);
+    // about 8192 blocks, each over as many planes as that allows
+    const int64_t D0 = g.dims[0];
+    const int64_t zc = std::min<int64_t>(D0, std::max<int64_t>(1, (D0 * tiles + 8191) / 8192));
+    a.zc = (int)zc;
+    a.zblocks = (int)((D0 + zc - 1) / zc);
+    a.rows_per_plane = a.st[0] / g.dims[NDIM - 1];
+    const int64_t blocks = tiles * a.zblocks;  // fewer than 2^31: every tile holds a vertex
+    // a launch holds fewer than 2^32 threads; where the axes between the first
+    // and the last are short, most of a tile's threads have no vertex (8 X
+    // threads for X vertices in a row along the last axis of a 4D grid)
+    for (int64_t done = 0; done < blocks; done += kSlabBlocks) {
+        a.first = (int)done;
+        const int64_t n = std::min<int64_t>(blocks - done, kSlabBlocks);
+        hipLaunchKernelGGL((k_classify_slab<NDIM, MINMODE, WIDE>), dim3((unsigned)n), dim3(256), 0, s, w.keys, g, a,
+                           lab, ptr, w.mmask, w.smask);
+    }
+}
 
 template <int NDIM, bool MINMODE>
 static void launch_classify_t(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, const Work& w,
@@ -491,30 +548,15 @@ static void launch_classify_t(const float* f, const Grid& g, int32_t* lab, int32
     const int kblocks = (int)(kwant < 8192 ? kwant : 8192);
     hipLaunchKernelGGL(k_keys<MINMODE>, dim3(kblocks), dim3(256), 0, s, f, g.N, w.keys, w.ctr);
     if constexpr (NDIM >= 4) {
-        SlabArgs a{};
-        a.st[NDIM - 1] = 1;
-        for (int i = NDIM - 2; i >= 0; --i) a.st[i] = a.st[i + 1] * g.dims[i + 1];
-        int64_t tiles = 1;
-        for (int i = 1; i < NDIM; ++i) {
-            a.nt[i] = (g.dims[i] + slab_e<NDIM>(i) - 1) / slab_e<NDIM>(i);
-            tiles *= a.nt[i];
-        }
-        // about 8192 blocks, each over as many planes as that allows
-        const int64_t D0 = g.dims[0];
-        const int64_t zc = std::min<int64_t>(D0, std::max<int64_t>(1, (D0 * tiles + 8191) / 8192));
-        a.zc = (int)zc;
-        a.zblocks = (int)((D0 + zc - 1) / zc);
-        a.rows_per_plane = a.st[0] / g.dims[NDIM - 1];
-        const int64_t blocks = tiles * a.zblocks;  // fewer than 2^31: every tile holds a vertex
-        // a launch holds fewer than 2^32 threads; where the axes between the
-        // first and the last are short, most of a tile's threads have no
-        // vertex (X vertices in a row along the last axis: 32 X threads in 4D)
-        for (int64_t done = 0; done < blocks; done += kSlabBlocks) {
-            a.first = (int)done;
-            const int64_t n = std::min<int64_t>(blocks - done, kSlabBlocks);
-            hipLaunchKernelGGL((k_classify_slab<NDIM, MINMODE>), dim3((unsigned)n), dim3(256), 0, s, w.keys, g, a, lab,
-                               ptr, w.mmask, w.smask);
-        }
+        // a wide tile takes about one and a half times as long as one with rows
+        // of 8 (6D; between 0.8 and 1.7 times in 4D and 5D), so it is taken for
+        // two thirds of the tiles or fewer
+        int32_t nt[EG_MAX_NDIM];
+        const int64_t narrow = slab_tiles<NDIM, false>(g, nt), wide = slab_tiles<NDIM, true>(g, nt);
+        if (3 * wide <= 2 * narrow)
+            launch_slab<NDIM, MINMODE, true>(g, lab, ptr, w, s);
+        else
+            launch_slab<NDIM, MINMODE, false>(g, lab, ptr, w, s);
     } else {
         const int blocks = (int)((g.N + 255) / 256);
         hipLaunchKernelGGL((k_classify_generic<NDIM, MINMODE>), dim3(blocks), dim3(256), 0, s, w.keys, g, lab, ptr,

@@ -50,12 +50,12 @@ def test_long_untiled_paths(shape):
 
 
 def test_slab_of_more_threads_than_a_launch_holds():
-    """A 4D grid of one long row takes 32 threads per vertex: more blocks than
+    """A 4D grid of one long row takes eight threads per vertex: more blocks than
     one launch, the last of them ragged.  The same row as a 1D grid, whose
     kernels hold one thread per vertex, has the same graph."""
     import torch
     from paper_2303_02724_amd import eg
-    n = 2 ** 27 + 37
+    n = 2 ** 28 + 37
     f = torch.arange(n, device="cuda:0", dtype=torch.int32).remainder_(1000).sub_(500).abs_().to(torch.float32)
     f[-20:] += 3
     want = None
@@ -100,3 +100,18 @@ def test_exit_lists_of_long_axes(shape, exits_log2):
             print(ctx, flush=True)
             g = gpu_graph(f, minima, tuning=tuning, cap_max=f.size, cap_sad=f.size, cap_arc=4 * f.size)
             assert_same(g, O.extremum_graph(f, minima), KEYS + ["ptr"], ctx)
+
+
+@pytest.mark.parametrize("lead", [(3, 2, 2), (4, 1, 4), (5, 2, 2, 2), (2, 2, 1, 2), (2, 2, 1, 2, 2), (3, 1, 2, 2, 2)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("x", [9, 16, 17, 32, 33, 63, 64, 65, 97])
+def test_wide_slab_rows_of_thin_grids(lead, x):
+    """Axes shorter than the slab tiles before the last one: rows of 32 (16 in
+    6D) instead of 8, at the edges of the rows and of the 64-vertex mask word."""
+    f = W.random_field((*lead, x), 80 + x, "uniform")
+    f[..., ::3] = np.round(f[..., ::3] * 4) / 4  # ties too
+    for minima in (False, True):
+        ctx = f"shape={f.shape} minima={minima}"
+        print(ctx, flush=True)
+        g = gpu_graph(f, minima, cap_max=f.size, cap_sad=f.size, cap_arc=8 * f.size)
+        assert_same(g, O.extremum_graph(f, minima), KEYS + ["ptr"], ctx)
