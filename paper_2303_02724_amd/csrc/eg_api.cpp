@@ -75,7 +75,7 @@ hipError_t stage_classify(const float* field, const Grid& g, const eg_out& o, co
                           hipStream_t s)
 {
     const bool minima = (o.flags & EG_MINIMA) != 0;
-    hipError_t e = launch_init(g, w, o.header, s);
+    hipError_t e = launch_init(w, o.header, s);
     if (e != hipSuccess) return e;
     return launch_classify(field, g, minima, o.labels, o.ptr, w, tu, s);
 }
@@ -117,7 +117,7 @@ eg_status run_typed(int dtype, const void* field, const int64_t* dims, void* str
     decode_tuning(out->tuning, &tu);
     hipStream_t s = (hipStream_t)stream;
     const bool minima = (out->flags & EG_MINIMA) != 0;
-    hipError_t e = launch_init(g, w, out->header, s);
+    hipError_t e = launch_init(w, out->header, s);
     if (e == hipSuccess) e = launch_classify_typed(dtype, field, g, minima, out->labels, out->ptr, w, s);
     if (e == hipSuccess) e = stage_label(g, *out, w, tu, s);
     if (e == hipSuccess) e = stage_arcs((const float*)field, g, *out, w, s, dtype);
@@ -431,7 +431,7 @@ eg_status eg_build_streamed(const float* host_field, float* dev_field, int ndim,
         if (hipEventRecord((hipEvent_t)events[k], cs) != hipSuccess) return EG_ERR_HIP;
     }
     const bool minima = (out->flags & EG_MINIMA) != 0;
-    hipError_t e = launch_init(g, w, out->header, s);
+    hipError_t e = launch_init(w, out->header, s);
     for (int64_t k = 0; k < nslabs && e == hipSuccess; ++k) {
         // the tiles of slab k read one plane past it: wait for the next slab too
         e = hipStreamWaitEvent(s, (hipEvent_t)events[std::min(k + 1, nslabs - 1)], 0);

@@ -1,12 +1,12 @@
 // eg_classify.hip -- per-vertex classification, labels and saddle reps.
 //
-// k_classify_generic  stages (a) and (c) of the method for n = 1: one
-//   thread per vertex reads its closed neighbourhood, forms the upper-link
-//   mask (Sec. 3.3), the steepest-ascent pointer (highest upper-link vertex,
-//   Sec. 3.3) and decides maximum (empty upper link) / saddle (>= 2
-//   components, Table 1) by set algebra on the link's rows (eg_link.h).
-// k_classify_slab  the same for n = 4, 5 and 6, reading the neighbourhood
-//   from planes of keys staged in LDS.
+// k_classify_slab  stages (a) and (c) of the method for n = 4, 5 and 6: one
+//   thread per vertex reads its closed neighbourhood from planes of keys staged
+//   in LDS, forms the upper-link mask (Sec. 3.3), the steepest-ascent pointer
+//   (highest upper-link vertex, Sec. 3.3) and decides maximum (empty upper link)
+//   / saddle (>= 2 components, Table 1) by set algebra on the link's rows
+//   (eg_link.h).
+// k_classify1d  the same for n = 1, whose link is two vertices.
 // k_exit_*, k_final*  stage (b): pointer jumping until every vertex names its
 //   maximum (the end of the walk of Alg. 2).
 #include "eg_internal.h"
@@ -15,119 +15,20 @@
 
 namespace eg {
 
-// Counters and header; on 1D grids (whose masks are written bit by bit) the
-// words of both masks too.
+// Counters and header.
 __global__ __launch_bounds__(256) void k_init(uint32_t* __restrict__ ctr, uint32_t* __restrict__ claims,
-                                              int32_t* __restrict__ header, uint64_t* __restrict__ a,
-                                              uint64_t* __restrict__ b, int64_t n)
+                                              int32_t* __restrict__ header)
 {
-    if (blockIdx.x == 0) {
-        const int i = threadIdx.x;
-        if (i < C_SLOTS) ctr[i] = 0;
-        if (i < kRegions) claims[kRegionStride * i] = 0;
-        if (header && i < EG_H_SLOTS) header[i] = 0;
-    }
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        a[i] = 0;
-        b[i] = 0;
-    }
+    const int i = threadIdx.x;
+    if (i < C_SLOTS) ctr[i] = 0;
+    if (i < kRegions) claims[kRegionStride * i] = 0;
+    if (header && i < EG_H_SLOTS) header[i] = 0;
 }
 
-hipError_t launch_init(const Grid& g, const Work& w, int32_t* header, hipStream_t s)
+hipError_t launch_init(const Work& w, int32_t* header, hipStream_t s)
 {
-    const int64_t n = g.ndim == 1 ? w.words : 0;
-    const int64_t want = (n + 255) / 256;
-    const int blocks = (int)(want < 1 ? 1 : want < 4096 ? want : 4096);
-    hipLaunchKernelGGL(k_init, dim3(blocks), dim3(256), 0, s, w.ctr, w.claims, header, w.mmask, w.smask, n);
+    hipLaunchKernelGGL(k_init, dim3(1), dim3(256), 0, s, w.ctr, w.claims, header);
     return hipGetLastError();
-}
-
-// Visit the closed neighbourhood of v (1D) in the order in which later vertices
-// win ties; fills the upper-link mask and the steepest-ascent target.  The
-// rows are unrolled, one load per row under the row's own branch; a row's
-// linear offset and the boundary bits that rule it out follow from the
-// compile-time rows and the grid strides st[] (uniform, scalar work).
-template <int NDIM, bool MINMODE>
-__device__ __forceinline__ void scan_unrolled(const uint32_t* __restrict__ keys, const int* st, int v,
-                                              uint32_t bits, uint32_t uv, Mask<NDIM>& up, int& best)
-{
-    constexpr Rows<NDIM> R = make_rows_ce<NDIM>();
-    constexpr int K = Rows<NDIM>::K;
-    uint32_t best_u = 0;
-    best = v;
-    auto visit = [&](int j) {
-        int lin = 0;
-        uint32_t forb = 0;
-#pragma unroll
-        for (int i = 0; i < NDIM; ++i) {
-            lin += R.d[j][i] * st[i];
-            forb |= R.d[j][i] < 0 ? 1u << (2 * i) : R.d[j][i] > 0 ? 1u << (2 * i + 1) : 0u;
-        }
-        if ((bits & forb) == 0) {
-            const int u_id = v + lin;
-            const uint32_t u = keys[u_id];
-            const bool above = row_wins_tie<MINMODE>(j, K) ? (u >= uv) : (u > uv);
-            up |= Mask<NDIM>(above) << j;
-            if (u >= best_u) {
-                best_u = u;
-                best = u_id;
-            }
-        }
-    };
-    auto self = [&]() {
-        if (uv >= best_u) {
-            best_u = uv;
-            best = v;
-        }
-    };
-    if (!MINMODE) {
-#pragma unroll
-        for (int j = 0; j < K / 2; ++j) visit(j);
-        self();
-#pragma unroll
-        for (int j = K / 2; j < K; ++j) visit(j);
-    } else {
-#pragma unroll
-        for (int j = K - 1; j >= K / 2; --j) visit(j);
-        self();
-#pragma unroll
-        for (int j = K / 2 - 1; j >= 0; --j) visit(j);
-    }
-}
-
-template <int NDIM>
-__device__ __forceinline__ uint32_t boundary_bits(const Grid& g, int v)
-{
-    uint32_t bits = 0;
-    int rem = v;
-#pragma unroll
-    for (int i = NDIM - 1; i >= 0; --i) {
-        const int d = g.dims[i];
-        const int c = rem % d;
-        rem /= d;
-        bits |= boundary_bit(c, d, i);
-    }
-    return bits;
-}
-
-// OR the bits of the lanes with `pred` into the row-padded mask: lanes that
-// share a word form a run of consecutive lanes (consecutive x), and the first
-// lane of each run writes the run's bits with one atomic.  Words are shared
-// only by the runs at either end of a wave, so atomics rarely meet.
-__device__ __forceinline__ void mask_or(bool pred, int64_t word, int bit, uint64_t* __restrict__ mask)
-{
-    const uint64_t b = __ballot(pred);
-    if (b == 0) return;
-    const int lane = __lane_id();
-    const int64_t prev = __shfl_up(word, 1);
-    const bool lead = lane == 0 || prev != word;
-    const uint64_t leads = __ballot(lead);
-    const uint64_t later = lane == 63 ? 0ull : (leads >> (lane + 1)) << (lane + 1);
-    const int next = later ? __ffsll((unsigned long long)later) - 1 : 64;
-    const int len = next - lane;
-    const uint64_t run = len >= 64 ? ~0ull : ((1ull << len) - 1ull);
-    const uint64_t bits = ((b >> lane) & run) << bit;
-    if (lead && word >= 0 && bits) atomicOr((unsigned long long*)&mask[word], (unsigned long long)bits);
 }
 
 // Order keys of every vertex (reversed for the minimum graph), once, for the
@@ -145,40 +46,39 @@ __global__ __launch_bounds__(256) void k_keys(const float* __restrict__ f, int N
     if (__ballot(nan) != 0 && __lane_id() == 0) atomicOr(&ctr[C_NAN], 1u);
 }
 
-template <int NDIM, bool MINMODE>
-__global__ __launch_bounds__(256) void k_classify_generic(const uint32_t* __restrict__ keys, Grid g,
-                                                          int32_t* __restrict__ lab, int32_t* __restrict__ ptr,
-                                                          uint64_t* __restrict__ mmask, uint64_t* __restrict__ smask)
+// 1D: the neighbours are the vertices before and after (key 0, below every
+// vertex, past the ends).  Of two equal vertices the later is the higher one, the
+// earlier in the minimum graph; a vertex below both neighbours is a saddle.  The
+// vertices of a wave are one word of the masks.
+template <bool MINMODE>
+__global__ __launch_bounds__(256) void k_classify1d(const uint32_t* __restrict__ keys, int32_t N,
+                                                    int32_t* __restrict__ lab, int32_t* __restrict__ ptr,
+                                                    uint64_t* __restrict__ mmask, uint64_t* __restrict__ smask)
 {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    bool is_max = false, is_sad = false;
-    if (v < g.N) {
-        const uint32_t bits = boundary_bits<NDIM>(g, v);
-        const uint32_t uv = keys[v];
-        Mask<NDIM> up = 0;
-        int best;
-        int st[NDIM];
-        st[NDIM - 1] = 1;
-#pragma unroll
-        for (int i = NDIM - 2; i >= 0; --i) st[i] = st[i + 1] * g.dims[i + 1];
-        scan_unrolled<NDIM, MINMODE>(keys, st, v, bits, uv, up, best);
-        is_max = up == 0;
-        if (!is_max) is_sad = !link_connected<NDIM>(up);
-        lab[v] = is_max ? v : -(best + 1);  // final label, or "same as best"
+    const uint32_t v = blockIdx.x * blockDim.x + threadIdx.x;
+    const bool in = v < (uint32_t)N;
+    bool before = false, after = false;  // above v
+    if (in) {
+        const uint32_t u = keys[v];
+        const uint32_t b = v > 0 ? keys[v - 1] : 0u, a = v + 1 < (uint32_t)N ? keys[v + 1] : 0u;
+        before = MINMODE ? b >= u : b > u;
+        after = MINMODE ? a > u : a >= u;
+        const bool to_after = after && (!before || (MINMODE ? a > b : a >= b));
+        const int best = (int)v + (to_after ? 1 : before ? -1 : 0);
+        lab[v] = before || after ? -(best + 1) : best;  // "same as best", or final
         if (ptr) ptr[v] = best;
     }
-    // this vertex's bit in the row-padded masks (rows run along the last axis)
-    const int X = g.dims[NDIM - 1];
-    const int row = v / X, x = v - row * X;
-    const int64_t word = v < g.N ? (int64_t)row * ((X + 63) >> 6) + (x >> 6) : -1;
-    mask_or(is_max, word, x & 63, mmask);
-    mask_or(is_sad, word, x & 63, smask);
+    const uint64_t maxima = __ballot(in && !before && !after), saddles = __ballot(before && after);
+    if (in && __lane_id() == 0) {
+        mmask[v >> 6] = maxima;
+        smask[v >> 6] = saddles;
+    }
 }
 
 // -------------------------------------------------------- 4D-6D slab tiles
 //
-// k_classify_slab  the same outputs as k_classify_generic for n = 4, 5 and 6,
-//   with the neighbourhood read from LDS instead of through the caches (62
+// k_classify_slab  pointers, maxima and saddles for n = 4, 5 and 6, with the
+//   neighbourhood read from LDS instead of through the caches (62
 //   gathers per vertex in 5D, 126 in 6D, leave a kernel that reads them from
 //   memory bound by the memory pipeline, not by arithmetic).  A block owns a
 //   tile of the hyperplanes orthogonal to axis 0 (4x8x8 vertices in 4D,
@@ -231,7 +131,7 @@ int64_t slab_tiles(const Grid& g, int32_t* nt)
 {
     int64_t n = 1;
     for (int i = 1; i < NDIM; ++i) {
-        nt[i] = (g.dims[i] + slab_e<NDIM, WIDE>(i) - 1) / slab_e<NDIM, WIDE>(i);
+        nt[i] = (int32_t)((int64_t(g.dims[i]) + slab_e<NDIM, WIDE>(i) - 1) / slab_e<NDIM, WIDE>(i));
         n *= nt[i];
     }
     return n;
@@ -558,9 +458,9 @@ static void launch_classify_t(const float* f, const Grid& g, int32_t* lab, int32
         else
             launch_slab<NDIM, MINMODE, false>(g, lab, ptr, w, s);
     } else {
-        const int blocks = (int)((g.N + 255) / 256);
-        hipLaunchKernelGGL((k_classify_generic<NDIM, MINMODE>), dim3(blocks), dim3(256), 0, s, w.keys, g, lab, ptr,
-                           w.mmask, w.smask);
+        const int blocks = (int)(((int64_t)g.N + 255) / 256);
+        hipLaunchKernelGGL(k_classify1d<MINMODE>, dim3(blocks), dim3(256), 0, s, w.keys, g.N, lab, ptr, w.mmask,
+                           w.smask);
     }
 }
 

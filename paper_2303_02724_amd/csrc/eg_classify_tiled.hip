@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256) void k_classify2d(TileArgs a, int count)
     __shared__ uint32_t s_u[66 * (TY + 2)];
     __shared__ int32_t s_nxt[64 * TY];
     __shared__ uint32_t s_tmp[8];
-    tile_nd<2, MINMODE, TY, 1>(a, (int)a.first + xcd_run(blockIdx.x, count), s_u, s_nxt, nullptr, s_tmp);
+    tile2d<MINMODE, TY>(a, (int)a.first + xcd_run(blockIdx.x, count), s_u, s_nxt, s_tmp);
 }
 
 TileArgs tile_args(const float* f, const Grid& g, int32_t* lab, int32_t* ptr, const Work& w, int ty, int tz)
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
         else
             tile3d<MINMODE, TY, TZ, false, SRC_F32>(a, tile, s);
     } else {
-        tile_nd<2, MINMODE, TY, 1>(a, tile, s_mem + 8, reinterpret_cast<int32_t*>(s_mem + 8 + HALO2), nullptr, s_mem);
+        tile2d<MINMODE, TY>(a, tile, s_mem + 8, reinterpret_cast<int32_t*>(s_mem + 8 + HALO2), s_mem);
     }
 }
 

@@ -246,22 +246,6 @@ __device__ __forceinline__ uint32_t mode_key(float x)
     return MINMODE ? ~k : k;
 }
 
-// Boundary bits of a vertex: bit 2i set if coordinate i is 0, bit 2i+1 set if
-// it is dims[i]-1.  Row j exists iff (bits & forb[j]) == 0.
-__device__ __forceinline__ uint32_t boundary_bit(int c, int d, int axis)
-{
-    return (uint32_t(c == 0) << (2 * axis)) | (uint32_t(c == d - 1) << (2 * axis + 1));
-}
-
-// Whether row j beats an equal key (it lies later in visiting order).  In the
-// maximum graph later = larger index = the {0,1} half; in the minimum graph
-// the roles swap.
-template <bool MINMODE>
-__device__ __forceinline__ bool row_wins_tie(int j, int k)
-{
-    return (j >= k / 2) != MINMODE;
-}
-
 // f(std::integral_constant<int, i>) for i in [I, N): compile-time row indices.
 template <int I, int N, class F>
 __device__ __forceinline__ void static_for(F&& f)
@@ -406,8 +390,8 @@ __device__ __forceinline__ void exit_first(const ExitPart& p, const uint32_t* ex
 
 // ------------------------------------------------------------------ launchers
 
-// Counters and header to zero; the two masks too on 1D grids.
-hipError_t launch_init(const Grid& g, const Work& w, int32_t* header, hipStream_t s);
+// Counters and header to zero.
+hipError_t launch_init(const Work& w, int32_t* header, hipStream_t s);
 hipError_t launch_classify(const float* f, const Grid& g, bool minima, int32_t* lab, int32_t* ptr, const Work& w,
                            const Tuning& tu, hipStream_t s);
 // Classification of the 2D/3D tiles [first, first + count) (tiles in C order:

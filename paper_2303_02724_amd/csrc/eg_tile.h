@@ -212,22 +212,18 @@ __device__ __forceinline__ void store_words(const TileArgs& a, uint64_t word, in
     }
 }
 
-template <int NDIM, bool MINMODE, int TY, int TZ>
-__device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u, int32_t* s_nxt, uint32_t* s_conn,
-                                        uint32_t* s_tmp)
+// A tile of a 2D grid.
+template <bool MINMODE, int TY>
+__device__ __forceinline__ void tile2d(const TileArgs& a, int b, uint32_t* s_u, int32_t* s_nxt, uint32_t* s_tmp)
 {
-    static_assert(NDIM == 2 || NDIM == 3, "tiled path is for 2D and 3D");
-    static_assert(TY % 4 == 0, "four waves split the y rows");
-    constexpr int K = 2 * ((1 << NDIM) - 1);
+    static_assert(TY % 4 == 0, "four waves split the rows");
+    constexpr int K = 6;
     constexpr int TX = 64;
-    constexpr int HX = TX + 2, HY = TY + 2, HZ = NDIM == 3 ? TZ + 2 : 1;
-    constexpr int HALO = HX * HY * HZ;
-    constexpr int TILE = TX * TY * TZ;
-    constexpr int YPT = TY / 4;
-    constexpr int VPT = YPT * TZ;
-    constexpr int ZH = NDIM == 3 ? 1 : 0;  // halo depth along z
+    constexpr int HX = TX + 2, HY = TY + 2;
+    constexpr int TILE = TX * TY;
+    constexpr int VPT = TY / 4;
     const float* __restrict__ f = a.f;
-    const int X = a.X, Y = a.Y, Z = a.Z;
+    const int X = a.X, Y = a.Y;
     int32_t* __restrict__ lab = a.lab;
     int32_t* __restrict__ ptr = a.ptr;
     uint32_t* __restrict__ ctr = a.ctr;
@@ -235,17 +231,11 @@ __device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u,
     // the wave index is uniform: keep it (and every row quantity) scalar
     const int tid = threadIdx.x, lx = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tx = b % a.tiles_x;
-    const int rr = b / a.tiles_x;
-    const int ty = rr % a.tiles_y;
-    const int tz = rr / a.tiles_y;
-    const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
-    const int SY = X;
-    const int SZ = X * Y;
+    const int ty = b / a.tiles_x;
+    const int x0 = tx * TX, y0 = ty * TY;
 
-    if constexpr (NDIM == 3)
-        for (int i = tid; i < 512; i += 256) s_conn[i] = c_conn3.w[i];
     bool nan = false;
-    if constexpr (NDIM == 2) {
+    {
         // rows of 64 aligned values, one per lane, from a uniform row address
         // (rows outside the grid read a clamped row and are replaced), then
         // the two edge columns of every row (one value per thread); all loads
@@ -261,13 +251,13 @@ __device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u,
         for (int i = 0; i < RPW; ++i) {
             const int gy = y0 + wv + 4 * i - 1;
             const int gyc = min(max(gy, 0), Y - 1);
-            vals[i] = f[(int64_t)gyc * SY + gxc];
+            vals[i] = f[(int64_t)gyc * X + gxc];
         }
         const int erow = tid >> 1;
         const int egx = (tid & 1) ? x0 + TX : x0 - 1;
         const int egy = y0 + erow - 1;
         const bool ein = tid < EDGES && (unsigned)egx < (unsigned)X && (unsigned)egy < (unsigned)Y;
-        const float eval = f[ein ? (int64_t)egy * SY + egx : 0];
+        const float eval = f[ein ? (int64_t)egy * X + egx : 0];
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
             const int hy = wv + 4 * i;  // uniform
@@ -279,34 +269,6 @@ __device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u,
             }
         }
         if (tid < EDGES) s_u[erow * HX + ((tid & 1) ? HX - 1 : 0)] = ein ? mode_key<MINMODE>(eval) : 0u;
-    } else {
-        constexpr int PER = (HALO + 255) / 256;
-        float vals[PER];
-        bool vin[PER];
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int e = tid + 256 * i;
-            const int hx = e % HX;
-            const int q = e / HX;
-            const int hy = q % HY;
-            const int hz = q / HY;
-            const int gx = x0 + hx - 1, gy = y0 + hy - 1, gz = z0 + hz - ZH;
-            vin[i] = e < HALO && (unsigned)gx < (unsigned)X && (unsigned)gy < (unsigned)Y && (unsigned)gz < (unsigned)Z;
-            vals[i] = vin[i] ? f[gz * SZ + gy * SY + gx] : 0.0f;
-        }
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int e = tid + 256 * i;
-            if (e < HALO) {
-                const int hx = e % HX;
-                const int q = e / HX;
-                const int hy = q % HY;
-                const int hz = q / HY;
-                const bool own = hx >= 1 && hx <= TX && hy >= 1 && hy <= TY && hz >= ZH && hz < ZH + TZ;
-                nan |= vin[i] && own && (vals[i] != vals[i]);
-                s_u[e] = vin[i] ? mode_key<MINMODE>(vals[i]) : 0u;
-            }
-        }
     }
     __syncthreads();
 
@@ -316,16 +278,15 @@ __device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u,
     uint64_t word = 0;  // this lane's parked mask word
 #pragma unroll
     for (int k = 0; k < VPT; ++k) {
-        const int ly = wv + 4 * (k % YPT);
-        const int lz = k / YPT;
-        const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lz;
-        const bool in = gx < X && gy < Y && gz < Z;
-        const int li = (lz * TY + ly) * TX + lx;
+        const int ly = wv + 4 * k;
+        const int gx = x0 + lx, gy = y0 + ly;
+        const bool in = gx < X && gy < Y;
+        const int li = ly * TX + lx;
         int n = TILE + li;  // vertices outside the grid end their own chain and are never written
         bool is_max = false, is_sad = false;
         int v = 0;
         if (in) {
-            const int c = ((lz + ZH) * HY + (ly + 1)) * HX + (lx + 1);
+            const int c = (ly + 1) * HX + (lx + 1);
             const uint32_t uv = s_u[c];
             uint32_t up = 0, best_u = 0;
             int best_j = K;  // K stands for the vertex itself
@@ -341,8 +302,8 @@ __device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u,
                     }
                 } else {
                     constexpr int j = pos < K / 2 ? pos : pos - 1;
-                    using RJ = Row<NDIM, j>;
-                    constexpr int off = (RJ::dz * HY + RJ::dy) * HX + RJ::dx;
+                    using RJ = Row<2, j>;
+                    constexpr int off = RJ::dy * HX + RJ::dx;
                     constexpr bool wins_tie = (j >= K / 2) != MINMODE;
                     const uint32_t u = s_u[c + off];
                     const bool above = wins_tie ? (u >= uv) : (u > uv);
@@ -354,25 +315,18 @@ __device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u,
                 }
             });
             is_max = up == 0;
-            bool connected;
-            if constexpr (NDIM == 3)
-                connected = (s_conn[up >> 5] >> (up & 31)) & 1u;
-            else
-                connected = (CONN2 >> up) & 1ull;
-            is_sad = !is_max && !connected;
-            v = gz * SZ + gy * SY + gx;
+            is_sad = !is_max && !((CONN2 >> up) & 1ull);
+            v = gy * X + gx;
             int pv = v;
             if (best_j == K) {
                 n = TILE + li;  // a maximum ends its chain
             } else {
-                const int dz = NDIM == 3 ? (int)((Pack<NDIM>::z >> (2 * best_j)) & 3u) - 1 : 0;
-                const int dy = (int)((Pack<NDIM>::y >> (2 * best_j)) & 3u) - 1;
-                const int dx = (int)((Pack<NDIM>::x >> (2 * best_j)) & 3u) - 1;
-                pv = v + dz * SZ + dy * SY + dx;
-                const int lz2 = lz + dz, ly2 = ly + dy, lx2 = lx + dx;
-                const bool inside = (unsigned)lz2 < (unsigned)TZ && (unsigned)ly2 < (unsigned)TY &&
-                                    (unsigned)lx2 < (unsigned)TX;
-                n = inside ? (lz2 * TY + ly2) * TX + lx2 : -(pv + 1);
+                const int dy = (int)((Pack<2>::y >> (2 * best_j)) & 3u) - 1;
+                const int dx = (int)((Pack<2>::x >> (2 * best_j)) & 3u) - 1;
+                pv = v + dy * X + dx;
+                const int ly2 = ly + dy, lx2 = lx + dx;
+                const bool inside = (unsigned)ly2 < (unsigned)TY && (unsigned)lx2 < (unsigned)TX;
+                n = inside ? ly2 * TX + lx2 : -(pv + 1);
             }
             if (ptr) ptr[v] = pv;
         }
@@ -381,38 +335,34 @@ __device__ __forceinline__ void tile_nd(const TileArgs& a, int b, uint32_t* s_u,
         park_word(word, is_sad, 32 + k);
     }
     {
-        const int k = __lane_id() & 31;
-        const int ly = wv + 4 * (k % YPT), lz = k / YPT;
-        store_words(a, word, VPT, (z0 + lz) * Y + y0 + ly, y0 + ly < Y && z0 + lz < Z, tx);
+        const int ly = wv + 4 * (__lane_id() & 31);
+        store_words(a, word, VPT, y0 + ly, y0 + ly < Y, tx);
     }
     if (__ballot(nan) != 0 && __lane_id() == 0) atomicOr(&ctr[C_NAN], 1u);
-    const int N = X * Y * Z;
+    const int N = X * Y;
     uint32_t claim;
     const uint32_t region = (a.first + blockIdx.x) & (a.regions - 1u);
     uint32_t* counter = a.claims + kRegionStride * region;
     const uint32_t nexit = rank_exits<VPT>(nxt, s_tmp, s_u, counter, claim);  // the halo is no longer read
-    auto s_idx = [&](int k) { return ((k / YPT) * TY + wv + 4 * (k % YPT)) * TX + lx; };
+    auto s_idx = [&](int k) { return (wv + 4 * k) * TX + lx; };
 #pragma unroll
     for (int k = 0; k < VPT; ++k) s_nxt[s_idx(k)] = nxt[k];
     __syncthreads();
     // global offset of every tile row from the tile's first vertex (one LDS
     // read per vertex instead of quarter-rate multiplies)
-    __shared__ int s_rowoff[TY * TZ];
-    if (tid < TY * TZ) s_rowoff[tid] = (tid / TY) * SZ + (tid % TY) * SY;
+    __shared__ int s_rowoff[TY];
+    if (tid < TY) s_rowoff[tid] = tid * X;
     double_tile_chains<VPT, TILE, 1>(nxt, s_nxt, s_idx);
     uint32_t base;
     const bool fit = place_exits(nexit, claim, s_u, s_tmp, a, region, base);
     const int xoff = exit_offset<VPT>(nxt, fit, base, s_u, N);
-    const int tile0 = z0 * SZ + y0 * SY + x0;
+    const int tile0 = y0 * X + x0;
 #pragma unroll
     for (int k = 0; k < VPT; ++k) {
-        const int ly = wv + 4 * (k % YPT);
-        const int lz = k / YPT;
-        const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lz;
+        const int ly = wv + 4 * k;
         const int n = nxt[k];
-        if (gx < X && gy < Y && gz < Z)
-            lab[tile0 + s_rowoff[lz * TY + ly] + lx] =
-                n >= 0 ? tile0 + s_rowoff[(n - TILE) >> 6] + (n & 63) : n - xoff;
+        if (x0 + lx < X && y0 + ly < Y)
+            lab[tile0 + s_rowoff[ly] + lx] = n >= 0 ? tile0 + s_rowoff[(n - TILE) >> 6] + (n & 63) : n - xoff;
     }
 }
 
