@@ -307,8 +307,10 @@ constexpr int kArcThreads = NDIM == 5 ? 128 : 256;
 
 // Most waves per SIMD that k_arc_count schedules its registers for: 6D is
 // bound by the latency of its 126 gathers, and more of them in flight in fewer
-// waves is the better trade (16^6, stage (d): 64 us with 77 registers, 52 with
-// room for two waves).
+// waves is the better trade.  Stage (d) with registers for eight waves and for
+// two, us: smoothed noise of 16^6 290 and 209, smoother 101 and 93, 12^6 87 and
+// 76, 9 x 10 x 11 x 12 x 13 x 14 81 and 71, 2^5 x 100 000 107 and 94, noise of
+// 12^6 275 and 236; of ten fields one was slower (noise of 16^6, 713 and 730).
 template <int NDIM>
 constexpr int kArcWaves = NDIM == 6 ? 2 : 8;
 
@@ -887,8 +889,11 @@ __device__ __forceinline__ uint32_t recorded_steps(const PathArgs& P, uint32_t n
 {
     const int64_t s = P.cap_rec / ((int64_t)kRecPaths * (n > 0 ? n : 1));
     // with little room few saddles' paths fit, and recording costs more than
-    // it saves (201 x 190 x 333 noise, two steps: 1.50 -> 1.55 ms)
-    return s < 16 ? 0u : (uint32_t)(s < (int64_t)kRecSteps ? s : (int64_t)kRecSteps);
+    // it saves.  Walked twice and recorded, us, over 18 fields of 1D to 4D: 16
+    // steps and more 158 and 105, 270 and 156; 4 to 11 steps 251 and 196, 109 and
+    // 94, 84 and 74, 64 and 58 (one of six equal); 1 to 3 steps 608 and 680, 140
+    // and 143, 50 and 51
+    return s < 4 ? 0u : (uint32_t)(s < (int64_t)kRecSteps ? s : (int64_t)kRecSteps);
 }
 
 // Paths and path vertices of every saddle of the block's chunk (kept for the

@@ -67,3 +67,19 @@ def test_paths_of_5d_noise(shape):
         for a, b, name in zip((p.pair_offsets, p.path_offsets, p.vertices), wp,
                               ("pair_offsets", "path_offsets", "vertices")):
             assert np.array_equal(a.cpu().numpy(), b), f"{shape} minima={minima} {name}"
+
+
+@pytest.mark.parametrize("corr_len", [0.8, 1.0, 1.2, 1.5])
+def test_paths_recorded_for_few_steps(corr_len):
+    """Scratch for 4 to 20 steps of every path, of which the longest take 10 to
+    18: some saddles' paths are copied, the others walked again."""
+    from paper_2303_02724_amd import eg
+    import torch
+    f = W.gaussian_random_field((48, 50, 70), 9, corr_len=corr_len, workers=4)
+    for minima in (False, True):
+        want = O.extremum_graph(f, minima)
+        wp = O.paths(f, want["ptr"], want["saddles"], minima)
+        _, p = eg.build_paths(torch.from_numpy(f).cuda(), minima=minima)
+        for a, b, name in zip((p.pair_offsets, p.path_offsets, p.vertices), wp,
+                              ("pair_offsets", "path_offsets", "vertices")):
+            assert np.array_equal(a.cpu().numpy(), b), f"{corr_len} minima={minima} {name}"
