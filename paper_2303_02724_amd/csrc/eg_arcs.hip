@@ -297,7 +297,7 @@ constexpr bool kStoredKeys = NDIM != 2 && NDIM != 3;
 // 4D (0.92 M of 10 M vertices) 132 -> 95, 5D (3.8 M) 577 -> 523.  What bounds
 // 5D now is the L2: a gather fetches 128 bytes for the 8 it uses.  6D (126
 // rows, 32 KB a wave) reads the keys of a component's rows again instead, as
-// the write and path kernels do everywhere: they need the waves.
+// k_arc_write does everywhere: they need the waves (the path kernels: kPathKeys).
 template <int NDIM>
 constexpr bool kKeysInLds = NDIM <= 5;
 // Threads per block: a 5D wave's keys take 16 KB of LDS, and ten of them fit a
@@ -876,7 +876,8 @@ __device__ __forceinline__ bool walk(const ArcArgs& A, EG_GPTR(const int32_t) co
 constexpr uint32_t kRecPaths = 3;
 // Keys of the path kernels.  Walking wants waves, so 5D has no room to park
 // them, and reading a component's keys again costs more than scanning
-// registers at four waves per SIMD (32^5: 2.96 ms again, 3.9 parked, 2.6).
+// registers at four waves per SIMD (32^5, in blocks of 128 threads: 2.96 ms
+// again, 3.9 parked, 2.6 in registers).
 template <int NDIM>
 constexpr int kPathKeys = NDIM <= 4 ? KEYS_LDS : NDIM == 5 ? KEYS_REGS : KEYS_AGAIN;
 // Threads per block of the path kernels.  A chunk is whole rounds of 256

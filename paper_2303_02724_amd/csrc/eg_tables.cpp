@@ -1,8 +1,8 @@
-// eg_tables.cpp -- host-side neighbour tables and workspace layout.
+// eg_tables.cpp -- the neighbour rows for the host, the tuning word and the
+// workspace layout.
 //
-// The neighbour rows come from the compile-time tables of eg_rows.h
-// (GridAdjacency, Sec. 3.2 Alg. 1); here they get the grid's linear offsets
-// and boundary bits.
+// The rows come from the compile-time tables of eg_rows.h (GridAdjacency, Sec.
+// 3.2 Alg. 1).
 #include <algorithm>
 #include <cstring>
 

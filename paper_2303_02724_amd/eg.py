@@ -6,7 +6,8 @@ no CPU path: if the library is missing or no HIP device is present, the
 calls raise.
 
     res = eg.build(field)                # field: CUDA tensor, n = 1..6 axes
-                                         # (float32; other types via eg_order_field)
+                                         # (float32; other types as they are in 3D,
+                                         # via eg_order_field elsewhere)
     res.maxima, res.saddles, res.arc_offsets, res.arc_maxima, res.labels
 
 ``Builder`` keeps the buffers of one shape allocated so that repeated calls
@@ -230,7 +231,7 @@ class EGPaths:
     vertices: torch.Tensor
 
 
-# eg_dtype codes of the sample types eg_order_field accepts
+# eg_dtype codes of the sample types
 DTYPES = {torch.float32: 0, torch.float64: 1, torch.int8: 2, torch.uint8: 3, torch.int16: 4, torch.uint16: 5,
           torch.int32: 6, torch.uint32: 7, torch.int64: 8, torch.uint64: 9}
 
@@ -684,7 +685,7 @@ def build_paths(field: torch.Tensor, minima: bool = False, tuning: int = 0, **ca
 def build(field: torch.Tensor, minima: bool = False, want_ptr: bool = False, tuning: int = 0,
           **caps) -> EGResult:
     """Extremum graph of ``field`` (device tensor, 1..6 axes; float32, or any
-    other type of DTYPES through its order surrogate)."""
+    other type of DTYPES: as it is in 3D, else through its order surrogate)."""
     b = Builder(field.shape, minima=minima, want_ptr=want_ptr, device=field.device, tuning=tuning, **caps)
     return b.run(field.contiguous())
 
