@@ -522,8 +522,13 @@ hipError_t launch_classify(const float* f, const Grid& g, bool minima, int32_t* 
 
 constexpr int kEvenBlocks = 1024;  // four waves a SIMD
 
-// Blocks over n entries, four a thread, whose waves' quads are spread: a power
-// of two and a multiple of the XCDs (and of the exit list's regions).
+// Blocks over n entries, four a thread: a multiple of the XCDs (and of the exit
+// list's regions); a power of two where the waves' quads are spread.
+static int all_blocks(int64_t n)
+{
+    const int64_t want = (n / 4 + 255) / 256;
+    return (int)(want < 2048 ? (want / 8 + 1) * 8 : 2048);
+}
 static int even_blocks(int64_t n)
 {
     int blocks = 8;
@@ -571,13 +576,14 @@ struct LabelRun {
     int32_t* lab;
     uint32_t n, t, stride;
 };
-__device__ __forceinline__ LabelRun label_run(int32_t* lab, int32_t N)
+__device__ __forceinline__ LabelRun label_run(int32_t* lab, int32_t N, bool even)
 {
     // runs of whole quads; the last run ends with the vertices left over
     const uint32_t x = blockIdx.x & 7u, q = (uint32_t)N >> 5, lo = 4u * q * x;
     // waves of the run (four a block), and this one's number
     const uint32_t n = gridDim.x >> 1, w = (blockIdx.x >> 3) * 4u + (threadIdx.x >> 6);
-    return LabelRun{lab + lo, x == 7u ? (uint32_t)N - lo : 4u * q, spread(w, n) * 64u + (threadIdx.x & 63u), n * 64u};
+    return LabelRun{lab + lo, x == 7u ? (uint32_t)N - lo : 4u * q, (even ? spread(w, n) : w) * 64u + (threadIdx.x & 63u),
+                    n * 64u};
 }
 
 // The first pass follows four links, so that no wave waits for the longest of
@@ -589,19 +595,20 @@ __device__ __forceinline__ LabelRun label_run(int32_t* lab, int32_t N)
 // 90 to 290 us at one address.
 constexpr int kFirstHops = 4;
 __global__ __launch_bounds__(256) void k_final(int32_t* lab, int32_t N, uint32_t* __restrict__ ctr,
-                                               uint32_t* __restrict__ open_flags)
+                                               uint32_t* __restrict__ open_flags, bool even)
 {
-    const LabelRun r = label_run(lab, N);
+    const LabelRun r = label_run(lab, N, even);
     const int open = __syncthreads_or(sweep(r.lab, r.n, lab, lab, N, kFirstHops, r.t, r.stride, false));
     if (threadIdx.x == 0) open_flags[blockIdx.x] = open != 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) ctr[C_PASSES] = 1;
 }
 
 __global__ __launch_bounds__(256) void k_final_rest(int32_t* lab, int32_t N, uint32_t* __restrict__ ctr,
-                                                    const uint32_t* __restrict__ open_flags, int hops, int sweeps)
+                                                    const uint32_t* __restrict__ open_flags, int hops, int sweeps,
+                                                    bool even)
 {
     if (open_flags[blockIdx.x] == 0) return;
-    const LabelRun r = label_run(lab, N);
+    const LabelRun r = label_run(lab, N, even);
     bool open = true;
     int k = 0;
     for (; __ballot(open) != 0 && k < sweeps; ++k)
@@ -624,8 +631,7 @@ hipError_t launch_labels(const Grid& g, int32_t* lab, const Work& w, const Tunin
         int ty, tz;
         tile_shape(tu, g.ndim, &ty, &tz);
         const TileArgs a = tile_args(nullptr, g, lab, nullptr, w, ty, tz);
-        const int64_t ewant = (w.cap_exit / 4 + 255) / 256;
-        const int eblocks = (int)(ewant < 2048 ? (ewant / 8 + 1) * 8 : 2048);  // a multiple of the regions
+        const int eblocks = all_blocks(w.cap_exit);
         // the jump reads entries that other threads have already advanced,
         // which shortens long chains: it needs every entry initialised first
         hipLaunchKernelGGL(k_exit_init, dim3(eblocks), dim3(256), 0, s, a, w.exres);
@@ -644,10 +650,15 @@ hipError_t launch_labels(const Grid& g, int32_t* lab, const Work& w, const Tunin
         hipLaunchKernelGGL(k_codes_rest, dim3(even_blocks(N)), dim3(256), 0, s, lab, w.exres, N, w.ctr, tu.hops, sweeps);
         return hipGetLastError();
     }
-    const int blocks = even_blocks(N);
+    // paths of thousands of vertices need an axis as long (or a field made for
+    // it); elsewhere eight waves a SIMD in order are the better trade (labels of
+    // 16^6 46.8 and 47.6 us, 24^6 773 and 851, 32^6 4.84 and 5.51 ms)
+    constexpr int kLongAxis = 4096;  // vertices
+    const bool even = *std::max_element(g.dims, g.dims + g.ndim) >= kLongAxis;
+    const int blocks = even ? even_blocks(N) : all_blocks(N);
     uint32_t* flags = w.bsum + kSumRow;  // free until stage (d)
-    hipLaunchKernelGGL(k_final, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, flags);
-    hipLaunchKernelGGL(k_final_rest, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, flags, tu.hops, sweeps);
+    hipLaunchKernelGGL(k_final, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, flags, even);
+    hipLaunchKernelGGL(k_final_rest, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, flags, tu.hops, sweeps, even);
     return hipGetLastError();
 }
 
