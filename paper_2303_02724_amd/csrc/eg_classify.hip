@@ -650,11 +650,18 @@ hipError_t launch_labels(const Grid& g, int32_t* lab, const Work& w, const Tunin
         hipLaunchKernelGGL(k_codes_rest, dim3(even_blocks(N)), dim3(256), 0, s, lab, w.exres, N, w.ctr, tu.hops, sweeps);
         return hipGetLastError();
     }
-    // paths of thousands of vertices need an axis as long (or a field made for
-    // it); elsewhere eight waves a SIMD in order are the better trade (labels of
-    // 16^6 46.8 and 47.6 us, 24^6 773 and 851, 32^6 4.84 and 5.51 ms)
-    constexpr int kLongAxis = 4096;  // vertices
-    const bool even = *std::max_element(g.dims, g.dims + g.ndim) >= kLongAxis;
+    // long paths whose vertices lie close together in memory need an axis as
+    // long, and close to the last one (or a field made for it); elsewhere eight
+    // waves a SIMD in order are the better trade (labels of 16^6 46.8 and 47.6
+    // us, 24^6 773 and 851; slopes along the last axis of 16 x 16 x 16 x 4000
+    // 2.6 and 1.0 ms, of 16 x 16 x 16 x 1000 0.40 and 0.30, along the first of
+    // 4000 x 16 x 16 x 16 0.30 and 0.45)
+    bool even = false;
+    int64_t stride = 1;
+    for (int i = g.ndim - 1; i >= 0 && stride <= 256; --i) {
+        even |= g.dims[i] >= 512;
+        stride *= g.dims[i];
+    }
     const int blocks = even ? even_blocks(N) : all_blocks(N);
     uint32_t* flags = w.bsum + kSumRow;  // free until stage (d)
     hipLaunchKernelGGL(k_final, dim3(blocks), dim3(256), 0, s, lab, N, w.ctr, flags, even);

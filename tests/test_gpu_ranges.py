@@ -115,3 +115,17 @@ def test_wide_slab_rows_of_thin_grids(lead, x):
         print(ctx, flush=True)
         g = gpu_graph(f, minima, cap_max=f.size, cap_sad=f.size, cap_arc=8 * f.size)
         assert_same(g, O.extremum_graph(f, minima), KEYS + ["ptr"], ctx)
+
+
+@pytest.mark.parametrize("shape", [(2, 3, 3, 511), (2, 3, 3, 512), (2, 2, 530, 3), (3, 2, 2, 2, 515), (2, 2, 2, 2, 2, 513),
+                                   (600, 3, 3, 5), (600, 5, 6, 9)], ids=lambda s: "x".join(map(str, s)))
+def test_untiled_labels_around_long_axes(shape):
+    """Axes of 512 vertices and more close to the last one: the label kernels
+    deal their entries out another way than on other grids."""
+    slope = np.arange(int(np.prod(shape)), dtype=np.float32).reshape(shape)
+    for f in (slope, W.random_field(shape, 90, "uniform"), W.gaussian_mixture(shape, 9, n_gauss=5, noise=1e-3)):
+        for minima in (False, True):
+            ctx = f"shape={shape} minima={minima}"
+            print(ctx, flush=True)
+            g = gpu_graph(f, minima, cap_max=f.size, cap_sad=f.size, cap_arc=8 * f.size)
+            assert_same(g, O.extremum_graph(f, minima), KEYS + ["ptr"], ctx)
