@@ -890,11 +890,11 @@ __device__ __forceinline__ uint32_t recorded_steps(const PathArgs& P, uint32_t n
 {
     const int64_t s = P.cap_rec / ((int64_t)kRecPaths * (n > 0 ? n : 1));
     // with little room few saddles' paths fit, and recording costs more than
-    // it saves.  Walked twice and recorded, us, over 18 fields of 1D to 4D: 16
-    // steps and more 158 and 105, 270 and 156; 4 to 11 steps 251 and 196, 109 and
-    // 94, 84 and 74, 64 and 58 (one of six equal); 1 to 3 steps 608 and 680, 140
-    // and 143, 50 and 51
-    return s < 4 ? 0u : (uint32_t)(s < (int64_t)kRecSteps ? s : (int64_t)kRecSteps);
+    // it saves.  Walked twice and recorded, us, over 25 fields of 1D to 4D: 16
+    // steps and more 158 and 105, 270 and 156; 4 to 15 steps gain on large
+    // fields (256^3 251 and 196, 2000^2 109 and 94) and lose on small ones (17 x
+    // 300 x 300 40 and 47, 300^2 30 and 36); 1 to 3 steps 608 and 680, 140 and 143
+    return s < 16 ? 0u : (uint32_t)(s < (int64_t)kRecSteps ? s : (int64_t)kRecSteps);
 }
 
 // Paths and path vertices of every saddle of the block's chunk (kept for the
