@@ -75,7 +75,7 @@ typedef enum eg_status {
 #define EG_H_NARC 3   /* number of arcs (required size of arc_maxima[]); -1 if unknown */
 #define EG_H_NPAIRS 4 /* number of (saddle, upper-link component) pairs, the sum of beta; -1 if unknown */
 #define EG_H_PASSES 5 /* most sweeps over the labels, of an untiled grid or with a capped exit list (diagnostic) */
-#define EG_H_EXITS 6  /* tile exit-list entries the labels used (diagnostic) */
+#define EG_H_EXITS 6  /* exit-list entries that the tiles asked for (diagnostic) */
 #define EG_H_SLOTS 8
 
 /*
